@@ -161,14 +161,14 @@ template <class T>
 using EdgeVec = std::vector<T, NoInit<T>>;
 
 struct HostImages {
-    std::vector<int32_t> in_rp, outdeg, tile_row, pr_slot;
+    std::vector<int32_t> in_rp, outdeg, tile_row, slot;
     EdgeVec<int32_t> in_col, pr_src;
     EdgeVec<uint32_t> in_w;
+    EdgeVec<uint2> in_adj;
     std::vector<int32_t> sym_rp;
     EdgeVec<int32_t> sym_col;
-    EdgeVec<uint2> pull_w, pull_sym;
-    std::vector<uint4> pull_w_units, pull_sym_units;
-    PullSlices pull_w_off{}, pull_sym_off{};
+    std::vector<int32_t> in_blk;
+    std::vector<uint4> pull_segs, sym_segs;
     std::vector<uint32_t> rem_out, rem_any, master, master_rep;
 };
 
@@ -182,7 +182,7 @@ static gx_status validate(const gx_graph_desc *d) {
                GX_EINVAL, "pr_tile_edges=%u not 0, 256, 512, 1024 or 2048", d->pr_tile_edges);
     GX_REQUIRE(d->needs != 0 && (d->needs & ~7u) == 0, GX_EINVAL, "needs=%u invalid", d->needs);
     // the symmetric image holds up to two entries per directed edge, indexed by int32 row pointers
-    GX_REQUIRE(!(d->needs & GX_NEED_SYM) || 2 * d->E <= (int64_t)INT32_MAX - PULL_VT * 64, GX_EINVAL,
+    GX_REQUIRE(!(d->needs & GX_NEED_SYM) || 2 * d->E <= (int64_t)INT32_MAX - 512, GX_EINVAL,
                "E=%lld too large for the symmetric (CC) image: 2E must stay below 2^31", (long long)d->E);
     GX_REQUIRE(d->row_ptr || d->V == 0, GX_EINVAL, "row_ptr is NULL");
     GX_REQUIRE(d->col || d->E == 0, GX_EINVAL, "col is NULL");
@@ -312,26 +312,30 @@ static void build_in_csr(const gx_graph_desc *d, HostImages &h) {
     });
 }
 
-// PageRank contribution slots: the PR_HOT vertices with the most out-edges
-// (ties by id) take slots 0.. in that order, the others follow in id order,
-// so the gathers of hub contributions fall on a few cache lines.
-static void build_pr_slots(const gx_graph_desc *d, HostImages &h) {
-    const int64_t V = d->V, E = d->E;
-    const int64_t K = std::min<int64_t>(V, PR_HOT);
-    std::vector<int32_t> ids(V);
-    for (int64_t v = 0; v < V; v++) ids[v] = (int32_t)v;
-    auto deg = [d](int32_t v) { return d->row_ptr[v + 1] - d->row_ptr[v]; };
-    auto hotter = [&](int32_t a, int32_t b) { return deg(a) != deg(b) ? deg(a) > deg(b) : a < b; };
-    std::partial_sort(ids.begin(), ids.begin() + K, ids.end(), hotter);
-    h.pr_slot.assign(V, -1);
-    for (int64_t i = 0; i < K; i++) h.pr_slot[ids[i]] = (int32_t)i;
+// Slots: the HOT_SLOTS vertices with the most out-edges (ties by id) take
+// slots 0.. in that order, the others follow in id order, so what is gathered
+// from hubs falls on a few cache lines.
+static void build_slots(const gx_graph_desc *d, HostImages &h) {
+    const int64_t V = d->V;
+    const int64_t K = std::min<int64_t>(V, HOT_SLOTS);
+    auto deg = [d](int64_t v) { return d->row_ptr[v + 1] - d->row_ptr[v]; };
+    // vertices per degree, then the first slot of every degree, largest first
+    int32_t top = 0;
+    for (int64_t v = 0; v < V; v++) top = std::max(top, deg(v));
+    std::vector<int64_t> at((size_t)top + 2, 0);
+    for (int64_t v = 0; v < V; v++) at[deg(v)]++;
+    int64_t acc = 0;
+    for (int32_t x = top; x >= 0; x--) {
+        const int64_t n = at[x];
+        at[x] = acc;
+        acc += n;
+    }
+    h.slot.resize(V);
     int64_t next = K;
-    for (int64_t v = 0; v < V; v++)
-        if (h.pr_slot[v] < 0) h.pr_slot[v] = (int32_t)next++;
-    h.pr_src.resize(E);
-    parallel_for(E, [&](int64_t lo, int64_t hi) {
-        for (int64_t e = lo; e < hi; e++) h.pr_src[e] = h.pr_slot[h.in_col[e]];
-    });
+    for (int64_t v = 0; v < V; v++) {
+        const int64_t s = at[deg(v)]++;
+        h.slot[v] = (int32_t)(s < K ? s : next++);
+    }
 }
 
 // Pull tiles: tile t covers edges [t*T, (t+1)*T) of a CSR and owns the rows
@@ -360,87 +364,75 @@ static void build_tiles(const std::vector<int32_t> &rp, std::vector<int32_t> &ti
     tile_row[nt] = (int32_t)V;
 }
 
-// Pull records from a CSR over destinations (rows) listing sources in
-// ascending order.  Destinations are taken in blocks of
-// 2^PULL_SLICE_SHIFT and dealt to PULL_SLICES * S bins greedily, heaviest
-// in-edge count first, each to the lightest bin so far (degree skew would
-// otherwise pile most edges onto one bin).  Bin j belongs to XCD slice
-// j mod PULL_SLICES; S is chosen so a bin's destination values fit
-// PULL_BIN_BYTES, and an XCD sweeps its S bins one after another.  Within a
-// bin the records are grouped by source band, keeping the (destination,
-// source) order of the CSR inside a group; every group is padded to whole
-// PULL_VT records with sentinels (destination PULL_SENTINEL) and cut into
-// units of at most PULL_UNIT records.  Weighted records are
-// {dst, (src mod PULL_BAND) << 8 | w}: the unit names the band, so a source
-// takes 12 bits and any vertex count fits; with `w` null they are {dst, src}
-// (sentinel source: the band base).
-static void build_pull(const std::vector<int32_t> &rp, const int32_t *src, const uint32_t *w,
-                       EdgeVec<uint2> &out, std::vector<uint4> &units, PullSlices &sl) {
-    const int64_t V = (int64_t)rp.size() - 1;
-    const int64_t nb = (V >> PULL_BAND_BITS) + 1;
-    const int64_t nbin = pull_bins(V), S = nbin / PULL_SLICES;
-    const int64_t nblk = (V + (1 << PULL_SLICE_SHIFT) - 1) >> PULL_SLICE_SHIFT;
-    std::vector<int64_t> bcnt((size_t)nblk, 0);
-    for (int64_t v = 0; v < V; v++) bcnt[v >> PULL_SLICE_SHIFT] += rp[v + 1] - rp[v];
-    std::vector<int64_t> order((size_t)nblk);
-    for (int64_t i = 0; i < nblk; i++) order[i] = i;
-    std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) { return bcnt[a] > bcnt[b]; });
-    // group index of block b's bin: slices are contiguous, their bins in order
-    std::vector<int32_t> group((size_t)nblk, 0);
-    std::vector<int64_t> load((size_t)nbin, 0);
-    for (int64_t b : order) {
-        int64_t j = 0;
-        for (int64_t y = 1; y < nbin; y++)
-            if (load[y] < load[j]) j = y;
-        load[j] += bcnt[b];
-        group[b] = (int32_t)((j % PULL_SLICES) * S + j / PULL_SLICES);
+// The segments of the rows with more than PULL_SMALL entries.
+static void build_segs(const std::vector<int32_t> &rp, std::vector<uint4> &segs) {
+    segs.clear();
+    for (size_t v = 0; v + 1 < rp.size(); v++) {
+        if (rp[v + 1] - rp[v] <= PULL_SMALL) continue;
+        for (int32_t e = rp[v]; e < rp[v + 1]; e += PULL_SEG)
+            segs.push_back(make_uint4((uint32_t)v, (uint32_t)e, (uint32_t)std::min(rp[v + 1], e + PULL_SEG), 0u));
     }
-    const int64_t ng = nbin * nb;
-    std::vector<int64_t> cnt((size_t)ng, 0);
-    // one thread per slice: it owns the groups of its bins, so the counts and
-    // the fill below need no shared counters
-    auto per_slice = [&](auto &&body) {
-        std::vector<std::thread> th;
-        for (int x = 0; x < PULL_SLICES; x++)
-            th.emplace_back([&, x] {
-                const int64_t glo = x * S, ghi = (x + 1) * S;
-                for (int64_t v = 0; v < V; v++) {
-                    const int64_t gb = group[v >> PULL_SLICE_SHIFT];
-                    if (gb >= glo && gb < ghi) body(v, gb * nb);
-                }
-            });
-        for (auto &t : th) t.join();
-    };
-    per_slice([&](int64_t v, int64_t g0) {
-        for (int32_t e = rp[v]; e < rp[v + 1]; e++) cnt[g0 + (src[e] >> PULL_BAND_BITS)]++;
-    });
-    std::vector<int64_t> pos((size_t)ng + 1, 0);
-    for (int64_t g = 0; g < ng; g++) pos[g + 1] = pos[g] + (cnt[g] + PULL_VT - 1) / PULL_VT * PULL_VT;
-    out.resize((size_t)pos[ng]);  // every slot is written below: a record or a sentinel
-    for (int64_t g = 0; g < ng; g++) {  // sentinels: a source inside their band, weight 0
-        const uint32_t bb = (uint32_t)((g % nb) << PULL_BAND_BITS);
-        for (int64_t i = pos[g] + cnt[g]; i < pos[g + 1]; i++) out[i] = make_uint2(PULL_SENTINEL, w ? 0u : bb);
-    }
-    std::vector<int64_t> fill(pos.begin(), pos.end() - 1);
-    per_slice([&](int64_t v, int64_t g0) {
-        for (int32_t e = rp[v]; e < rp[v + 1]; e++) {
-            const uint32_t u = (uint32_t)src[e];
-            out[fill[g0 + (u >> PULL_BAND_BITS)]++] =
-                make_uint2((uint32_t)v, w ? (((u & (PULL_BAND - 1)) << 8) | w[e]) : u);
-        }
-    });
-    units.clear();
-    for (int x = 0; x < PULL_SLICES; x++) {
-        sl.uoff[x] = (int64_t)units.size();
-        for (int64_t g = x * S * nb; g < (x + 1) * S * nb; g++)
-            for (int64_t s0 = pos[g]; s0 < pos[g + 1]; s0 += PULL_UNIT)
-                units.push_back(make_uint4((uint32_t)s0, (uint32_t)std::min<int64_t>(PULL_UNIT, pos[g + 1] - s0),
-                                           (uint32_t)((g % nb) << PULL_BAND_BITS), 0u));
-    }
-    sl.uoff[PULL_SLICES] = (int64_t)units.size();
 }
 
-static bool banded_weights_fit(const gx_graph_desc *d) {
+// A row of the SSSP pull by ascending weight, weights of at most 8 bits: counted over the 256 weights (rows here are longer than
+// PULL_SMALL).
+static void row_by_weight(const int32_t *src, const int32_t *slot, const uint32_t *w, int32_t n, uint32_t tag,
+                          uint2 *out) {
+    int32_t at[257] = {};
+    for (int32_t i = 0; i < n; i++) at[w[i] + 1]++;
+    for (int i = 0; i < 256; i++) at[i + 1] += at[i];
+    for (int32_t i = 0; i < n; i++) out[at[w[i]]++] = make_uint2((uint32_t)slot[src[i]], tag | w[i]);
+}
+
+// In-edges of the SSSP pull, {source slot, (destination mod 64) << 8 | weight}:
+// the entries of short rows first, in row order (blk_ptr: where every block
+// of 64 rows starts), then the long rows by ascending weight, cut into
+// segments.
+static void build_in_adj(HostImages &h) {
+    const int64_t V = (int64_t)h.in_rp.size() - 1, E = h.in_rp[V];
+    const std::vector<int32_t> &rp = h.in_rp;
+    h.in_adj.resize(E);
+    h.in_blk.assign((size_t)(V + 63) / 64 + 1, 0);
+    EdgeVec<int32_t> off(V), seg(V);  // first entry (and segment) of every row
+    int32_t at = 0;
+    for (int64_t v = 0; v < V; v++) {
+        if ((v & 63) == 0) h.in_blk[v >> 6] = at;
+        off[v] = at;
+        const int32_t n = rp[v + 1] - rp[v];
+        if (n <= PULL_SMALL) at += n;
+    }
+    h.in_blk.back() = at;
+    h.pull_segs.clear();
+    for (int64_t v = 0; v < V; v++) {
+        const int32_t n = rp[v + 1] - rp[v];
+        if (n <= PULL_SMALL) continue;
+        off[v] = at;
+        seg[v] = (int32_t)h.pull_segs.size();
+        for (int32_t e = 0; e < n; e += PULL_SEG)
+            h.pull_segs.push_back(
+                make_uint4((uint32_t)v, (uint32_t)(at + e), (uint32_t)(at + std::min(n, e + PULL_SEG)), 0u));
+        at += n;
+    }
+    std::atomic<int64_t> next{0};  // rows differ in length: blocks are handed out one at a time
+    const int64_t step = 4096;
+    parallel_for(host_threads(), [&](int64_t, int64_t) {
+        for (int64_t lo; (lo = next.fetch_add(step)) < V;)
+            for (int64_t v = lo; v < std::min(V, lo + step); v++) {
+                const int32_t e0 = rp[v], n = rp[v + 1] - e0;
+                const uint32_t tag = (uint32_t)(v & 63) << 8;
+                if (n > PULL_SMALL) {
+                    row_by_weight(&h.in_col[e0], h.slot.data(), &h.in_w[e0], n, tag, &h.in_adj[off[v]]);
+                    for (int32_t e = 0, i = seg[v]; e < n; e += PULL_SEG, i++)
+                        h.pull_segs[i].w = h.in_adj[off[v] + e].y & 0xFFu;
+                    continue;
+                }
+                for (int32_t i = 0; i < n; i++)
+                    h.in_adj[off[v] + i] = make_uint2((uint32_t)h.slot[h.in_col[e0 + i]], tag | h.in_w[e0 + i]);
+            }
+    }, 2);
+}
+
+static bool byte_weights(const gx_graph_desc *d) {
     std::atomic<bool> ok{true};
     parallel_for(d->E, [&](int64_t lo, int64_t hi) {
         for (int64_t e = lo; e < hi; e++)
@@ -520,17 +512,17 @@ static void layout(const gx_graph_desc *desc, int64_t E_sym, Carver &c, DevGraph
         d->in_col = c.take<int32_t>(E);
         d->outdeg = c.take<int32_t>(V);
         d->pr_src = c.take<int32_t>(E);
-        d->pr_slot = c.take<int32_t>(V);
     }
-    if ((desc->needs & GX_NEED_OUT) && (desc->E == 0 || banded_weights_fit(desc))) {
-        d->pull_w = c.take<uint2>(pull_rec_cap(V, E));
-        d->pull_w_units = c.take<uint4>(pull_unit_cap(V, E));
+    if (desc->needs & (GX_NEED_IN | GX_NEED_OUT)) d->slot = c.take<int32_t>(V);
+    if ((desc->needs & GX_NEED_OUT) && (desc->E == 0 || byte_weights(desc))) {
+        d->in_adj = c.take<uint2>(E);
+        d->in_blk = c.take<int32_t>((V + 63) / 64 + 1);
+        d->pull_segs = c.take<uint4>(pull_seg_cap(E));
     }
     if (desc->needs & GX_NEED_SYM) {
         d->sym_rp = c.take<int32_t>(V + 1);
         d->sym_col = c.take<int32_t>(E_sym);
-        d->pull_sym = c.take<uint2>(pull_rec_cap(V, E_sym));
-        d->pull_sym_units = c.take<uint4>(pull_unit_cap(V, E_sym));
+        d->sym_segs = c.take<uint4>(pull_seg_cap(E_sym));
     }
     if (desc->l2g) d->l2g = c.take<int32_t>(V);
     if (desc->outdeg_global) {
@@ -653,12 +645,17 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
     try {
         build_in_csr(desc, h);
         build_tiles(h.in_rp, h.tile_row, pr_tile_for(desc));
-        if (desc->needs & GX_NEED_IN) build_pr_slots(desc, h);
-        if ((desc->needs & GX_NEED_OUT) && (desc->E == 0 || banded_weights_fit(desc)))
-            build_pull(h.in_rp, h.in_col.data(), h.in_w.data(), h.pull_w, h.pull_w_units, h.pull_w_off);
+        if (desc->needs & (GX_NEED_IN | GX_NEED_OUT)) build_slots(desc, h);
+        if (desc->needs & GX_NEED_IN) {
+            h.pr_src.resize(desc->E);
+            parallel_for(desc->E, [&](int64_t lo, int64_t hi) {
+                for (int64_t e = lo; e < hi; e++) h.pr_src[e] = h.slot[h.in_col[e]];
+            });
+        }
+        if ((desc->needs & GX_NEED_OUT) && desc->E > 0 && byte_weights(desc)) build_in_adj(h);
         if (desc->needs & GX_NEED_SYM) {
             build_sym(desc, h);
-            build_pull(h.sym_rp, h.sym_col.data(), nullptr, h.pull_sym, h.pull_sym_units, h.pull_sym_off);
+            build_segs(h.sym_rp, h.sym_segs);
         }
         build_flags(desc, W, h);
     } catch (const std::bad_alloc &) {
@@ -673,10 +670,8 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
     GX_REQUIRE(g, GX_ENOMEM, "host allocation failed");
     Carver c(dev_arena, arena_bytes);
     layout(desc, (int64_t)h.sym_col.size(), c, &g->d);
-    g->d.pull_w_off = h.pull_w_off;
-    g->d.pull_sym_off = h.pull_sym_off;
-    for (const uint4 &u : h.pull_w_units) g->pull_w_recs.push_back(u.y);
-    for (const uint4 &u : h.pull_sym_units) g->pull_sym_recs.push_back(u.y);
+    g->d.pull_nsegs = (int64_t)h.pull_segs.size();
+    g->d.sym_nsegs = (int64_t)h.sym_segs.size();
     g->needs = desc->needs;
     g->arena = dev_arena;
     g->arena_bytes = arena_bytes;
@@ -715,21 +710,19 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
         e = up.put_array((void *)d.in_col, h.in_col.data(), E * 4);
         if (e == hipSuccess) e = up.put_array((void *)d.outdeg, g->host_outdeg.data(), V * 4);
         if (e == hipSuccess) e = up.put_array((void *)d.pr_src, h.pr_src.data(), E * 4);
-        if (e == hipSuccess) e = up.put_array((void *)d.pr_slot, h.pr_slot.data(), V * 4);
     }
-    if (e == hipSuccess && d.pull_w) {
-        e = up.put_array((void *)d.pull_w, h.pull_w.data(), h.pull_w.size() * sizeof(uint2));
+    if (e == hipSuccess && d.slot) e = up.put_array((void *)d.slot, h.slot.data(), V * 4);
+    if (e == hipSuccess && d.in_adj && !h.in_adj.empty()) {
+        e = up.put_array((void *)d.in_blk, h.in_blk.data(), h.in_blk.size() * 4);
+        if (e == hipSuccess) e = up.put_array((void *)d.in_adj, h.in_adj.data(), h.in_adj.size() * sizeof(uint2));
         if (e == hipSuccess)
-            e = up.put_array((void *)d.pull_w_units, h.pull_w_units.data(), h.pull_w_units.size() * sizeof(uint4));
+            e = up.put_array((void *)d.pull_segs, h.pull_segs.data(), h.pull_segs.size() * sizeof(uint4));
     }
     if (e == hipSuccess && d.sym_rp) {
         e = up.put_array((void *)d.sym_rp, h.sym_rp.data(), (V + 1) * 4);
         if (e == hipSuccess) e = up.put_array((void *)d.sym_col, h.sym_col.data(), h.sym_col.size() * 4);
         if (e == hipSuccess)
-            e = up.put_array((void *)d.pull_sym, h.pull_sym.data(), h.pull_sym.size() * sizeof(uint2));
-        if (e == hipSuccess)
-            e = up.put_array((void *)d.pull_sym_units, h.pull_sym_units.data(),
-                             h.pull_sym_units.size() * sizeof(uint4));
+            e = up.put_array((void *)d.sym_segs, h.sym_segs.data(), h.sym_segs.size() * sizeof(uint4));
     }
     if (e == hipSuccess && d.l2g) e = up.put_array((void *)d.l2g, desc->l2g, V * 4);
     if (e == hipSuccess && d.outdeg_g) e = up.put_array((void *)d.outdeg_g, desc->outdeg_global, V * 4);

@@ -62,41 +62,31 @@ struct Carver {
 // Edge tile of the PageRank pull (in-edges per workgroup tile): PR_BLOCK
 // threads times 1, 2, 4 or 8 edges, chosen per graph at load.
 constexpr int PR_BLOCK = 256;
-// Contribution slots of the hottest sources, contiguous at the front: 2 MiB
-// of fp32, which a workgroup's L2 keeps while the in-edges stream past (on
-// R-MAT graphs they are the sources of about 70% of the in-edges).
-constexpr int64_t PR_HOT = int64_t(1) << 19;
+// What is gathered per in-edge from its source (PageRank contributions, SSSP
+// values) lives in slots: the HOT_SLOTS vertices with the most out-edges
+// first, 2 MiB of 4-byte values that an L2 keeps while the in-edges stream
+// past (on R-MAT graphs they are the sources of 70 to 93% of the in-edges).
+constexpr int64_t HOT_SLOTS = int64_t(1) << 19;
 constexpr int PR_TILE_MAX = PR_BLOCK * 8;
-// Records of the SSSP / CC pull.  Destinations are dealt to PULL_SLICES
-// slices in blocks of 2^PULL_SLICE_SHIFT vertices, balanced by in-edge
-// count; a slice is a sequence of bins of at most PULL_BIN_BYTES of
-// destination values; a bin's records are grouped by source band
-// (source >> PULL_BAND_BITS) and ordered by (destination, source) inside a
-// group.  Groups are padded to whole PULL_VT records with sentinels and cut
-// into work units of at most PULL_UNIT records.  The workgroups of a pull
-// take the units of the slice of the XCD they run on (slice x belongs to XCD
-// x of the 8), so each XCD's L2 holds one bin's destination values, and a
-// unit's band of source snapshots (PULL_BAND words) is staged in LDS.
+// Row pull of SSSP / CC: rows of at most PULL_SMALL entries are taken in
+// blocks, longer ones in segments of at most PULL_SEG entries from a table
+// built at load.  The rows (and the segments) are dealt to PULL_SLICES slices
+// in runs of blocks; a launch's workgroups take the slice of the XCD they run
+// on.
 constexpr int PULL_SLICES = 8;
-constexpr int PULL_SLICE_SHIFT = 6;
-constexpr int64_t PULL_BIN_BYTES = int64_t(2) << 20;  // destination values an XCD sweeps at a time
-constexpr int PULL_BAND_BITS = 13;  // 8192 sources: 32 KB of snapshots in LDS
-constexpr int PULL_BAND = 1 << PULL_BAND_BITS;
-constexpr int PULL_VT = 8;       // records per thread and group padding
-constexpr int PULL_UNIT = 8192;  // records per work unit at most (a multiple of PULL_VT)
-constexpr uint32_t PULL_SENTINEL = 0xFFFFFFFFu;  // destination of a padding record
-struct PullSlices {
-    int64_t uoff[PULL_SLICES + 1];  // slice x owns work units uoff[x] .. uoff[x+1]-1
-};
-// Capacity of the record array and of the unit table (upper bounds, known
-// before the layout is built).
-inline int64_t pull_bins(int64_t V) {
-    return PULL_SLICES *
-           std::max<int64_t>(1, (V * 4 + PULL_SLICES * PULL_BIN_BYTES - 1) / (PULL_SLICES * PULL_BIN_BYTES));
-}
-inline int64_t pull_groups(int64_t V) { return pull_bins(V) * ((V >> PULL_BAND_BITS) + 1); }
-inline int64_t pull_rec_cap(int64_t V, int64_t E) { return E + (PULL_VT - 1) * pull_groups(V) + PULL_VT; }
-inline int64_t pull_unit_cap(int64_t V, int64_t E) { return pull_rec_cap(V, E) / PULL_UNIT + pull_groups(V) + 1; }
+constexpr int PULL_SMALL = 32;
+constexpr int PULL_SEG = 256;
+constexpr int PULL_BLOCK = 256;     // rows a workgroup takes at a time (one per thread)
+constexpr int PULL_SEG_BLOCK = 64;  // segments (16 per wave)
+constexpr int PULL_RUN_LOG = 2;     // blocks per run (1 below PULL_RUN_FROM blocks, to reach every XCD)
+constexpr int PULL_RUN_FROM = 2048;
+// SSSP: slots whose frontier bits a pulling workgroup keeps in LDS (16 KiB;
+// on R-MAT scale 22 the sources of 75% of the in-edges).
+constexpr int PULL_BITS = 1 << 17;
+constexpr int PULL_BIT_WORDS = PULL_BITS / 32;
+// Capacity of the segment table of E entries (known before the rows are: a
+// row in it has more than PULL_SMALL entries).
+inline int64_t pull_seg_cap(int64_t E) { return E / PULL_SMALL + 1; }
 
 // Label propagation: vertices are grouped by the number of distinct
 // neighbours d.  Classes 0..4 take d <= 4, 8, 16, 32, 64 and run as lane
@@ -120,28 +110,30 @@ struct DevGraph {
     const int32_t *in_rp = nullptr;
     const int32_t *in_col = nullptr;
     const int32_t *outdeg = nullptr;
-    // PageRank contributions live in slots: the PR_HOT sources with the most
-    // out-edges first (by out-degree, then id), every other vertex after them
-    // in id order.  pr_src = the slot of each in-edge's source, pr_slot = the
-    // slot of each vertex.
+    // slot[v]: where vertex v's gathered values live, the HOT_SLOTS vertices
+    // with the most out-edges first (by out-degree, then id), every other
+    // vertex after them in id order; pr_src = the slot of each in-edge's source
     const int32_t *pr_src = nullptr;
-    const int32_t *pr_slot = nullptr;
+    const int32_t *slot = nullptr;
     int32_t pr_tile = PR_TILE_MAX;  // in-edges per PageRank tile
     int32_t pr_ntiles = 0;
     const int32_t *pr_tile_row = nullptr;  // [pr_ntiles + 1]
-    // sliced, banded in-edge records for the SSSP pull:
-    // {dst, (src mod PULL_BAND) << 8 | w} (padded to whole PULL_VT groups);
-    // null when a weight exceeds 255 (the engine then only pushes)
-    const uint2 *pull_w = nullptr;
-    const uint4 *pull_w_units = nullptr;  // {first record, records, band base, 0}
-    PullSlices pull_w_off{};
-    // symmetric adjacency (CC push and pull) and its equal edge tiles
+    // in-edges of the SSSP pull, {source slot, (destination mod 64) << 8 | weight}:
+    // the entries of the rows of at most PULL_SMALL, in row order (block b of
+    // 64 rows owns in_blk[b] .. in_blk[b + 1]), then the longer rows, each by
+    // ascending weight; null when a weight exceeds 255 (the engine
+    // then only pushes).  pull_segs: {row, first entry, end entry, first
+    // weight} of the long rows.
+    const uint2 *in_adj = nullptr;
+    const int32_t *in_blk = nullptr;
+    const uint4 *pull_segs = nullptr;
+    int64_t pull_nsegs = 0;
+    // symmetric adjacency (CC push and pull, neighbours ascending) and the
+    // segments of its long rows
     const int32_t *sym_rp = nullptr;
     const int32_t *sym_col = nullptr;
-    // sliced, banded symmetric records for the CC pull: {dst, src}
-    const uint2 *pull_sym = nullptr;
-    const uint4 *pull_sym_units = nullptr;
-    PullSlices pull_sym_off{};
+    const uint4 *sym_segs = nullptr;
+    int64_t sym_nsegs = 0;
     // partition metadata
     const int32_t *l2g = nullptr;          // nullptr = identity
     const uint32_t *remote_out = nullptr;  // bitmaps of W words (nullptr = none remote)
@@ -165,7 +157,6 @@ struct gx_graph {
     bool dev_error = false;
     std::vector<int32_t> host_outdeg;  // out-degree (host copy, for sources and stats)
     std::vector<int32_t> host_symdeg;  // distinct neighbours (with GX_NEED_SYM; label propagation classes)
-    std::vector<uint32_t> pull_w_recs, pull_sym_recs;  // records of each pull unit (sizes fix-up regions)
     // supersteps of the last converged SSSP / CC run on this graph: the size
     // of the next run's first speculative group (solves on one graph tend to
     // need similar superstep counts)
@@ -207,7 +198,9 @@ struct DevStep {
     unsigned long long rot_mixed; // pull: 1 when its workgroups saw different XCD rotations
     unsigned long long spare0[12];
     unsigned long long frontier;  // |F_k|
-    unsigned long long spare1[15];
+    uint32_t inv_min;             // ~(smallest active value), so that a cleared slot says "none"
+    uint32_t pad1;
+    unsigned long long spare1[14];
 };
 static_assert(sizeof(DevStep) == 256, "DevStep spans two 128-byte lines");
 constexpr int STEP_RING = 4096;
@@ -233,17 +226,17 @@ struct gx_state {
     bool dev_error = false;
     int relax_grid = 0;   // persistent grid of the relaxation kernel
     uint32_t xcd_shift = 0;  // added to the XCD a workgroup is expected on (non-zero only to exercise the check)
-    uint2 *fix = nullptr;         // fix-up regions, fix_cap entries per relaxation workgroup
-    uint32_t *fixn = nullptr;     // entries recorded per workgroup
-    uint32_t fix_cap = 0;
+    uint32_t *rot = nullptr;      // XCD rotation each workgroup of the last pull saw
     // SSSP / CC
     uint32_t *val = nullptr;
     uint8_t *front8[2] = {nullptr, nullptr};  // frontier byte maps: A_k lives in front8[k & 1]
     uint8_t *dirty8 = nullptr;                // changed since the last sync (byte per vertex)
     uint4 *list = nullptr;
     uint32_t *tile_start = nullptr;
-    uint32_t *snap = nullptr;      // start-of-superstep values of active vertices (pull)
+    uint32_t *snap = nullptr;      // start-of-superstep values of every vertex (pull; SSSP: by slot)
+    uint32_t *hot[2] = {nullptr, nullptr};  // SSSP: at least A_k's bits of the first PULL_BITS slots, hot[k & 1]
     uint32_t pull_edges = 0xFFFFFFFFu;
+    bool merged = false;           // other parts' values were merged (gx_apply_delta)
     // PageRank
     float *x[2] = {nullptr, nullptr};
     float *contrib[2] = {nullptr, nullptr};

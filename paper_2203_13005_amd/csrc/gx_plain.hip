@@ -16,13 +16,11 @@
 //               read; a candidate that passes marks the destination in the
 //               next frontier (a plain, idempotent byte store; the next
 //               compaction carries the marks into the dirty map).
-//   pull      : for large frontiers instead: one streaming sweep over all
-//               in-edge records, grouped by source band so the gathered
-//               snapshots are staged in LDS, 64 consecutive records per
-//               wave; improving candidates are stored plainly and recorded,
-//               and k_fixup re-applies the ones a racing store overwrote.
-//               The device picks push or pull from the frontier's out-edge
-//               count; no host round trip.
+//   pull      : for large frontiers instead: every row of in-edges (CC:
+//               neighbours) takes the minimum over its entries itself, in an
+//               order that lets it stop early, and is its value's only
+//               writer.  The device picks push or pull from the frontier's
+//               out-edge count; no host round trip.
 //   k_compact : frontier byte map A_{k+1} -> active list of (edge offset,
 //               CSR base, snapshot) for active vertices with out-edges; one
 //               64-bit atomic per workgroup reserves list slots and edge
@@ -72,11 +70,12 @@ namespace {
 
 // ------------------------------------------------------------ SSSP / CC
 
-__global__ __launch_bounds__(256) void k_min_init(uint32_t *val, uint8_t *f0, uint8_t *f1, uint8_t *dirty,
-                                                  const int32_t *l2g, const int32_t *rp, int64_t V, int32_t algo,
-                                                  int32_t source, DevStep *step0) {
+__global__ __launch_bounds__(256) void k_min_init(uint32_t *val, uint32_t *snap, uint8_t *f0, uint8_t *f1,
+                                                  uint8_t *dirty, const int32_t *l2g, const int32_t *rp, int64_t V, int32_t algo,
+                                                  int32_t source, DevStep *step0, uint32_t *hot0, uint32_t *hot1) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i == 0) *step0 = DevStep{};
+    if (i < PULL_BIT_WORDS && hot0) hot0[i] = hot1[i] = 0u;
     if (i < V) {
         uint32_t x;
         uint8_t f;
@@ -88,6 +87,7 @@ __global__ __launch_bounds__(256) void k_min_init(uint32_t *val, uint8_t *f0, ui
             f = i == source;
         }
         val[i] = x;
+        snap[i] = algo == GX_CC ? x : INF;  // (by slot for SSSP: the source's is written when it is compacted)
         f0[i] = f;
         f1[i] = 0;
         dirty[i] = 0;
@@ -103,31 +103,51 @@ __global__ __launch_bounds__(256) void k_min_init(uint32_t *val, uint8_t *f0, ui
 // vertices with out-edges get a list entry (edge offset, CSR base,
 // snapshot, vertex) and the tiles that start inside an entry's edges record
 // it.  When the next superstep may pull (snap_all), threads with an active
-// vertex also store their vertices' values as snapshots (the pull stages
-// them with the frontier map and treats inactive sources as INF).  |A_{k+1}|
-// is the number of vertices superstep k changed.
+// vertex also store their vertices' values as snapshots, and the smallest
+// active value is left in the step: a value changes only when its vertex is
+// active next, so after every compaction `snap` holds the value of every
+// vertex at the start of the superstep (k_min_init wrote the first ones).
+// |A_{k+1}| is the number of vertices superstep k changed.
 constexpr int CVT = 16;
 // Threads per compaction workgroup: each workgroup makes one list
 // reservation (an add with return on a single counter, which serialises
 // across workgroups), so fewer, larger workgroups shorten that chain.
 constexpr int CBLOCK = 1024;
 
+// Flags the superstep if the workgroups of its pull saw different XCD
+// rotations (one workgroup of the launch that follows the pull calls this).
+__device__ __forceinline__ void check_rotations(DevStep *step, const uint32_t *__restrict__ rot, int n) {
+    if (step->pad == 0) return;  // it pushed
+    const uint32_t r0 = rot[0];
+    bool mixed = false;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) mixed |= rot[i] != r0;
+    if (mixed) step->rot_mixed = 1ull;
+}
+
 __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ front, uint8_t *__restrict__ front_clear,
                                                  const int32_t *__restrict__ rp, const uint32_t *__restrict__ val,
                                                  uint32_t *__restrict__ snap, int64_t V,
                                                  uint4 *__restrict__ list, uint32_t *__restrict__ tile_start,
                                                  DevStep *__restrict__ step, DevStep *__restrict__ next_step,
-                                                 int snap_all, const DevStep *__restrict__ prev,
-                                                 uint8_t *__restrict__ dirty, uint32_t pull_edges) {
+                                                 int snap_all, DevStep *__restrict__ prev,
+                                                 uint8_t *__restrict__ dirty, uint32_t pull_edges,
+                                                 const uint32_t *__restrict__ rot, int nrot,
+                                                 const int32_t *__restrict__ slot, uint32_t *__restrict__ hot,
+                                                 uint32_t *__restrict__ hot_clear) {
     __shared__ unsigned long long s_scan[CBLOCK / 64];
     __shared__ unsigned long long s_base;
     __shared__ int s_nf[CBLOCK / 64];
+    __shared__ uint32_t s_min[CBLOCK / 64];
     const int tid = threadIdx.x;
     if (blockIdx.x == 0 && tid == 0) *next_step = DevStep{};
+    if (blockIdx.x == 0 && prev != nullptr) check_rotations(prev, rot, nrot);
     // The previous superstep had no active vertex: nothing was relaxed, the
     // map read here is still the cleared one and the map cleared here is
     // empty, so A_{k+1} is empty without a sweep (its counters stay zero).
     if (prev != nullptr && prev->frontier == 0) return;
+    if (slot != nullptr)  // the bits of the superstep after the one compacted here
+        for (int64_t i = (int64_t)blockIdx.x * CBLOCK + tid; i < PULL_BIT_WORDS; i += (int64_t)gridDim.x * CBLOCK)
+            hot_clear[i] = 0u;
     const int64_t u0 = ((int64_t)blockIdx.x * CBLOCK + tid) * CVT;
     uint32_t actmask = 0;
     if (u0 < V) {  // byte maps are padded to whole 32-vertex words: the 16 bytes at u0 exist
@@ -175,10 +195,22 @@ __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ 
             }
         }
     }
-    // Snapshots for the pull: a thread with an active vertex stores the values
-    // of all its CVT vertices (the pull masks inactive sources with the
-    // frontier map, so whatever an inactive entry holds is never used).
-    if (snap_all && actmask) {
+    // Snapshots for the pull.  SSSP: the active vertices' values go to their
+    // slots, and their bits with them (a bit too many only costs a read).
+    // CC: a thread with an active vertex stores the values of all its CVT
+    // vertices (whole vectors; an inactive vertex's value is the one its
+    // snapshot holds already).
+    if (snap_all && actmask && slot != nullptr) {
+        int32_t sl[CVT];
+#pragma unroll
+        for (int i = 0; i < CVT; i++) sl[i] = slot[min(u0 + i, V - 1)];
+#pragma unroll
+        for (int i = 0; i < CVT; i++) {
+            if (!((actmask >> i) & 1u)) continue;
+            snap[sl[i]] = x[i];
+            if (sl[i] < PULL_BITS) atomicOr(&hot[sl[i] >> 5], 1u << (sl[i] & 31));
+        }
+    } else if (snap_all && actmask) {
         if (u0 + CVT <= V) {
             uint4 *s4 = reinterpret_cast<uint4 *>(snap + u0);
 #pragma unroll
@@ -189,28 +221,39 @@ __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ 
                 if (u0 + i < V) snap[u0 + i] = x[i];
         }
     }
-    uint32_t cnt = 0, edges = 0;
+    uint32_t cnt = 0, edges = 0, low = INF;
 #pragma unroll
     for (int i = 0; i < CVT; i++) {
         const int32_t dg = r[i + 1] - r[i];
         if (((actmask >> i) & 1u) && dg > 0) {
             cnt++;
             edges += (uint32_t)dg;
+            low = min(low, x[i]);
         }
     }
     unsigned long long mine = ((unsigned long long)cnt << 32) | edges, total;
     unsigned long long pre = block_excl_scan_u64(mine, &total, s_scan);
     int nf = __popc(actmask);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) nf += __shfl_down(nf, o, 64);
-    if ((tid & 63) == 0) s_nf[tid >> 6] = nf;
+    for (int o = 32; o > 0; o >>= 1) {
+        nf += __shfl_down(nf, o, 64);
+        low = min(low, (uint32_t)__shfl_down(low, o, 64));
+    }
+    if ((tid & 63) == 0) {
+        s_nf[tid >> 6] = nf;
+        s_min[tid >> 6] = low;
+    }
     if (tid == 0) s_base = total ? atomicAdd(&step->list, total) : 0ull;
     __syncthreads();
     if (tid == 0) {
         int nfb = 0;
 #pragma unroll
-        for (int w = 0; w < CBLOCK / 64; w++) nfb += s_nf[w];
+        for (int w = 0; w < CBLOCK / 64; w++) {
+            nfb += s_nf[w];
+            low = min(low, s_min[w]);
+        }
         atomicAdd(&step->frontier, (unsigned long long)nfb);
+        if (snap_all && low != INF) atomicMax(&step->inv_min, ~low);
     }
     // The out-edges counted up to this workgroup are a lower bound of the
     // frontier's: once it reaches pull_edges the next superstep pulls and
@@ -238,63 +281,6 @@ struct PushLds {
     int32_t own[PUSH_TILE];
     int32_t red[4];
 };
-
-// Where a pulling workgroup's improving candidates go.  A candidate below a
-// value read during the superstep is below the destination's start value
-// (values only fall), so the destination changes whatever else lands: it is
-// marked in the next frontier, its value is set with a plain store, and the
-// pair (destination, candidate) is appended to the workgroup's fix-up
-// region.  Plain stores racing on one destination may leave a larger
-// candidate; the fix-up kernel then re-applies every recorded candidate
-// still below the stored value with an atomic minimum.  Min atomics cost
-// several times a plain store here.  This is sound because every writer of
-// a destination in the pull runs on the XCD that owns the destination's
-// slice (one L2 sees all of its plain stores) and the fix-up is a later
-// launch; regions are sized for every record a workgroup can meet, so no
-// candidate bypasses them (plain stores and atomics on one word in one
-// kernel would not be ordered).
-// A relaxation workgroup leaves its fix-up count in the low bits of its word
-// and, from a pull, the XCD rotation it saw in the top three.
-constexpr int FIX_ROT_SHIFT = 29;
-
-struct FixRegion {
-    uint2 *ent;        // this workgroup's region
-    uint32_t cap;      // its capacity
-    uint32_t *count;   // LDS: candidates offered so far
-};
-
-template <int N>
-__device__ __forceinline__ void apply_hits(const uint32_t (&dst)[N], const uint32_t (&m)[N], uint32_t hits,
-                                           uint32_t *__restrict__ val, uint8_t *__restrict__ front_next,
-                                           const FixRegion &fr) {
-    // one LDS reservation per wave: lane-ordered, contiguous entries
-    const int lane = threadIdx.x & 63;
-    const uint32_t cnt = (uint32_t)__popc(hits);
-    uint32_t incl = cnt;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += y;
-    }
-    const uint32_t total = __shfl(incl, 63, 64);
-    uint32_t base = 0;
-    if (lane == 63 && total) base = atomicAdd(fr.count, total);
-    base = __shfl(base, 63, 64);
-    uint32_t pos = base + incl - cnt;
-#pragma unroll
-    for (int i = 0; i < N; i++) {
-        if ((hits >> i) & 1u) {
-            if (pos < fr.cap) {
-                fr.ent[pos] = make_uint2(dst[i], m[i]);
-                val[dst[i]] = m[i];
-            } else {
-                atomicMin(&val[dst[i]], m[i]);
-            }
-            front_next[dst[i]] = 1;
-            pos++;
-        }
-    }
-}
 
 template <bool WEIGHTED>
 __device__ __forceinline__ void push_body(const uint4 *__restrict__ list, const uint32_t *__restrict__ tile_start,
@@ -371,157 +357,268 @@ __device__ __forceinline__ void push_body(const uint4 *__restrict__ list, const 
     }
 }
 
-// Pull form of the same superstep, for large frontiers.  The in-edges are
-// stored as records {dst, (src mod PULL_BAND) << 8 | w} (CC: {dst, src}) in
-// work units of one destination slice and one band of PULL_BAND sources
-// (layout built at load).  A workgroup takes the units of the slice of the
-// XCD it runs on (the j-th workgroup of an XCD takes units j, j + grid/8,
-// ...), so each XCD's L2 holds its slice's destination values and every
-// writer of a destination shares that L2.  A unit's band of
-// snapshots is staged in LDS, INF where the frontier map A_k says the source
-// is inactive, so a record's gather is an LDS read.  The 64 lanes of a wave
-// take 64 consecutive records (destinations in ascending order), so lanes
-// whose destinations share a cache line make one memory request between
-// them: the destination reads, one per record, are what bounds the pull,
-// and wider bands make consecutive records' destinations denser.  A record
-// without a candidate (inactive source or padding) reads nothing: the
-// destination reads are buffer loads whose offset for such lanes lies past
-// the buffer, which fetches nothing and returns 0.  Lanes holding the same
-// destination each apply their candidate; the fix-up pass leaves the
-// minimum.  Runs only when the frontier's out-edges reach pull_edges (V * 4
-// must fit the 32-bit buffer range; the host enables the pull only then).
+// Pull form of the same superstep, for large frontiers: every row takes the
+// minimum over its in-edges (CC: its neighbours) of the values at the
+// superstep's start.  What an inactive source sends was merged into the row
+// when that source last changed, so no frontier test is needed per entry,
+// and a row needs only those of its entries that could still lower it: no
+// message is below `low`, the smallest active value, plus the entry's
+// weight.  A row is its value's only writer and stores plainly; the segments
+// of a long row, and a merge into an accumulator, use an atomic minimum.
+//
+// Long rows (segments), and every row of CC: one per thread is tested, the
+// survivors are queued in LDS and scanned by groups of G lanes, 2 G
+// consecutive entries at a time.  The entries of SSSP's long rows ascend by
+// weight, so a row ends at the first entry whose bound is not below the best
+// value found so far; a CC row ends as soon as it holds the smallest active
+// label (hubs reach it first and, in graphs whose ids go by degree, come
+// first in a row).
+// SSSP's short rows: a wave streams the entries of 64 rows, whatever rows
+// they belong to (an entry names its row within the 64), and takes the
+// minimum per row in LDS, so no load waits for another row's.
+// An entry whose source is not active (a bit in LDS for the sources with the
+// most out-edges) or whose bound is too large reads no value.
+//
+// Bound by the latency of dependent reads (entries, then values) and, in the
+// first pull of a solve, by the rate of random 4-byte reads.  R-MAT scale 22
+// (65 M in-edges), the six pulls of one solve: a sweep over every in-edge
+// record with racing stores and a fix-up pass took 250-280 us each; this one
+// 272, 197, 122, 95, 84 and 77 us.  Short rows of at most 16, 32, 64, 128:
+// 861, 847, 1060, 1104 us for the six.
+struct RowItems {
+    uint32_t row[64], beg[64], end[64], best[64];
+};
+
+struct PullArgs {
+    const int32_t *rp;      // CC: rows; SSSP: first entry of every block of 64 short rows
+    const void *adj;        // uint2 {source slot, (row mod 64) << 8 | weight} (SSSP) or int32 neighbour (CC)
+    const uint4 *segs;
+    int64_t nsegs;
+    int first_only;         // CC before anything changed: labels ascend with the neighbours, so the first decides
+    int atomic_rows;        // rows merge into an accumulator
+    const uint32_t *bound;  // values that messages must be below (the vertex values)
+    const uint32_t *hot;    // SSSP: frontier bits of the first slots
+};
+
+struct PullLds {
+    RowItems items[4];
+    uint32_t bits[PULL_BIT_WORDS];
+};
+
+// Whether slot `u` may be active (slots past the bits always may).
+__device__ __forceinline__ bool may_be_active(const uint32_t *bits, uint32_t u) {
+    return u >= (uint32_t)PULL_BITS || ((bits[u >> 5] >> (u & 31)) & 1u);
+}
+
+template <bool WEIGHTED, int G, int UN>
+__device__ __forceinline__ void scan_items(const RowItems &it, const uint32_t *bits, int n, const PullArgs &pa, uint32_t low,
+                                           const uint32_t *__restrict__ snap, uint32_t *tgt,
+                                           uint8_t *__restrict__ front_next, bool atomic) {
+    const int lane = threadIdx.x & 63, g = lane / G, gl = lane % G;
+    for (int i0 = 0; i0 < n; i0 += 64 / G) {
+        const int i = min(i0 + g, n - 1);
+        bool live = i0 + g < n;
+        const uint32_t row = it.row[i], end = it.end[i], start = it.best[i];
+        uint32_t p = it.beg[i] + (uint32_t)gl, best = start;
+        while (__any(live)) {
+            // (every load is unconditional, so the chunk's loads overlap)
+            uint32_t u[UN], w[UN], s[UN], bnd = INF, cand = INF;
+            bool take[UN];
+#pragma unroll
+            for (int j = 0; j < UN; j++) {
+                const uint32_t q = min(p + (uint32_t)(j * G), end - 1);
+                if (WEIGHTED) {
+                    const uint2 a = static_cast<const uint2 *>(pa.adj)[q];
+                    u[j] = a.x, w[j] = a.y & 0xFFu;
+                } else {
+                    u[j] = (uint32_t) static_cast<const int32_t *>(pa.adj)[q], w[j] = 0;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < UN; j++) {
+                bnd = live && p + (uint32_t)(j * G) < end ? sat_add(low, w[j]) : INF;
+                take[j] = bnd < best && (!WEIGHTED || may_be_active(bits, u[j]));
+                s[j] = snap[take[j] ? u[j] : row];
+            }
+#pragma unroll
+            for (int j = 0; j < UN; j++) cand = min(cand, take[j] ? sat_add(s[j], w[j]) : INF);
+#pragma unroll
+            for (int o = G / 2; o > 0; o >>= 1) cand = min(cand, (uint32_t)__shfl_xor(cand, o, 64));
+            best = min(best, cand);
+            // the chunk's last entry has its largest bound (INF past the row's end)
+            live = live && (uint32_t)__shfl(bnd, lane | (G - 1), 64) < best;
+            p += UN * G;
+        }
+        if (gl == 0 && i0 + g < n && best < start) {
+            if (atomic) atomicMin(&tgt[row], best);
+            else tgt[row] = best;
+            front_next[row] = 1;
+        }
+    }
+}
+
+// Queues the threads' rows (or segments) that pass the filter, a wave's in
+// its own LDS list; returns their number.
+__device__ __forceinline__ int queue_items(RowItems &it, bool take, uint32_t row, uint32_t beg, uint32_t end,
+                                           uint32_t best) {
+    const unsigned long long m = __ballot(take);
+    if (take) {
+        const int pos = __popcll(m & ((1ull << (threadIdx.x & 63)) - 1ull));
+        it.row[pos] = row;
+        it.beg[pos] = beg;
+        it.end[pos] = end;
+        it.best[pos] = best;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    return __popcll(m);
+}
+
+// The 64 rows of one wave, all short (SSSP): best[i] is row v0 + i's minimum.
+__device__ __forceinline__ void stream_rows(uint32_t *best, const uint32_t *bits, int64_t v, uint32_t cur, int32_t rp0,
+                                            int32_t rp1, const PullArgs &pa, uint32_t low,
+                                            const uint32_t *__restrict__ snap, uint32_t *tgt,
+                                            uint8_t *__restrict__ front_next) {
+    constexpr int UN = 4;
+    const int lane = threadIdx.x & 63;
+    const uint32_t beg = (uint32_t)rp0, end = (uint32_t)rp1;
+    if (!__any(low < cur) || beg == end) return;
+    const uint2 *adj = static_cast<const uint2 *>(pa.adj);
+    best[lane] = cur;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (uint32_t p0 = beg; p0 < end; p0 += 64 * UN) {
+        uint2 q[UN];
+        uint32_t s[UN];
+        bool take[UN];
+#pragma unroll
+        for (int j = 0; j < UN; j++) q[j] = adj[min(p0 + 64u * j + (uint32_t)lane, end - 1)];
+#pragma unroll
+        for (int j = 0; j < UN; j++) {  // (an entry past the end repeats the last one: harmless)
+            take[j] = sat_add(low, q[j].y & 0xFFu) < best[q[j].y >> 8] && may_be_active(bits, q[j].x);
+            s[j] = snap[take[j] ? q[j].x : (uint32_t)(v - lane)];
+        }
+#pragma unroll
+        for (int j = 0; j < UN; j++) {
+            const uint32_t c = sat_add(s[j], q[j].y & 0xFFu);
+            if (take[j] && c < best[q[j].y >> 8]) atomicMin(&best[q[j].y >> 8], c);
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t b = best[lane];
+    if (b < cur) {
+        if (pa.atomic_rows) atomicMin(&tgt[v], b);
+        else tgt[v] = b;
+        front_next[v] = 1;
+    }
+}
+
 template <bool WEIGHTED>
-__device__ __forceinline__ void pull_body(const uint2 *__restrict__ rec, const uint4 *__restrict__ units,
-                                          const PullSlices &sl, int64_t V, const uint32_t *__restrict__ snap,
-                                          const uint8_t *__restrict__ front_cur, uint32_t *__restrict__ val,
-                                          uint8_t *__restrict__ front_next, DevStep *__restrict__ step,
-                                          uint32_t *__restrict__ s_snap, const FixRegion &fr, uint32_t xcd_shift,
-                                          uint32_t *rot) {
+__device__ __forceinline__ void pull_body(const PullArgs &pa, int64_t V, const uint32_t *__restrict__ snap,
+                                          uint32_t *tgt, uint8_t *__restrict__ front_next,
+                                          DevStep *__restrict__ step, PullLds &lds, uint32_t xcd_shift,
+                                          uint32_t *__restrict__ rot) {
     const int tid = threadIdx.x;
-    if (blockIdx.x == 0 && tid == 0) step->pad = 1;
-    const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(val, (short)0, (int)(uint32_t)(V * 4), 0x00020000);
-    // The workgroup takes the slice of the XCD it runs on, so every writer of
-    // a destination shares one L2.  The hardware deals a launch's workgroups
-    // to the XCDs in turn, from XCD r for workgroup 0 (r has been seen to
-    // differ between launches), so workgroup b runs on XCD (b + r) mod 8 and
-    // is the (b / 8)-th of its XCD (the grid is a multiple of 8).  Each
-    // workgroup leaves the r it saw beside its fix-up count, and the fix-up
-    // pass flags the superstep if the workgroups of one launch saw more than
-    // one.  (xcd_shift, zero outside tests, offsets the odd workgroups' XCD
-    // to exercise that check.)
-    const uint32_t xr = (xcc_id() + ((blockIdx.x & 1u) ? xcd_shift : 0u)) % PULL_SLICES;
-    *rot = (xr + PULL_SLICES - blockIdx.x % PULL_SLICES) % PULL_SLICES;
-    const int x = (int)xr;
-    const int64_t nblk = gridDim.x / PULL_SLICES;
-    for (int64_t ui = sl.uoff[x] + blockIdx.x / PULL_SLICES; ui < sl.uoff[x + 1]; ui += nblk) {
-        const uint4 un = units[ui];
-        const uint32_t start = un.x, cnt = un.y, bb = un.z;
-        __syncthreads();  // the previous unit's gathers are done
-        // the band's snapshots, INF where the source is not in A_k
-        if ((int64_t)bb + PULL_BAND <= V) {
-            const uint4 *s4 = reinterpret_cast<const uint4 *>(snap + bb);
-            const uint32_t *f4 = reinterpret_cast<const uint32_t *>(front_cur + bb);
-            uint4 sv[PULL_BAND / 4 / 256];
-            uint32_t fv[PULL_BAND / 4 / 256];
+    RowItems &it = lds.items[tid >> 6];
+    const uint32_t low = ~step->inv_min;
+    if (WEIGHTED) {
+        const uint4 *h4 = reinterpret_cast<const uint4 *>(pa.hot);
 #pragma unroll
-            for (int q = 0; q < PULL_BAND / 4 / 256; q++) {
-                sv[q] = s4[q * 256 + tid];
-                fv[q] = f4[q * 256 + tid];
-            }
-#pragma unroll
-            for (int q = 0; q < PULL_BAND / 4 / 256; q++)
-                reinterpret_cast<uint4 *>(s_snap)[q * 256 + tid] =
-                    make_uint4(fv[q] & 0xFFu ? sv[q].x : INF, fv[q] & 0xFF00u ? sv[q].y : INF,
-                               fv[q] & 0xFF0000u ? sv[q].z : INF, fv[q] & 0xFF000000u ? sv[q].w : INF);
-        } else {  // the last band ends at V
-            for (int i = tid; i < PULL_BAND; i += 256) s_snap[i] = bb + i < V && front_cur[bb + i] ? snap[bb + i] : INF;
-        }
+        for (int q = 0; q < PULL_BIT_WORDS / 4 / 256; q++)
+            reinterpret_cast<uint4 *>(lds.bits)[q * 256 + tid] = h4[q * 256 + tid];
         __syncthreads();
-        // every lane runs every chunk (the hits' reservation is a wave-wide
-        // scan); lanes past the unit's end load its first record and offer nothing
-        for (uint32_t c0 = start; c0 < start + cnt; c0 += 256 * PULL_VT) {
-            uint32_t dst[PULL_VT], src[PULL_VT], m[PULL_VT], cur[PULL_VT];
-#pragma unroll
-            for (int i = 0; i < PULL_VT; i++) {  // record c0 + 256 i + tid; past the unit: no candidate
-                const uint32_t e = c0 + (uint32_t)i * 256 + (uint32_t)tid;
-                const bool in = e < start + cnt;
-                const uint2 q = rec[in ? e : start];
-                dst[i] = in ? q.x : PULL_SENTINEL;
-                src[i] = q.y;
+    }
+    // The workgroup takes the slice of the XCD it runs on: of every 8 runs of
+    // consecutive blocks one run (neighbouring rows, whose sources often
+    // neighbour each other too, share an L2), another one in each group of 8:
+    // where rows get shorter with every bit set in their id, as on R-MAT, a
+    // fixed one would give one XCD many times the others' entries (scale 22,
+    // first pull of a solve: 380 us, with the turn 335 us).  The hardware deals a launch's
+    // workgroups to the XCDs in turn, from XCD r for workgroup 0 (r has been
+    // seen to differ between launches), so workgroup b runs on XCD
+    // (b + r) mod 8 and is the (b / 8)-th of its XCD (the grid is a multiple
+    // of 8).  If the workgroups of one launch saw different r, some blocks
+    // would be taken twice and others never: each leaves the r it saw, and
+    // the launch that follows flags the superstep if they differ.
+    // (xcd_shift, zero outside tests, offsets the odd workgroups' XCD to
+    // exercise that check.)
+    const uint32_t x = (xcc_id() + ((blockIdx.x & 1u) ? xcd_shift : 0u)) % PULL_SLICES;
+    if (tid == 0) rot[blockIdx.x] = (x + PULL_SLICES - blockIdx.x % PULL_SLICES) % PULL_SLICES;
+    if (blockIdx.x == 0 && tid == 0) step->pad = 1;
+    const int64_t nper = gridDim.x / PULL_SLICES;
+    const int64_t nseg = pa.first_only ? 0 : (pa.nsegs + PULL_SEG_BLOCK - 1) / PULL_SEG_BLOCK;
+    const int64_t nblk = nseg + (V + PULL_BLOCK - 1) / PULL_BLOCK;
+    const int lg = nblk >= PULL_RUN_FROM ? PULL_RUN_LOG : 0;
+    for (int64_t j = blockIdx.x / PULL_SLICES;; j += nper) {
+        const uint32_t grp = (uint32_t)(j >> lg);
+        if ((int64_t)grp * PULL_SLICES << lg >= nblk) break;
+        const uint32_t turn = (x + (grp * 0x9E3779B1u >> 29)) % PULL_SLICES;
+        const int64_t blk = (((int64_t)grp * PULL_SLICES + turn) << lg) + (j & ((1 << lg) - 1));
+        if (blk >= nblk) continue;
+        __builtin_amdgcn_wave_barrier();
+        if (blk < nseg) {  // segments of long rows first: they are the longest work
+            // (a wave takes few segments, so that a superstep that has to
+            // read them all finds every wave at work)
+            const int64_t q = blk * PULL_SEG_BLOCK + (tid >> 6) * (PULL_SEG_BLOCK / 4) + (tid & 63);
+            uint4 sg = make_uint4(0u, 0u, 0u, 0u);
+            uint32_t cur = 0;
+            if ((tid & 63) < PULL_SEG_BLOCK / 4 && q < pa.nsegs) {
+                sg = pa.segs[q];
+                cur = pa.bound[sg.x];
             }
-#pragma unroll
-            for (int i = 0; i < PULL_VT; i++) {
-                const uint32_t sv = s_snap[(WEIGHTED ? (src[i] >> 8) : (src[i] - bb)) & (PULL_BAND - 1)];
-                m[i] = WEIGHTED ? sat_add(sv, src[i] & 0xFFu) : sv;
-                if (dst[i] == PULL_SENTINEL) m[i] = INF;
-            }
-            // one batched read of the destinations (only records with a
-            // candidate fetch), then the compares and the merge
-#pragma unroll
-            for (int i = 0; i < PULL_VT; i++)
-                cur[i] = __builtin_amdgcn_raw_buffer_load_b32(vrs, m[i] != INF ? dst[i] * 4u : 0x80000000u, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);  // every read above is issued before the first compare
-            uint32_t hits = 0;
-#pragma unroll
-            for (int i = 0; i < PULL_VT; i++) hits |= (uint32_t)(m[i] < cur[i]) << i;
-            apply_hits<PULL_VT>(dst, m, hits, val, front_next, fr);
+            const int n = queue_items(it, sat_add(low, sg.w) < cur, sg.x, sg.y, sg.z, cur);
+            scan_items<WEIGHTED, 16, 4>(it, lds.bits, n, pa, low, snap, tgt, front_next, true);
+            continue;
         }
+        const int64_t v = (blk - nseg) * PULL_BLOCK + tid;
+        const uint32_t cur = v < V ? pa.bound[v] : 0u;
+        if (WEIGHTED) {
+            const int64_t b = min(v, V - 1) >> 6;
+            stream_rows(it.best, lds.bits, v, cur, pa.rp[b], pa.rp[b + 1], pa, low, snap, tgt, front_next);
+            continue;
+        }
+        uint32_t beg = 0, end = 0;
+        if (v < V) {
+            beg = (uint32_t)pa.rp[v];
+            end = (uint32_t)pa.rp[v + 1];
+        }
+        if (pa.first_only) {
+            if (beg < end && low < cur) {
+                const uint32_t c = snap[(uint32_t) static_cast<const int32_t *>(pa.adj)[beg]];
+                if (c < cur) {
+                    if (pa.atomic_rows) atomicMin(&tgt[v], c);
+                    else tgt[v] = c;
+                    front_next[v] = 1;
+                }
+            }
+            continue;
+        }
+        const int n = queue_items(it, beg < end && end - beg <= PULL_SMALL && low < cur, (uint32_t)v, beg, end, cur);
+        scan_items<WEIGHTED, 4, 2>(it, lds.bits, n, pa, low, snap, tgt, front_next, pa.atomic_rows != 0);
     }
 }
 
 // One launch per superstep: the frontier's edge count, known on the device
 // after the compaction, picks the form (a second, idle launch would cost a
 // dispatch and a sweep of exiting workgroups every superstep).
-struct PullArgs {
-    const uint2 *rec;
-    const uint4 *units;
-    PullSlices sl;
-};
 union RelaxLds {
     PushLds push;
-    uint32_t pull_snap[PULL_BAND];
+    PullLds pull;
 };
 
 template <bool WEIGHTED>
 __global__ __launch_bounds__(256) void k_relax(const uint4 *__restrict__ list, const uint32_t *__restrict__ tile_start,
                                                const void *__restrict__ adj, PullArgs pa, int64_t V,
-                                               const uint32_t *__restrict__ snap, uint32_t *__restrict__ val,
-                                               const uint8_t *__restrict__ front_cur, uint8_t *__restrict__ front_next,
-                                               DevStep *__restrict__ step, uint32_t pull_edges,
-                                               uint2 *__restrict__ fix, uint32_t *__restrict__ fixn, uint32_t fix_cap,
-                                               uint32_t xcd_shift) {
+                                               const uint32_t *__restrict__ snap, uint32_t *val,
+                                               uint8_t *__restrict__ front_next, DevStep *__restrict__ step,
+                                               uint32_t pull_edges, uint32_t *__restrict__ rot, uint32_t xcd_shift) {
     __shared__ RelaxLds lds;
-    __shared__ uint32_t s_fixn;
-    if (threadIdx.x == 0) s_fixn = 0;
-    __syncthreads();
-    const FixRegion fr{fix + (size_t)blockIdx.x * fix_cap, fix_cap, &s_fixn};
     const unsigned long long le = step->list;
-    uint32_t rot = 0;
-    if ((uint32_t)le >= pull_edges) {
-        pull_body<WEIGHTED>(pa.rec, pa.units, pa.sl, V, snap, front_cur, val, front_next, step, lds.pull_snap, fr,
-                            xcd_shift, &rot);
-    } else {
+    if ((uint32_t)le >= pull_edges)
+        pull_body<WEIGHTED>(pa, V, snap, val, front_next, step, lds.pull, xcd_shift, rot);
+    else
         push_body<WEIGHTED>(list, tile_start, adj, val, front_next, le, lds.push);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) fixn[blockIdx.x] = min(s_fixn, fix_cap) | (rot << FIX_ROT_SHIFT);
-}
-
-// The relaxation's fix-up: workgroup b re-applies the recorded candidates of
-// relaxation workgroup b that are still below the stored value (a separate
-// launch: the relaxation's stores are visible to every XCD by then), and
-// flags the superstep if relaxation workgroup b saw another XCD rotation
-// than workgroup 0 (a push leaves rotation 0 everywhere).
-__global__ __launch_bounds__(256) void k_fixup(const uint2 *__restrict__ fix, const uint32_t *__restrict__ fixn,
-                                               uint32_t fix_cap, uint32_t *__restrict__ val, DevStep *__restrict__ step) {
-    const uint32_t w = fixn[blockIdx.x];
-    if (threadIdx.x == 0 && (w >> FIX_ROT_SHIFT) != (fixn[0] >> FIX_ROT_SHIFT)) step->rot_mixed = 1ull;
-    const uint32_t n = w & ((1u << FIX_ROT_SHIFT) - 1u);
-    const uint2 *e = fix + (size_t)blockIdx.x * fix_cap;
-    for (uint32_t i = threadIdx.x; i < n; i += 256) {
-        const uint2 q = e[i];
-        if (q.y < val[q.x]) atomicMin(&val[q.x], q.y);
-    }
 }
 
 // ------------------------------------------------------------ PageRank
@@ -1102,8 +1199,9 @@ __global__ __launch_bounds__(256) void k_fill_u32(uint32_t *p, int64_t n, uint32
 // accumulator is reset for the next merge.
 __global__ __launch_bounds__(256) void k_ph_apply(uint32_t *__restrict__ acc, uint32_t *__restrict__ val,
                                                   uint8_t *__restrict__ pend, uint8_t *__restrict__ dirty, int64_t V,
-                                                  DevStep *step) {
+                                                  DevStep *step, const uint32_t *__restrict__ rot, int nrot) {
     __shared__ unsigned long long s_c[4];
+    if (blockIdx.x == 0) check_rotations(step, rot, nrot);
     const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
     unsigned c = 0;
     if (v < V) {
@@ -1184,26 +1282,15 @@ static int relax_grid_for(gx_graph *g, const gx_params *p) {
     return std::max(PULL_SLICES, pg / PULL_SLICES * PULL_SLICES);
 }
 
-// Fix-up entries per relaxation workgroup: the records of the pull units a
-// workgroup sweeps (the j-th workgroup on the XCD of slice x takes units j,
-// j + nper, ... of slice x), maximised over x and j, so a region never
-// overflows.
-static uint32_t fix_cap_for(const gx_graph *g, const gx_params *p, int grid) {
-    const DevGraph &d = g->d;
-    const bool cc = p->algo == GX_CC;
-    const bool has_pull = cc ? d.pull_sym != nullptr : d.pull_w != nullptr;
-    if (!has_pull) return 0;
-    const PullSlices &sl = cc ? d.pull_sym_off : d.pull_w_off;
-    const std::vector<uint32_t> &recs = cc ? g->pull_sym_recs : g->pull_w_recs;
-    const int64_t nper = grid / PULL_SLICES;
-    uint64_t bound = 0;
-    for (int x = 0; x < PULL_SLICES; x++)
-        for (int64_t j = 0; j < nper; j++) {
-            uint64_t sum = 0;
-            for (int64_t u = sl.uoff[x] + j; u < sl.uoff[x + 1]; u += nper) sum += recs[(size_t)u];
-            bound = std::max(bound, sum);
-        }
-    return (uint32_t)std::min<uint64_t>(bound, (1u << FIX_ROT_SHIFT) - 1u);
+// What the pull of `s` reads; `bound`: the vertex values.  CC labels ascend
+// with the neighbour ids until the first superstep ran or another part's
+// labels were merged, so that superstep reads one neighbour per vertex.
+static PullArgs pull_args(const gx_state *s) {
+    const DevGraph &d = s->g->d;
+    if (s->p.algo == GX_CC)
+        return {d.sym_rp, d.sym_col, d.sym_segs, d.sym_nsegs, s->k == 0 && !s->merged, s->acc != nullptr, s->val,
+                nullptr};
+    return {d.in_blk, d.in_adj, d.pull_segs, d.pull_nsegs, 0, s->acc != nullptr, s->val, s->hot[s->k & 1]};
 }
 
 static size_t state_layout(gx_graph *g, const gx_params *p, Carver &c, gx_state *s) {
@@ -1240,9 +1327,9 @@ static size_t state_layout(gx_graph *g, const gx_params *p, Carver &c, gx_state 
         s->tile_start = c.take<uint32_t>(Eimg / PUSH_TILE + 2);
         s->snap = c.take<uint32_t>(V);
         s->relax_grid = relax_grid_for(g, p);
-        s->fix_cap = fix_cap_for(g, p, s->relax_grid);
-        s->fix = c.take<uint2>((size_t)s->relax_grid * s->fix_cap);
-        s->fixn = c.take<uint32_t>(s->relax_grid);
+        s->rot = c.take<uint32_t>(s->relax_grid);
+        if (p->algo == GX_SSSP)
+            for (uint32_t *&h : s->hot) h = c.take<uint32_t>(PULL_BIT_WORDS);
     }
     if (p->phases) {
         if (p->algo == GX_PAGERANK) {
@@ -1331,9 +1418,7 @@ extern "C" gx_status gx_state_init(gx_graph *g, const gx_params *p, void *dev_st
     state_layout(g, p, c, s);
     if (p->algo == GX_SSSP || p->algo == GX_CC) {
         const DevGraph &dg = g->d;
-        // (the pull addresses values through a 32-bit buffer range)
-        bool can_pull = dg.V < (int64_t(1) << 30) &&
-                        (p->algo == GX_SSSP ? (dg.pull_w != nullptr) : (dg.pull_sym != nullptr));
+        bool can_pull = p->algo == GX_SSSP ? dg.in_adj != nullptr : dg.sym_col != nullptr;
         double frac = p->pull_fraction > 0.f ? (double)p->pull_fraction : 0.3;
         double Eimg = (double)(p->algo == GX_SSSP ? dg.E : dg.E_sym);
         s->pull_edges = (!can_pull || frac >= 1.0) ? 0xFFFFFFFFu : (uint32_t)std::max(1.0, std::ceil(frac * Eimg));
@@ -1352,15 +1437,16 @@ extern "C" gx_status gx_state_init(gx_graph *g, const gx_params *p, void *dev_st
         float x0 = V > 0 ? (float)(1.0 / (double)Vn) : 0.f;
         unsigned nb = grid_for<int64_t>(V, 256);
         hipLaunchKernelGGL(k_pr_init, dim3(nb), dim3(256), 0, hs, s->x[0], s->contrib[0], s->synced, d.outdeg,
-                           d.pr_slot, V, x0, s->dpart, s->steps);
+                           d.slot, V, x0, s->dpart, s->steps);
         hipLaunchKernelGGL(k_reduce_D, dim3(1), dim3(1024), 0, hs, s->dpart, (int)nb, s->Dval);
         (void)hipMemsetAsync(s->fix_done, 0, sizeof(uint32_t), hs);
     } else {
-        int64_t n = std::max<int64_t>(V, d.W);
+        const int64_t n = std::max<int64_t>(V, s->hot[0] ? PULL_BIT_WORDS : 0);
         const int32_t *rp = p->algo == GX_CC ? d.sym_rp : d.out_rp;
         // (padding bytes of the maps beyond V are cleared too)
-        hipLaunchKernelGGL(k_min_init, dim3(grid_for<int64_t>(n, 256)), dim3(256), 0, hs, s->val, s->front8[0],
-                           s->front8[1], s->dirty8, d.l2g, rp, V, p->algo, p->source, s->steps);
+        hipLaunchKernelGGL(k_min_init, dim3(grid_for<int64_t>(n, 256)), dim3(256), 0, hs, s->val, s->snap,
+                           s->front8[0], s->front8[1], s->dirty8, d.l2g, rp, V, p->algo, p->source, s->steps,
+                           s->hot[0], s->hot[1]);
         if ((int64_t)d.W * 32 > V) {
             size_t pad = (size_t)d.W * 32 - (size_t)V;
             (void)hipMemsetAsync(s->front8[0] + V, 0, pad, hs);
@@ -1374,7 +1460,9 @@ extern "C" gx_status gx_state_init(gx_graph *g, const gx_params *p, void *dev_st
         if (V > 0 && !p->phases)
             hipLaunchKernelGGL(k_compact, dim3(grid_for<int64_t>(V, CBLOCK * CVT)), dim3(CBLOCK), 0, hs, s->front8[0],
                                s->front8[1], rp, s->val, s->snap, V, s->list, s->tile_start, s->steps,
-                               s->steps + 1, (int)(s->pull_edges != 0xFFFFFFFFu), nullptr, nullptr, s->pull_edges);
+                               s->steps + 1, (int)(s->pull_edges != 0xFFFFFFFFu), nullptr, nullptr, s->pull_edges,
+                               s->rot, 0, s->hot[0] ? d.slot : nullptr,
+                               s->hot[0], s->hot[1]);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
@@ -1516,7 +1604,7 @@ static gx_status enqueue_superstep(gx_state *s, hipStream_t hs) {
         int cur = (int)(s->k & 1);
         double dd = p.damping;
         PrApply ap{(1.0 - dd) / (double)d.V, dd, 0.0, d.outdeg, s->x[cur], s->x[cur ^ 1], s->contrib[cur ^ 1],
-                   d.pr_slot};
+                   d.slot};
         double inv_V = d.V > 0 ? 1.0 / (double)d.V : 0.0;
         if (d.V > 0) {
             if (e0) (void)hipEventRecord(e0, hs);
@@ -1539,23 +1627,16 @@ static gx_status enqueue_superstep(gx_state *s, hipStream_t hs) {
         DevStep *next2 = s->steps + ((s->k + 2) % STEP_RING);
         if (d.V > 0) {
             if (e0) (void)hipEventRecord(e0, hs);
-            if (!cc) {
-                const PullArgs pa{d.pull_w, d.pull_w_units, d.pull_w_off};
-                hipLaunchKernelGGL(k_relax<true>, dim3(s->relax_grid), dim3(256), 0, hs, s->list, s->tile_start,
-                                   (const void *)d.out_adj, pa, d.V, s->snap, s->val, s->front8[cur], s->front8[cur ^ 1],
-                                   step, s->pull_edges, s->fix, s->fixn, s->fix_cap, s->xcd_shift);
-            } else {
-                const PullArgs pa{d.pull_sym, d.pull_sym_units, d.pull_sym_off};
-                hipLaunchKernelGGL(k_relax<false>, dim3(s->relax_grid), dim3(256), 0, hs, s->list, s->tile_start,
-                                   (const void *)d.sym_col, pa, d.V, s->snap, s->val, s->front8[cur], s->front8[cur ^ 1],
-                                   step, s->pull_edges, s->fix, s->fixn, s->fix_cap, s->xcd_shift);
-            }
-            hipLaunchKernelGGL(k_fixup, dim3(s->relax_grid), dim3(256), 0, hs, s->fix, s->fixn, s->fix_cap, s->val,
-                               step);
+            auto relax = cc ? k_relax<false> : k_relax<true>;
+            hipLaunchKernelGGL(relax, dim3(s->relax_grid), dim3(256), 0, hs, s->list, s->tile_start,
+                               cc ? (const void *)d.sym_col : (const void *)d.out_adj, pull_args(s), d.V, s->snap, s->val,
+                               s->front8[cur ^ 1], step, s->pull_edges, s->rot, s->xcd_shift);
             if (e1) (void)hipEventRecord(e1, hs);
             hipLaunchKernelGGL(k_compact, dim3(grid_for<int64_t>(d.V, CBLOCK * CVT)), dim3(CBLOCK), 0, hs,
                                s->front8[cur ^ 1], s->front8[cur], rp, s->val, s->snap, d.V, s->list, s->tile_start,
-                               next, next2, (int)(s->pull_edges != 0xFFFFFFFFu), step, s->dirty8, s->pull_edges);
+                               next, next2, (int)(s->pull_edges != 0xFFFFFFFFu), step, s->dirty8, s->pull_edges, s->rot,
+                               s->relax_grid, s->hot[0] ? d.slot : nullptr,
+                               s->hot[cur ^ 1], s->hot[cur]);
         }
     }
     hipError_t e = hipGetLastError();
@@ -1943,6 +2024,7 @@ extern "C" gx_status gx_apply_delta(gx_state *s, const int32_t *dev_gid, const u
         // A_{k+1} (the frontier of the superstep about to run) and its counter slot
         uint8_t *front = s->front8[s->k & 1];
         DevStep *slot = s->steps + (s->k % STEP_RING), *slot2 = s->steps + ((s->k + 1) % STEP_RING);
+        s->merged |= n > 0;
         if (n > 0)
             hipLaunchKernelGGL(k_apply_delta, dim3(grid_for<uint32_t>(n, 256)), dim3(256), 0, hs, dev_gid, dev_val, n,
                                d.l2g, d.V, s->val, front);
@@ -1951,7 +2033,9 @@ extern "C" gx_status gx_apply_delta(gx_state *s, const int32_t *dev_gid, const u
         const int32_t *rp = s->p.algo == GX_CC ? d.sym_rp : d.out_rp;
         hipLaunchKernelGGL(k_compact, dim3(grid_for<int64_t>(d.V, CBLOCK * CVT)), dim3(CBLOCK), 0, hs, front,
                            s->front8[(s->k & 1) ^ 1], rp, s->val, s->snap, d.V, s->list, s->tile_start, slot, slot2,
-                           (int)(s->pull_edges != 0xFFFFFFFFu), nullptr, nullptr, s->pull_edges);
+                           (int)(s->pull_edges != 0xFFFFFFFFu), nullptr, nullptr, s->pull_edges,
+                               s->rot, 0, s->hot[0] ? d.slot : nullptr,
+                               s->hot[s->k & 1], s->hot[(s->k + 1) & 1]);
         GX_CHECK_HIP(hipGetLastError(), s);
     }
     if (active_next) {
@@ -1987,7 +2071,7 @@ extern "C" gx_status gx_msg_gen(gx_state *s, void *stream) {
             const unsigned nb = grid_for<int64_t>(d.V, 256);
             const bool parts = s->p.phases == GX_PHASES_MASTERS;
             hipLaunchKernelGGL(k_ph_pr_gen, dim3(nb), dim3(256), 0, hs, s->x[0], parts ? d.outdeg_g : d.outdeg,
-                               d.pr_slot, s->contrib[0], d.V, s->dpart, parts ? d.master : nullptr);
+                               d.slot, s->contrib[0], d.V, s->dpart, parts ? d.master : nullptr);
             hipLaunchKernelGGL(k_reduce_D, dim3(1), dim3(1024), 0, hs, s->dpart, (int)nb, s->Dval);
         } else {
             // the pending map's vertices become the active list (with the values
@@ -1997,7 +2081,8 @@ extern "C" gx_status gx_msg_gen(gx_state *s, void *stream) {
             hipLaunchKernelGGL(k_compact, dim3(grid_for<int64_t>(d.V, CBLOCK * CVT)), dim3(CBLOCK), 0, hs,
                                s->front8[s->ph_p], s->front8[s->ph_p ^ 1], rp, s->val, s->snap, d.V, s->list,
                                s->tile_start, step, next, (int)(s->pull_edges != 0xFFFFFFFFu), nullptr, nullptr,
-                               s->pull_edges);
+                               s->pull_edges, s->rot, 0, s->hot[0] ? d.slot : nullptr,
+                               s->hot[s->k & 1], s->hot[(s->k + 1) & 1]);
         }
         GX_CHECK_HIP(hipGetLastError(), s);
     }
@@ -2029,20 +2114,11 @@ extern "C" gx_status gx_msg_merge(gx_state *s, void *stream) {
             // the relaxation of the fused superstep, against the accumulator:
             // it combines the messages by minimum and changes no vertex value
             DevStep *step = s->steps + (s->k % STEP_RING);
-            const uint8_t *cur = s->front8[s->ph_p ^ 1];
-            if (s->p.algo == GX_SSSP) {
-                const PullArgs pa{d.pull_w, d.pull_w_units, d.pull_w_off};
-                hipLaunchKernelGGL(k_relax<true>, dim3(s->relax_grid), dim3(256), 0, hs, s->list, s->tile_start,
-                                   (const void *)d.out_adj, pa, d.V, s->snap, s->acc, cur, s->junk8, step,
-                                   s->pull_edges, s->fix, s->fixn, s->fix_cap, s->xcd_shift);
-            } else {
-                const PullArgs pa{d.pull_sym, d.pull_sym_units, d.pull_sym_off};
-                hipLaunchKernelGGL(k_relax<false>, dim3(s->relax_grid), dim3(256), 0, hs, s->list, s->tile_start,
-                                   (const void *)d.sym_col, pa, d.V, s->snap, s->acc, cur, s->junk8, step,
-                                   s->pull_edges, s->fix, s->fixn, s->fix_cap, s->xcd_shift);
-            }
-            hipLaunchKernelGGL(k_fixup, dim3(s->relax_grid), dim3(256), 0, hs, s->fix, s->fixn, s->fix_cap, s->acc,
-                               step);
+            const bool cc = s->p.algo == GX_CC;
+            auto relax = cc ? k_relax<false> : k_relax<true>;
+            hipLaunchKernelGGL(relax, dim3(s->relax_grid), dim3(256), 0, hs, s->list, s->tile_start,
+                               cc ? (const void *)d.sym_col : (const void *)d.out_adj, pull_args(s), d.V, s->snap, s->acc,
+                               s->junk8, step, s->pull_edges, s->rot, s->xcd_shift);
         }
         GX_CHECK_HIP(hipGetLastError(), s);
     }
@@ -2070,7 +2146,7 @@ extern "C" gx_status gx_msg_apply(gx_state *s, void *stream, gx_step_stats *stat
                                next, parts ? d.master : nullptr);
         } else {
             hipLaunchKernelGGL(k_ph_apply, dim3(grid_for<int64_t>(d.V, 256)), dim3(256), 0, hs, s->acc, s->val,
-                               s->front8[s->ph_p], s->dirty8, d.V, step);
+                               s->front8[s->ph_p], s->dirty8, d.V, step, s->rot, s->relax_grid);
         }
         GX_CHECK_HIP(hipGetLastError(), s);
     }
