@@ -145,6 +145,18 @@ struct DevGraph {
     int64_t V_global = 0;
 };
 
+// Label propagation's class sizes (off[c]: first list slot of class c), hubs
+// and their chunks.
+struct LpPlan {
+    bool made = false;
+    int64_t off[LP_CLASSES + 1] = {};
+    int64_t nwave = 0, tab_slots = 0;
+    int64_t slot_bound = 0;       // upper bound of the hub table slots
+    std::vector<uint32_t> hubs;   // vertices, ascending
+    std::vector<uint4> chunks;    // {hub, first entry, end entry, 0}
+    std::vector<uint2> hub;       // per hub {first table slot, slots}
+};
+
 }  // namespace gx
 
 struct gx_graph {
@@ -156,6 +168,8 @@ struct gx_graph {
     int num_cus = 0;
     bool dev_error = false;
     std::vector<int32_t> host_outdeg;  // out-degree (host copy, for sources and stats)
+    std::mutex lp_mu;
+    gx::LpPlan lp;
     std::vector<int32_t> host_symdeg;  // distinct neighbours (with GX_NEED_SYM; label propagation classes)
     // supersteps of the last converged SSSP / CC run on this graph: the size
     // of the next run's first speculative group (solves on one graph tend to
@@ -260,6 +274,12 @@ struct gx_state {
     uint2 *lp_hub = nullptr;                  // per hub {first table slot, slots (a power of two)}
     uint2 *lp_tab = nullptr;                  // hub tables {label, count}; label LP_NONE = free
     int64_t lp_tab_slots = 0;
+    int64_t lp_nwave = 0;                     // vertices of class 5 that take one wave (listed first)
+    unsigned long long *lp_best = nullptr;    // per hub: largest (count, ~label) so far (0 between supersteps)
+    uint32_t *lp_log = nullptr;               // hub table slots taken in a superstep ([0]: how many)
+    uint32_t *lp_cursor = nullptr;            // next slot of every list while they are filled
+    uint8_t *lp_touch = nullptr;              // a neighbour's label changed: recompute
+    uint2 *lp_changed = nullptr;              // the vertices the last superstep changed {vertex, neighbour chunk}
     // separate template calls (gx_params.phases): merged messages per vertex,
     // the index of the pending map in front8, and what is waiting
     uint32_t *acc = nullptr;         // SSSP / CC: min of the merged messages (INF = none)
@@ -290,7 +310,8 @@ struct gx_state {
 
 namespace gx {
 // Label propagation (gx_lp.hip): state layout (also sizes the arena with a
-// measuring Carver), initialisation (synchronises `hs`), one superstep.
+// measuring Carver), initialisation, one superstep.
+const LpPlan &lp_plan(gx_graph *g);
 size_t lp_layout(gx_graph *g, Carver &c, gx_state *s);
 gx_status lp_init(gx_state *s, hipStream_t hs);
 void lp_enqueue(gx_state *s, hipStream_t hs, DevStep *step, DevStep *next);

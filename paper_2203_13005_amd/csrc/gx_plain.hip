@@ -1373,8 +1373,12 @@ static gx_status check_params(const gx_graph *g, const gx_params *p) {
     if (p->algo == GX_LP) {
         GX_REQUIRE(g->needs & GX_NEED_SYM, GX_EINVAL, "LP needs GX_NEED_SYM");
         int64_t slots = 0;
-        for (int32_t d : g->host_symdeg)
-            if (d > LP_MID_MAX) slots += 3 * (int64_t)d + 256;
+        try {
+            slots = lp_plan(const_cast<gx_graph *>(g)).slot_bound;
+        } catch (const std::bad_alloc &) {
+            set_error("host allocation failed while laying out the label propagation lists");
+            return GX_ENOMEM;
+        }
         GX_REQUIRE(slots < (int64_t(1) << 32), GX_EINVAL, "LP hub tables would exceed 2^32 slots");
     }
     return GX_OK;
