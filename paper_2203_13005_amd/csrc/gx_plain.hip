@@ -95,10 +95,10 @@ __global__ __launch_bounds__(256) void k_min_init(uint32_t *val, uint32_t *snap,
 }
 
 // Frontier byte map -> active list.  Each thread takes CVT consecutive
-// vertices: one 16-byte load of their frontier bytes (and one 16-byte store
-// clearing the byte map the next relaxation fills, which held A_{k-1}); a
-// thread with an active vertex loads its CVT+1 row pointers and CVT values
-// as whole vectors, so no load waits on another.  A workgroup covers
+// vertices: one load of their frontier bytes (and one store clearing the
+// byte map the next relaxation fills, which held A_{k-1}); a thread with an
+// active vertex loads its CVT+1 row pointers, CVT values and slots as whole
+// vectors, so no load waits on another.  A workgroup covers
 // CBLOCK*CVT vertices and issues two counter atomics (list, |A|).  Active
 // vertices with out-edges get a list entry (edge offset, CSR base,
 // snapshot, vertex) and the tiles that start inside an entry's edges record
@@ -108,7 +108,14 @@ __global__ __launch_bounds__(256) void k_min_init(uint32_t *val, uint32_t *snap,
 // active next, so after every compaction `snap` holds the value of every
 // vertex at the start of the superstep (k_min_init wrote the first ones).
 // |A_{k+1}| is the number of vertices superstep k changed.
-constexpr int CVT = 16;
+// CVT is COMPACT_WIDE from COMPACT_WIDE_FROM vertices on and 4 below: a small
+// graph then still has several workgroups, and a thread with hubs writes few
+// list entries one after another (scale-15 solve: 155 us against 212 us with
+// 16, together with idle pull workgroups leaving before they stage the
+// frontier bits; scale 22: 1212 us with 8 against 1357 us with 16, which
+// leaves no registers for the slots).
+constexpr int COMPACT_WIDE = 8;
+constexpr int64_t COMPACT_WIDE_FROM = int64_t(1) << 20;
 // Threads per compaction workgroup: each workgroup makes one list
 // reservation (an add with return on a single counter, which serialises
 // across workgroups), so fewer, larger workgroups shorten that chain.
@@ -124,6 +131,7 @@ __device__ __forceinline__ void check_rotations(DevStep *step, const uint32_t *_
     if (mixed) step->rot_mixed = 1ull;
 }
 
+template <int CVT>
 __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ front, uint8_t *__restrict__ front_clear,
                                                  const int32_t *__restrict__ rp, const uint32_t *__restrict__ val,
                                                  uint32_t *__restrict__ snap, int64_t V,
@@ -150,17 +158,23 @@ __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ 
             hot_clear[i] = 0u;
     const int64_t u0 = ((int64_t)blockIdx.x * CBLOCK + tid) * CVT;
     uint32_t actmask = 0;
-    if (u0 < V) {  // byte maps are padded to whole 32-vertex words: the 16 bytes at u0 exist
-        const uint4 f = *reinterpret_cast<const uint4 *>(front + u0);
-        *reinterpret_cast<uint4 *>(front_clear + u0) = make_uint4(0u, 0u, 0u, 0u);
-        if (dirty != nullptr && (f.x | f.y | f.z | f.w)) {  // changed vertices become dirty here
-            uint4 *d4 = reinterpret_cast<uint4 *>(dirty + u0);
-            const uint4 d = *d4;
-            *d4 = make_uint4(d.x | f.x, d.y | f.y, d.z | f.z, d.w | f.w);
-        }
-        const uint32_t fw[4] = {f.x, f.y, f.z, f.w};
+    if (u0 < V) {  // byte maps are padded to whole 32-vertex words: the CVT bytes at u0 exist
+        constexpr int NW = CVT / 4;
+        uint32_t fw[NW], any = 0;
 #pragma unroll
-        for (int q = 0; q < 4; q++)
+        for (int q = 0; q < NW; q++) {
+            fw[q] = reinterpret_cast<const uint32_t *>(front + u0)[q];
+            any |= fw[q];
+        }
+#pragma unroll
+        for (int q = 0; q < NW; q++) reinterpret_cast<uint32_t *>(front_clear + u0)[q] = 0u;
+        if (dirty != nullptr && any) {  // changed vertices become dirty here
+            uint32_t *d4 = reinterpret_cast<uint32_t *>(dirty + u0);
+#pragma unroll
+            for (int q = 0; q < NW; q++) d4[q] |= fw[q];
+        }
+#pragma unroll
+        for (int q = 0; q < NW; q++)
 #pragma unroll
             for (int b = 0; b < 4; b++)
                 if ((fw[q] >> (8 * b)) & 0xFFu) actmask |= 1u << (4 * q + b);
@@ -169,10 +183,13 @@ __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ 
     if (!__syncthreads_or(actmask != 0)) return;
     int32_t r[CVT + 1];
     uint32_t x[CVT];
+    int32_t sl[CVT];
+    const bool by_slot = snap_all && slot != nullptr;
 #pragma unroll
     for (int i = 0; i < CVT; i++) {
         r[i] = 0;
         x[i] = 0;
+        sl[i] = 0;
     }
     r[CVT] = 0;
     if (actmask) {
@@ -187,38 +204,19 @@ __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ 
                 x[4 * q] = b.x, x[4 * q + 1] = b.y, x[4 * q + 2] = b.z, x[4 * q + 3] = b.w;
             }
             r[CVT] = rp[u0 + CVT];
+            if (by_slot)
+#pragma unroll
+                for (int q = 0; q < CVT / 4; q++) {
+                    const int4 a = reinterpret_cast<const int4 *>(slot + u0)[q];
+                    sl[4 * q] = a.x, sl[4 * q + 1] = a.y, sl[4 * q + 2] = a.z, sl[4 * q + 3] = a.w;
+                }
         } else {
 #pragma unroll
             for (int i = 0; i < CVT; i++) {
                 if (u0 + i < V) x[i] = val[u0 + i];
+                if (by_slot && u0 + i < V) sl[i] = slot[u0 + i];
                 if (u0 + i <= V) r[i] = rp[u0 + i];
             }
-        }
-    }
-    // Snapshots for the pull.  SSSP: the active vertices' values go to their
-    // slots, and their bits with them (a bit too many only costs a read).
-    // CC: a thread with an active vertex stores the values of all its CVT
-    // vertices (whole vectors; an inactive vertex's value is the one its
-    // snapshot holds already).
-    if (snap_all && actmask && slot != nullptr) {
-        int32_t sl[CVT];
-#pragma unroll
-        for (int i = 0; i < CVT; i++) sl[i] = slot[min(u0 + i, V - 1)];
-#pragma unroll
-        for (int i = 0; i < CVT; i++) {
-            if (!((actmask >> i) & 1u)) continue;
-            snap[sl[i]] = x[i];
-            if (sl[i] < PULL_BITS) atomicOr(&hot[sl[i] >> 5], 1u << (sl[i] & 31));
-        }
-    } else if (snap_all && actmask) {
-        if (u0 + CVT <= V) {
-            uint4 *s4 = reinterpret_cast<uint4 *>(snap + u0);
-#pragma unroll
-            for (int q = 0; q < CVT / 4; q++) s4[q] = make_uint4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < CVT; i++)
-                if (u0 + i < V) snap[u0 + i] = x[i];
         }
     }
     uint32_t cnt = 0, edges = 0, low = INF;
@@ -244,6 +242,29 @@ __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ 
         s_min[tid >> 6] = low;
     }
     if (tid == 0) s_base = total ? atomicAdd(&step->list, total) : 0ull;
+    // Snapshots for the pull.  SSSP: the active vertices' values go to their
+    // slots, and their bits with them (a bit too many only costs a read).
+    // CC: a thread with an active vertex stores the values of all its CVT
+    // vertices (whole vectors; an inactive vertex's value is the one its
+    // snapshot holds already).
+    if (by_slot) {
+#pragma unroll
+        for (int i = 0; i < CVT; i++) {
+            if (!((actmask >> i) & 1u)) continue;
+            snap[sl[i]] = x[i];
+            if (sl[i] < PULL_BITS) atomicOr(&hot[sl[i] >> 5], 1u << (sl[i] & 31));
+        }
+    } else if (snap_all && actmask) {
+        if (u0 + CVT <= V) {
+            uint4 *s4 = reinterpret_cast<uint4 *>(snap + u0);
+#pragma unroll
+            for (int q = 0; q < CVT / 4; q++) s4[q] = make_uint4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < CVT; i++)
+                if (u0 + i < V) snap[u0 + i] = x[i];
+        }
+    }
     __syncthreads();
     if (tid == 0) {
         int nfb = 0;
@@ -522,13 +543,6 @@ __device__ __forceinline__ void pull_body(const PullArgs &pa, int64_t V, const u
     const int tid = threadIdx.x;
     RowItems &it = lds.items[tid >> 6];
     const uint32_t low = ~step->inv_min;
-    if (WEIGHTED) {
-        const uint4 *h4 = reinterpret_cast<const uint4 *>(pa.hot);
-#pragma unroll
-        for (int q = 0; q < PULL_BIT_WORDS / 4 / 256; q++)
-            reinterpret_cast<uint4 *>(lds.bits)[q * 256 + tid] = h4[q * 256 + tid];
-        __syncthreads();
-    }
     // The workgroup takes the slice of the XCD it runs on: of every 8 runs of
     // consecutive blocks one run (neighbouring rows, whose sources often
     // neighbour each other too, share an L2), another one in each group of 8:
@@ -550,6 +564,13 @@ __device__ __forceinline__ void pull_body(const PullArgs &pa, int64_t V, const u
     const int64_t nseg = pa.first_only ? 0 : (pa.nsegs + PULL_SEG_BLOCK - 1) / PULL_SEG_BLOCK;
     const int64_t nblk = nseg + (V + PULL_BLOCK - 1) / PULL_BLOCK;
     const int lg = nblk >= PULL_RUN_FROM ? PULL_RUN_LOG : 0;
+    if ((((int64_t)(blockIdx.x / PULL_SLICES) >> lg) * PULL_SLICES << lg) >= nblk) return;  // no block for it
+    if (WEIGHTED) {
+        const uint4 *h4 = reinterpret_cast<const uint4 *>(pa.hot);
+        const int n4 = (int)min((V + 127) / 128, (int64_t)(PULL_BIT_WORDS / 4));
+        for (int q = tid; q < n4; q += 256) reinterpret_cast<uint4 *>(lds.bits)[q] = h4[q];
+        __syncthreads();
+    }
     for (int64_t j = blockIdx.x / PULL_SLICES;; j += nper) {
         const uint32_t grp = (uint32_t)(j >> lg);
         if ((int64_t)grp * PULL_SLICES << lg >= nblk) break;
@@ -1293,6 +1314,23 @@ static PullArgs pull_args(const gx_state *s) {
     return {d.in_blk, d.in_adj, d.pull_segs, d.pull_nsegs, 0, s->acc != nullptr, s->val, s->hot[s->k & 1]};
 }
 
+// Compacts the map `front` (A_{s->k + ahead}) into the active list, counting
+// into `step`; clears `clear` and the slot after.  `prev`: the step that
+// filled the map, `dirty`: where its changes are kept (both NULL where no
+// superstep did).
+static void launch_compact(gx_state *s, hipStream_t hs, const uint8_t *front, uint8_t *clear, int ahead, DevStep *prev,
+                           uint8_t *dirty) {
+    const DevGraph &d = s->g->d;
+    const int64_t k = s->k + ahead;
+    const bool wide = d.V >= COMPACT_WIDE_FROM;
+    auto kern = wide ? k_compact<COMPACT_WIDE> : k_compact<4>;
+    hipLaunchKernelGGL(kern, dim3(grid_for<int64_t>(d.V, CBLOCK * (wide ? COMPACT_WIDE : 4))), dim3(CBLOCK), 0, hs, front,
+                       clear, s->p.algo == GX_CC ? d.sym_rp : d.out_rp, s->val, s->snap, d.V, s->list, s->tile_start,
+                       s->steps + (k % STEP_RING), s->steps + ((k + 1) % STEP_RING),
+                       (int)(s->pull_edges != 0xFFFFFFFFu), prev, dirty, s->pull_edges, s->rot, s->relax_grid,
+                       s->hot[0] ? d.slot : nullptr, s->hot[k & 1], s->hot[(k + 1) & 1]);
+}
+
 static size_t state_layout(gx_graph *g, const gx_params *p, Carver &c, gx_state *s) {
     const DevGraph &d = g->d;
     int64_t V = d.V;
@@ -1462,11 +1500,7 @@ extern "C" gx_status gx_state_init(gx_graph *g, const gx_params *p, void *dev_st
         // compaction of superstep 0 (each superstep then relaxes and compacts the
         // next); with separate template calls the first MSGGen does it
         if (V > 0 && !p->phases)
-            hipLaunchKernelGGL(k_compact, dim3(grid_for<int64_t>(V, CBLOCK * CVT)), dim3(CBLOCK), 0, hs, s->front8[0],
-                               s->front8[1], rp, s->val, s->snap, V, s->list, s->tile_start, s->steps,
-                               s->steps + 1, (int)(s->pull_edges != 0xFFFFFFFFu), nullptr, nullptr, s->pull_edges,
-                               s->rot, 0, s->hot[0] ? d.slot : nullptr,
-                               s->hot[0], s->hot[1]);
+            launch_compact(s, hs, s->front8[0], s->front8[1], 0, nullptr, nullptr);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
@@ -1627,8 +1661,6 @@ static gx_status enqueue_superstep(gx_state *s, hipStream_t hs) {
         // compact A_{k+1} for superstep k+1
         const int cur = (int)(s->k & 1);
         const bool cc = p.algo == GX_CC;
-        const int32_t *rp = cc ? d.sym_rp : d.out_rp;
-        DevStep *next2 = s->steps + ((s->k + 2) % STEP_RING);
         if (d.V > 0) {
             if (e0) (void)hipEventRecord(e0, hs);
             auto relax = cc ? k_relax<false> : k_relax<true>;
@@ -1636,11 +1668,7 @@ static gx_status enqueue_superstep(gx_state *s, hipStream_t hs) {
                                cc ? (const void *)d.sym_col : (const void *)d.out_adj, pull_args(s), d.V, s->snap, s->val,
                                s->front8[cur ^ 1], step, s->pull_edges, s->rot, s->xcd_shift);
             if (e1) (void)hipEventRecord(e1, hs);
-            hipLaunchKernelGGL(k_compact, dim3(grid_for<int64_t>(d.V, CBLOCK * CVT)), dim3(CBLOCK), 0, hs,
-                               s->front8[cur ^ 1], s->front8[cur], rp, s->val, s->snap, d.V, s->list, s->tile_start,
-                               next, next2, (int)(s->pull_edges != 0xFFFFFFFFu), step, s->dirty8, s->pull_edges, s->rot,
-                               s->relax_grid, s->hot[0] ? d.slot : nullptr,
-                               s->hot[cur ^ 1], s->hot[cur]);
+            launch_compact(s, hs, s->front8[cur ^ 1], s->front8[cur], 1, step, s->dirty8);
         }
     }
     hipError_t e = hipGetLastError();
@@ -2027,19 +2055,14 @@ extern "C" gx_status gx_apply_delta(gx_state *s, const int32_t *dev_gid, const u
     if (d.V > 0) {
         // A_{k+1} (the frontier of the superstep about to run) and its counter slot
         uint8_t *front = s->front8[s->k & 1];
-        DevStep *slot = s->steps + (s->k % STEP_RING), *slot2 = s->steps + ((s->k + 1) % STEP_RING);
+        DevStep *slot = s->steps + (s->k % STEP_RING);
         s->merged |= n > 0;
         if (n > 0)
             hipLaunchKernelGGL(k_apply_delta, dim3(grid_for<uint32_t>(n, 256)), dim3(256), 0, hs, dev_gid, dev_val, n,
                                d.l2g, d.V, s->val, front);
         // rebuild the active list of A_{k+1} from the merged values
         hipLaunchKernelGGL(k_zero_step, dim3(1), dim3(1), 0, hs, slot);
-        const int32_t *rp = s->p.algo == GX_CC ? d.sym_rp : d.out_rp;
-        hipLaunchKernelGGL(k_compact, dim3(grid_for<int64_t>(d.V, CBLOCK * CVT)), dim3(CBLOCK), 0, hs, front,
-                           s->front8[(s->k & 1) ^ 1], rp, s->val, s->snap, d.V, s->list, s->tile_start, slot, slot2,
-                           (int)(s->pull_edges != 0xFFFFFFFFu), nullptr, nullptr, s->pull_edges,
-                               s->rot, 0, s->hot[0] ? d.slot : nullptr,
-                               s->hot[s->k & 1], s->hot[(s->k + 1) & 1]);
+        launch_compact(s, hs, front, s->front8[(s->k & 1) ^ 1], 0, nullptr, nullptr);
         GX_CHECK_HIP(hipGetLastError(), s);
     }
     if (active_next) {
@@ -2080,13 +2103,7 @@ extern "C" gx_status gx_msg_gen(gx_state *s, void *stream) {
         } else {
             // the pending map's vertices become the active list (with the values
             // they send); the other map is cleared to collect the next changes
-            const int32_t *rp = s->p.algo == GX_CC ? d.sym_rp : d.out_rp;
-            DevStep *step = s->steps + (s->k % STEP_RING), *next = s->steps + ((s->k + 1) % STEP_RING);
-            hipLaunchKernelGGL(k_compact, dim3(grid_for<int64_t>(d.V, CBLOCK * CVT)), dim3(CBLOCK), 0, hs,
-                               s->front8[s->ph_p], s->front8[s->ph_p ^ 1], rp, s->val, s->snap, d.V, s->list,
-                               s->tile_start, step, next, (int)(s->pull_edges != 0xFFFFFFFFu), nullptr, nullptr,
-                               s->pull_edges, s->rot, 0, s->hot[0] ? d.slot : nullptr,
-                               s->hot[s->k & 1], s->hot[(s->k + 1) & 1]);
+            launch_compact(s, hs, s->front8[s->ph_p], s->front8[s->ph_p ^ 1], 0, nullptr, nullptr);
         }
         GX_CHECK_HIP(hipGetLastError(), s);
     }
