@@ -8,8 +8,7 @@
 namespace gx {
 
 constexpr int BS_MIN_TILE = 1024;  // smallest SSSP work tile among the variants
-constexpr int BP_TILE = 256;       // in-edges per PPR pull tile (one wave)
-constexpr int BP_DCHUNK = 256;     // tiles per first-level dangling partial
+constexpr int BP_TILE = 256;       // tile the PPR tunings name (the graph fixes the tiles)
 constexpr double BARRIER_LIMIT_S = 20.0;  // longest wait of a grid barrier before it reports an error
 
 struct BsCtl {
@@ -53,23 +52,30 @@ struct BsVariant {
 };
 
 struct BpArgs {
-    const int32_t *in_rp, *in_col, *outdeg, *trow;
-    int64_t ntiles, V, E;
+    const int32_t *in_col;
+    const int2 *nz;
+    const uint64_t *row_last;
+    const int32_t *tile_nz;
+    const int4 *cross;
+    const int32_t *dang;
+    const int32_t *in_rp, *outdeg;
+    int64_t n_nz, ntiles, E, n_dang;
+    int32_t tile, dtile, ndtiles, n_cross, n_cross_long;
     uint32_t B;   // lane stride of the tiles
     uint32_t Bw;  // lanes processed (0..Bw-1); the rest keep their values untouched
     float d;
     const int32_t *seed;  // per lane; -1 = free lane
-    const int32_t *end;   // per lane: first superstep it no longer runs (NULL: every lane runs every superstep)
-    float *x[2], *c[2];
-    double *head, *tailp, *dsum, *dpart, *D[2];  // D[k & 1]: dangling mass of superstep k
-    int32_t *spill;
+    const int32_t *end;   // per lane: first superstep it no longer runs (NULL: every lane's is `last`)
+    uint32_t last;
+    float *x;             // ranks, written in a lane's last superstep
+    float *c[2];          // contributions x / out-degree (x itself where that is 0), c[k & 1] read by superstep k
+    double *head, *tailp, *dpart, *seed_acc;
 };
 
 struct BpWork {
-    int64_t ntiles;
-    float *x[2], *c[2];
-    double *head, *tailp, *dsum, *dpart, *D[2];
-    int32_t *spill, *trow, *seed, *end;
+    float *c[2];
+    double *head, *tailp, *dpart, *seed_acc;
+    int32_t *seed, *end;
 };
 
 const BsVariant *bs_variants(int *n);
@@ -84,9 +90,9 @@ hipError_t bs_launch_superstep(const BsArgs &a, uint32_t k, uint32_t it, int gri
 hipError_t bp_launch_superstep(const BpArgs &a, uint32_t k, int grid, hipStream_t s);
 hipError_t bs_lane_reset(uint32_t *D, uint32_t *Mc, uint32_t *Mn, int64_t V, uint32_t B, uint32_t G, uint32_t lane,
                          int32_t src, hipStream_t s);
-hipError_t bp_lane_reset(float *x, float *c, double *D, const int32_t *outdeg, int64_t V, uint32_t B, uint32_t lane,
-                         int32_t seed, hipStream_t s);
-hipError_t bp_make_tiles(const int32_t *in_rp, int64_t V, int64_t ntiles, int32_t *trow, hipStream_t s);
+BpArgs bp_args_for(const DevGraph &d, const BpWork &w, float *x, uint32_t B, float damping);
+// Lane `lane` restarts from `seed` at superstep k; `old`: its previous seed (-1: none).
+hipError_t bp_lane_reset(const BpArgs &a, uint32_t k, int64_t V, uint32_t lane, int32_t seed, int32_t old, hipStream_t s);
 hipError_t lane_extract(const uint32_t *tile, int64_t V, uint32_t B, uint32_t lane, uint32_t *out, hipStream_t s);
 
 }  // namespace gx

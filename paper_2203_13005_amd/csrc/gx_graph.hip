@@ -162,6 +162,11 @@ using EdgeVec = std::vector<T, NoInit<T>>;
 
 struct HostImages {
     std::vector<int32_t> in_rp, outdeg, tile_row, slot;
+    std::vector<int2> nz;
+    std::vector<uint64_t> row_last;
+    std::vector<int32_t> tile_nz, dang;
+    std::vector<int4> cross;
+    int32_t cross_long = 0;
     EdgeVec<int32_t> in_col, pr_src;
     EdgeVec<uint32_t> in_w;
     EdgeVec<uint2> in_adj;
@@ -338,6 +343,31 @@ static void build_slots(const gx_graph_desc *d, HostImages &h) {
     }
 }
 
+// The rows with in-edges, where they end, the rows that cross tiles and the
+// dangling vertices with in-edges.
+static void build_rows(const gx_graph_desc *d, HostImages &h) {
+    const int64_t V = d->V, E = d->E, T = rows_tile(E), nt = rows_tiles(E);
+    h.row_last.assign((size_t)(E + 63) / 64 + 1, 0);
+    h.tile_nz.assign((size_t)nt + 1, 0);
+    std::vector<int4> few;
+    h.nz.reserve((size_t)std::min(V, E));
+    for (int64_t v = 0, t = 0; v < V; v++) {
+        const int32_t a = h.in_rp[v], b = h.in_rp[v + 1];
+        if (a == b) continue;
+        const int32_t od = d->row_ptr[v + 1] - d->row_ptr[v];
+        const int32_t at = (int32_t)h.nz.size();
+        for (; t * T < b && t < nt; t++) h.tile_nz[t] = at;  // tiles whose first edge is in this row
+        h.nz.push_back(make_int2((int32_t)v, od));
+        h.row_last[(b - 1) >> 6] |= uint64_t(1) << ((b - 1) & 63);
+        const int32_t t0 = (int32_t)(a / T), t1 = (int32_t)((b - 1) / T);
+        if (t1 - t0 >= ROWS_LONG) h.cross.push_back(make_int4((int32_t)v, od, t0, t1));
+        else if (t1 > t0) few.push_back(make_int4((int32_t)v, od, t0, t1));
+        if (od == 0) h.dang.push_back((int32_t)v);
+    }
+    h.cross_long = (int32_t)h.cross.size();
+    h.cross.insert(h.cross.end(), few.begin(), few.end());
+}
+
 // Pull tiles: tile t covers edges [t*T, (t+1)*T) of a CSR and owns the rows
 // whose first edge position falls in that range (the last tile also owns the
 // rows starting at E).
@@ -414,8 +444,8 @@ static void build_in_adj(HostImages &h) {
         at += n;
     }
     std::atomic<int64_t> next{0};  // rows differ in length: blocks are handed out one at a time
-    const int64_t step = 4096;
-    parallel_for(host_threads(), [&](int64_t, int64_t) {
+    const int64_t step = E < (1 << 18) ? V : 4096;
+    parallel_for((V + step - 1) / step, [&](int64_t, int64_t) {
         for (int64_t lo; (lo = next.fetch_add(step)) < V;)
             for (int64_t v = lo; v < std::min(V, lo + step); v++) {
                 const int32_t e0 = rp[v], n = rp[v + 1] - e0;
@@ -509,7 +539,12 @@ static void layout(const gx_graph_desc *desc, int64_t E_sym, Carver &c, DevGraph
         d->pr_tile_row = c.take<int32_t>(d->pr_ntiles + 1);
     }
     if (desc->needs & GX_NEED_IN) {
-        d->in_col = c.take<int32_t>(E);
+        d->in_col = c.take<int32_t>(E + 64);  // (read in whole groups of 16)
+        d->nz = c.take<int2>(std::min(V, E));
+        d->row_last = c.take<uint64_t>((E + 63) / 64 + 1);
+        d->tile_nz = c.take<int32_t>(rows_tiles(E) + 1);
+        d->cross = c.take<int4>(rows_tiles(E));
+        d->dang = c.take<int32_t>(std::min(V, E) + 64);
         d->outdeg = c.take<int32_t>(V);
         d->pr_src = c.take<int32_t>(E);
     }
@@ -545,30 +580,39 @@ static int64_t sym_bound(const gx_graph_desc *d) { return 2 * d->E; }
 // through three rotating pinned buffers on a dedicated copy stream.
 struct Uploader {
     static constexpr size_t BLOCK = size_t(16) << 20;
+    size_t block = BLOCK;  // bytes of a buffer (less for a small graph: pinning memory costs)
+    size_t used = 0;       // bytes of the current buffer taken: small arrays share one
     hipStream_t copy = nullptr;
     void *buf[3] = {nullptr, nullptr, nullptr};
     hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
     uint64_t idx = 0;
     hipError_t err = hipSuccess;
 
-    hipError_t open() {
+    hipError_t open(size_t total) {
+        block = std::min(BLOCK, align_up(std::max<size_t>(total, 1), size_t(64) << 10));
         if ((err = hipStreamCreateWithFlags(&copy, hipStreamNonBlocking)) != hipSuccess) return err;
         for (int i = 0; i < 3; i++) {
-            if ((err = hipHostMalloc(&buf[i], BLOCK, hipHostMallocDefault)) != hipSuccess) return err;
+            if ((err = hipHostMalloc(&buf[i], block, hipHostMallocDefault)) != hipSuccess) return err;
             if ((err = hipEventCreateWithFlags(&ev[i], hipEventDisableTiming)) != hipSuccess) return err;
         }
         return hipSuccess;
     }
+    // The current buffer is full: the next one, once its last copies are done.
+    void turn() {
+        err = hipEventRecord(ev[idx % 3], copy);
+        idx++;
+        used = 0;
+        if (err == hipSuccess) err = hipEventSynchronize(ev[idx % 3]);
+    }
     hipError_t put(void *dev, size_t bytes, const std::function<void(char *, size_t, size_t)> &fill) {
-        for (size_t off = 0; off < bytes && err == hipSuccess; off += BLOCK) {
-            size_t n = std::min(BLOCK, bytes - off);
-            int b = (int)(idx++ % 3);
-            if ((err = hipEventSynchronize(ev[b])) != hipSuccess) break;  // buffer b free again
-            fill(static_cast<char *>(buf[b]), off, n);                     // package block (host)
-            if ((err = hipMemcpyAsync(static_cast<char *>(dev) + off, buf[b], n, hipMemcpyHostToDevice, copy)) !=
-                hipSuccess)
-                break;
-            err = hipEventRecord(ev[b], copy);
+        for (size_t off = 0, n; off < bytes && err == hipSuccess; off += n) {
+            n = std::min(block, bytes - off);
+            if (used + n > block) turn();
+            if (err != hipSuccess) break;
+            char *at = static_cast<char *>(buf[idx % 3]) + used;
+            fill(at, off, n);  // package block (host)
+            err = hipMemcpyAsync(static_cast<char *>(dev) + off, at, n, hipMemcpyHostToDevice, copy);
+            used = std::min(block, align_up(used + n));
         }
         return err;
     }
@@ -647,6 +691,7 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
         build_tiles(h.in_rp, h.tile_row, pr_tile_for(desc));
         if (desc->needs & (GX_NEED_IN | GX_NEED_OUT)) build_slots(desc, h);
         if (desc->needs & GX_NEED_IN) {
+            build_rows(desc, h);
             h.pr_src.resize(desc->E);
             parallel_for(desc->E, [&](int64_t lo, int64_t hi) {
                 for (int64_t e = lo; e < hi; e++) h.pr_src[e] = h.slot[h.in_col[e]];
@@ -671,6 +716,10 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
     Carver c(dev_arena, arena_bytes);
     layout(desc, (int64_t)h.sym_col.size(), c, &g->d);
     g->d.pull_nsegs = (int64_t)h.pull_segs.size();
+    g->d.n_nz = (int64_t)h.nz.size();
+    g->d.n_cross = (int32_t)h.cross.size();
+    g->d.n_cross_long = h.cross_long;
+    g->d.n_dang = (int64_t)h.dang.size();
     g->d.sym_nsegs = (int64_t)h.sym_segs.size();
     g->needs = desc->needs;
     g->arena = dev_arena;
@@ -686,7 +735,7 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     Uploader up;
-    hipError_t e = up.open();
+    hipError_t e = up.open(c.used);
     const DevGraph &d = g->d;
     int64_t V = desc->V, E = desc->E;
     if (e == hipSuccess && d.out_rp) e = up.put_array((void *)d.out_rp, desc->row_ptr, (V + 1) * 4);
@@ -709,6 +758,11 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
     if (e == hipSuccess && d.in_col) {
         e = up.put_array((void *)d.in_col, h.in_col.data(), E * 4);
         if (e == hipSuccess) e = up.put_array((void *)d.outdeg, g->host_outdeg.data(), V * 4);
+        if (e == hipSuccess) e = up.put_array((void *)d.nz, h.nz.data(), h.nz.size() * sizeof(int2));
+        if (e == hipSuccess) e = up.put_array((void *)d.row_last, h.row_last.data(), h.row_last.size() * 8);
+        if (e == hipSuccess) e = up.put_array((void *)d.tile_nz, h.tile_nz.data(), h.tile_nz.size() * 4);
+        if (e == hipSuccess) e = up.put_array((void *)d.cross, h.cross.data(), h.cross.size() * sizeof(int4));
+        if (e == hipSuccess) e = up.put_array((void *)d.dang, h.dang.data(), h.dang.size() * 4);
         if (e == hipSuccess) e = up.put_array((void *)d.pr_src, h.pr_src.data(), E * 4);
     }
     if (e == hipSuccess && d.slot) e = up.put_array((void *)d.slot, h.slot.data(), V * 4);

@@ -88,6 +88,15 @@ constexpr int PULL_BIT_WORDS = PULL_BITS / 32;
 // row in it has more than PULL_SMALL entries).
 inline int64_t pull_seg_cap(int64_t E) { return E / PULL_SMALL + 1; }
 
+// Row ends of the in-CSR (batched PPR): rows without in-edges are left out,
+// a bit per in-edge marks the last one of its row.  The in-edges are cut into
+// tiles of rows_tile(E) edges; rows that cross tiles are listed.
+constexpr int ROWS_PIECES = 16;     // a sum of at least ROWS_LONG partials is cut into this many pieces
+constexpr int ROWS_LONG = 64;
+constexpr int ROWS_DANGLING = 512;  // tiles of dangling vertices at most
+inline int64_t rows_tile(int64_t E) { return E >= (int64_t(1) << 22) ? 128 : 64; }
+inline int64_t rows_tiles(int64_t E) { return (E + rows_tile(E) - 1) / rows_tile(E); }
+
 // Label propagation: vertices are grouped by the number of distinct
 // neighbours d.  Classes 0..4 take d <= 4, 8, 16, 32, 64 and run as lane
 // groups of that width; class 5 (d <= LP_MID_MAX) runs one workgroup per
@@ -115,6 +124,15 @@ struct DevGraph {
     // vertex after them in id order; pr_src = the slot of each in-edge's source
     const int32_t *pr_src = nullptr;
     const int32_t *slot = nullptr;
+    const int2 *nz = nullptr;          // {row, out-degree} of the rows with in-edges, ascending
+    int64_t n_nz = 0;
+    const uint64_t *row_last = nullptr;  // bit e: in-edge e is its row's last
+    const int32_t *tile_nz = nullptr;  // per tile: position in nz of the row its first edge belongs to
+    const int4 *cross = nullptr;       // rows crossing tiles: {row, out-degree, first tile, last tile},
+    int32_t n_cross = 0;               // those with at least ROWS_LONG further tiles
+    int32_t n_cross_long = 0;          // first
+    const int32_t *dang = nullptr;     // vertices with in-edges and without out-edges
+    int64_t n_dang = 0;
     int32_t pr_tile = PR_TILE_MAX;  // in-edges per PageRank tile
     int32_t pr_ntiles = 0;
     const int32_t *pr_tile_row = nullptr;  // [pr_ntiles + 1]

@@ -104,6 +104,7 @@ struct Pool {
     BsWork bw{};
     uint32_t *lane_cnt = nullptr;
     // PPR
+    float *x = nullptr;
     BpWork pw{};
     // result staging: a finished lane is copied into a free slot (device, then
     // pinned host memory) on the pool's stream, and the completion thread
@@ -121,6 +122,7 @@ struct Pool {
     std::vector<int64_t> lane_age;   // supersteps since the lane joined
     std::vector<int64_t> lane_done;  // finished, waiting for a staging slot: supersteps it took (-1 = running)
     std::vector<int32_t> seeds;      // PPR seed per lane (-1 = free)
+    std::vector<int32_t> last_seed;  // PPR: the lane's latest seed (-1 = none yet)
     std::vector<uint32_t> ends;      // PPR: first superstep the lane no longer runs (mod 2^32)
     uint32_t k = 0;                  // supersteps run (buffer parity)
     bool in_flight = false;
@@ -141,6 +143,7 @@ size_t pool_bytes(const gx_graph *g, int32_t algo, uint32_t B, uint32_t epoch_ma
         bs_layout(d, B, c, &w);
         c.take<uint32_t>((size_t)epoch_max * B);
     } else {
+        c.take<float>((size_t)d.V * B);
         BpWork w;
         bp_layout(d, B, c, &w);
     }
@@ -300,6 +303,7 @@ struct gx_server {
         p->lane_age.assign(B, 0);
         p->lane_done.assign(B, -1);
         p->seeds.assign(B, -1);
+        p->last_seed.assign(B, -1);
         p->ends.assign(B, 0u);
         const DevGraph &d = g->d;
         Carver c(mem, bytes);
@@ -316,6 +320,7 @@ struct gx_server {
             bs_layout(d, B, c, &p->bw);
             p->lane_cnt = c.take<uint32_t>((size_t)epoch_max(algo) * B);
         } else {
+            p->x = c.take<float>((size_t)d.V * B);
             bp_layout(d, B, c, &p->pw);
         }
         for (int i = 0; i < Pool::SLOTS; i++) p->stage[i] = c.take<uint32_t>(d.V);
@@ -329,14 +334,11 @@ struct gx_server {
                      hipMemsetAsync(p->bw.ctl, 0, sizeof(BsCtl), s) == hipSuccess;
             } else {
                 const size_t n = (size_t)d.V * B * 4;
-                ok = hipMemsetAsync(p->pw.x[0], 0, n, s) == hipSuccess &&
-                     hipMemsetAsync(p->pw.x[1], 0, n, s) == hipSuccess &&
+                ok = hipMemsetAsync(p->x, 0, n, s) == hipSuccess &&
                      hipMemsetAsync(p->pw.c[0], 0, n, s) == hipSuccess &&
                      hipMemsetAsync(p->pw.c[1], 0, n, s) == hipSuccess &&
-                     hipMemsetAsync(p->pw.D[0], 0, B * 8, s) == hipSuccess &&
-                     hipMemsetAsync(p->pw.D[1], 0, B * 8, s) == hipSuccess &&
-                     hipMemsetAsync(p->pw.seed, 0xFF, B * 4, s) == hipSuccess &&
-                     bp_make_tiles(d.in_rp, d.V, p->pw.ntiles, p->pw.trow, s) == hipSuccess;
+                     hipMemsetAsync(p->pw.seed_acc, 0, B * 8, s) == hipSuccess &&
+                     hipMemsetAsync(p->pw.seed, 0xFF, B * 4, s) == hipSuccess;
             }
             ok = ok && hipStreamSynchronize(s) == hipSuccess;
         }
@@ -372,31 +374,8 @@ struct gx_server {
     }
 
     BpArgs bp_args(Pool &p) {
-        const DevGraph &d = p.g->d;
-        BpArgs a{};
-        a.in_rp = d.in_rp;
-        a.in_col = d.in_col;
-        a.outdeg = d.outdeg;
-        a.trow = p.pw.trow;
-        a.ntiles = p.pw.ntiles;
-        a.V = d.V;
-        a.E = d.E;
-        a.B = p.B;
-        a.Bw = p.B;
-        a.d = cfg.damping;
-        a.seed = p.pw.seed;
+        BpArgs a = bp_args_for(p.g->d, p.pw, p.x, p.B, cfg.damping);
         a.end = p.pw.end;
-        a.x[0] = p.pw.x[0];
-        a.x[1] = p.pw.x[1];
-        a.c[0] = p.pw.c[0];
-        a.c[1] = p.pw.c[1];
-        a.head = p.pw.head;
-        a.tailp = p.pw.tailp;
-        a.dsum = p.pw.dsum;
-        a.dpart = p.pw.dpart;
-        a.D[0] = p.pw.D[0];
-        a.D[1] = p.pw.D[1];
-        a.spill = p.pw.spill;
         return a;
     }
 
@@ -411,8 +390,8 @@ struct gx_server {
             // reach the device with the next epoch's lane table
             p.seeds[lane] = q.source;
             p.ends[lane] = p.k + (uint32_t)cfg.ppr_iters;
-            e = bp_lane_reset(p.pw.x[p.k & 1], p.pw.c[p.k & 1], p.pw.D[p.k & 1], d.outdeg, d.V, p.B, lane, q.source,
-                              p.stream);
+            e = bp_lane_reset(bp_args(p), p.k, d.V, lane, q.source, p.last_seed[lane], p.stream);
+            p.last_seed[lane] = q.source;
         }
         if (e != hipSuccess) return false;
         p.lane_q[lane] = q.id;
@@ -442,9 +421,8 @@ struct gx_server {
             return false;
         }
         SQuery &q = it->second;
-        // a PPR lane froze after its last superstep: its values are in x[end & 1]
-        const uint32_t *tile =
-            p.algo == GX_SSSP ? p.D : reinterpret_cast<const uint32_t *>(p.pw.x[p.ends[lane] & 1]);
+        // (a PPR lane's ranks were written in its last superstep)
+        const uint32_t *tile = p.algo == GX_SSSP ? p.D : reinterpret_cast<const uint32_t *>(p.x);
         hipError_t e = lane_extract(tile, d.V, p.B, lane, p.stage[slot], p.stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(p.host_stage[slot], p.stage[slot], d.V * 4, hipMemcpyDeviceToHost, p.stream);
