@@ -165,7 +165,7 @@ def batched_bytes_per_superstep(np, g, fronts, B):
 
 
 def bench_batched(gx, torch, np, gen, steps=3):
-    """256 seeded sources on R-MAT scale 20 (seed 4): one persistent batched
+    """256 seeded sources on R-MAT scale 20 (seed 4): one batched
     launch (autotuned) against 256 sequential plain solves on the same GPU;
     every lane is compared with its plain solve."""
     import paper_2203_13005_amd as m
@@ -240,7 +240,7 @@ def bench_batched(gx, torch, np, gen, steps=3):
 
 def bench_batched_ppr(gx, torch, g, dg, src, iters=50, reps=3):
     """Personalised PageRank lanes (50 iterations) on the same graph: 64 and
-    256 seeds in one persistent launch each."""
+    256 seeds in one run each."""
     out = {}
     for B in (64, 256):
         seeds = src[:B]

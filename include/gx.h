@@ -451,8 +451,8 @@ gx_status gx_balance_split(const double *c, int32_t m, double D, double *d_out);
 
 /* ---------------------------------------------------------------------
  * Batched lanes: B independent single-source SSSP (or personalised
- * PageRank) solves over one resident graph, run as one persistent kernel
- * over a [V x B] state tile (B contiguous per vertex).  Generalises the
+ * PageRank) solves over one resident graph, carried together in a [V x B]
+ * state tile (B contiguous per vertex).  Generalises the
  * evaluation's several SSSP sources computed simultaneously (Section
  * "Setup", first footnote).
  * --------------------------------------------------------------------- */
@@ -461,7 +461,7 @@ typedef struct gx_tune {
     uint32_t block;   /* threads per workgroup (64..1024, multiple of 64); 0 = default */
     uint32_t tile;    /* edges per work tile; 0 = default */
     uint32_t width;   /* lanes per pass (32, 64, 128 or 256, <= B); 0 = default */
-    uint32_t grid;    /* workgroups of the persistent grid; 0 = occupancy bound */
+    uint32_t grid;    /* workgroups of the push; 0 = as many as are resident */
 } gx_tune;
 
 /* Device workspace bytes gx_batch_run needs (excluding the output tile). */

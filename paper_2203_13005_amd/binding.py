@@ -467,7 +467,7 @@ class State:
 
 def batch_run(graph: DeviceGraph, algo: int, sources, damping: float = 0.85, iters: int = 50,
               tune: Tune | None = None, out=None, stream=None):
-    """B lanes in one persistent launch; returns ([V, B] tensor, RunStats)."""
+    """B lanes run together; returns ([V, B] tensor, RunStats)."""
     import torch
     src = np.ascontiguousarray(sources, np.int32)
     B = len(src)

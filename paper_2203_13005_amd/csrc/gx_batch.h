@@ -9,32 +9,35 @@ namespace gx {
 
 constexpr int BS_MIN_TILE = 1024;  // smallest SSSP work tile among the variants
 constexpr int BP_TILE = 256;       // tile the PPR tunings name (the graph fixes the tiles)
-constexpr double BARRIER_LIMIT_S = 20.0;  // longest wait of a grid barrier before it reports an error
 
+// Counters of four consecutive supersteps, slot k & 3; superstep k clears the
+// next one's.
 struct BsCtl {
-    GridBar bar;
-    unsigned long long list[4];     // per superstep slot: (entries << 32) | units
+    unsigned long long list[4];     // (entries << 32) | units
     unsigned long long changed[4];  // (vertex, lane) activations
-    unsigned int steps;             // supersteps run by the last launch
-    unsigned int pad[3];
+    uint32_t steps;                 // supersteps up to and including the first that changed nothing (0: none yet)
+    uint32_t pad[3];
+    uint32_t inv_low[4][256];       // pull: ~(smallest active distance) of every lane, 0: none active
 };
 
 struct BsArgs {
     const int32_t *rp;
     const uint2 *adj;
+    // pull (in_adj NULL: push only)
+    const uint2 *in_adj;
+    const uint4 *segs, *packs;
+    const int32_t *slot;
+    int64_t nsegs, npacks;
+    uint32_t pull_units;  // a superstep with at least this many units pulls
     int64_t V;
     uint32_t B, l0, G;  // lane stride, first lane of the pass, 32-lane groups in the pass
     uint32_t *D;
     uint32_t *M[2];
     uint4 *list;
-    uint4 *S;
+    uint4 *S;           // every row's distances at the superstep's start, by slot
     uint32_t *tile_start;
     BsCtl *ctl;
-    uint32_t max_steps;
-    uint32_t k0;          // global superstep index of the first superstep (mask parity)
-    uint32_t *lane_cnt;   // optional [max_steps x B] activations per lane and superstep
-    uint32_t stop_when_idle;
-    unsigned long long bar_ticks;  // wall-clock ticks a grid barrier waits before reporting an error
+    uint32_t *lane_cnt;   // optional [supersteps x B], 0 before: nonzero where a lane changed in a superstep
 };
 
 struct BsWork {
@@ -48,7 +51,7 @@ struct BsWork {
 
 struct BsVariant {
     uint32_t block, vt;
-    const void *fn;
+    const void *fn;  // k_bs_relax of that shape
 };
 
 struct BpArgs {
@@ -79,17 +82,17 @@ struct BpWork {
 };
 
 const BsVariant *bs_variants(int *n);
-int coop_grid(const void *kernel, int block, int num_cus, int want, int max_per_cu);
+BsArgs bs_args_for(const DevGraph &d, const BsWork &w, uint32_t *D, uint32_t B, uint32_t l0, uint32_t G);
 void bs_layout(const DevGraph &d, uint32_t B, Carver &c, BsWork *w);
 void bp_layout(const DevGraph &d, uint32_t B, Carver &c, BpWork *w);
-hipError_t launch_coop(const void *kernel, int grid, int block, void *args, hipStream_t s);
-unsigned long long barrier_limit_ticks(int device);
 gx_tune default_tune(uint32_t B);
 
-hipError_t bs_launch_superstep(const BsArgs &a, uint32_t k, uint32_t it, int grid, hipStream_t s);
+// Superstep k (lane_cnt row `it`); grid: workgroups of the push, 0 = as many as are resident.
+hipError_t bs_launch_superstep(const BsArgs &a, uint32_t k, uint32_t it, const BsVariant &v, int grid, int cus,
+                               hipStream_t s);
 hipError_t bp_launch_superstep(const BpArgs &a, uint32_t k, int grid, hipStream_t s);
-hipError_t bs_lane_reset(uint32_t *D, uint32_t *Mc, uint32_t *Mn, int64_t V, uint32_t B, uint32_t G, uint32_t lane,
-                         int32_t src, hipStream_t s);
+// Lane `lane` restarts from `src` at superstep k.
+hipError_t bs_lane_reset(const BsArgs &a, uint32_t k, uint32_t lane, int32_t src, hipStream_t s);
 BpArgs bp_args_for(const DevGraph &d, const BpWork &w, float *x, uint32_t B, float damping);
 // Lane `lane` restarts from `seed` at superstep k; `old`: its previous seed (-1: none).
 hipError_t bp_lane_reset(const BpArgs &a, uint32_t k, int64_t V, uint32_t lane, int32_t seed, int32_t old, hipStream_t s);

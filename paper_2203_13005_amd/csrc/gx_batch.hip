@@ -1,24 +1,28 @@
 // Batched lanes: B independent single-source problems over one resident
-// graph, carried in a [V x B] state tile (B contiguous per vertex) by one
-// persistent cooperative kernel per pass.  The evaluation of the paper runs
-// several SSSP sources simultaneously to raise the arithmetic intensity
-// (Section "Setup", first footnote); here the lanes are independent
-// problems, each equal to its plain solve.
+// graph, carried in a [V x B] state tile (B contiguous per vertex).  The
+// evaluation of the paper runs several SSSP sources simultaneously to raise
+// the arithmetic intensity (Section "Setup", first footnote); here the lanes
+// are independent problems, each equal to its plain solve.
 //
-// SSSP (k_bsssp): per superstep
+// SSSP: per superstep three ordinary launches
 //   compaction: every (vertex, 32-lane group) whose lane mask is non-zero
-//     and that has out-edges becomes one active entry; its 32 start-of-
-//     superstep distances are copied to a snapshot row (Jacobi semantics per
-//     lane); one 64-bit atomic per workgroup chunk reserves entries and edge
-//     offsets; tiles of equal (entry, edge) work units record where they
-//     start.
-//   relaxation: 8 threads per work unit handle the unit's 32 lanes (4 each,
-//     one 16-byte load of the destination's group); improvements are
-//     folded by atomicMin per lane (no result awaited: a candidate below a
-//     value read during the superstep already proves the lane changes), and
-//     the group's improved-lane bits by one atomicOr into the next mask.
-//   A grid barrier separates the phases; the loop ends when a superstep
-//   activates no (vertex, lane) pair.
+//     and that has out-edges becomes one active entry and its 32 distances
+//     are copied to its vertex's slot of the snapshot (Jacobi semantics per
+//     lane; a distance changes only when its vertex is active next, so the
+//     snapshot then holds every row); one 64-bit atomic per workgroup chunk
+//     reserves entries and edge offsets; tiles of equal (entry, edge) work
+//     units record where they start.
+//   push (small frontiers): 8 threads per work unit handle the unit's 32
+//     lanes (4 each, one 16-byte load of the destination's group);
+//     improvements are folded by atomicMin per lane (no result awaited: a
+//     candidate below a value read during the superstep already proves the
+//     lane changes), and the group's improved-lane bits by one atomicOr into
+//     the next mask.
+//   pull (large frontiers): a lane group takes a run of in-edges, reads each
+//     source's whole row and takes the minimum, so a row is written once and
+//     without atomics; see k_bs_pull.
+//   The host enqueues supersteps in groups and reads the counters back once
+//   per group; a superstep without active lanes changes nothing.
 // PPR: per superstep three ordinary launches: a pull over equal in-edge tiles
 //   (a lane group per tile, batch lanes across the group), rows crossing
 //   tiles completed in tile order, and the seeds' rows, which take the
@@ -51,19 +55,28 @@ struct BsShared {
     uint32_t base[T + 1];
     uint32_t mask[T + 1];
     uint32_t g[T + 1];
-    unsigned long long scan[NW];
-    unsigned long long base64;
+    uint32_t srow[T + 1];
     int32_t red[NW];
     unsigned long long cnt[NW];
     uint32_t lane[256];
-    unsigned int flag;
 };
 
-// Phase 1 of batched superstep k: active (vertex, group) pairs -> entries,
-// snapshots, tile starts.  Grid-strided over the V*G mask words.
-template <int BLOCK, int VT>
-__device__ __forceinline__ void bs_compact(const BsArgs &a, uint32_t k, BsShared<BLOCK, VT> &sh) {
-    constexpr int T = BLOCK * VT;
+// Compaction of batched superstep k: active (vertex, group) pairs -> entries,
+// snapshot rows, tile starts (tiles of `tile` units).  Grid-strided over the
+// V*G mask words, CW per thread (1 for a small graph, which then still has a
+// workgroup per CU).  Once the units counted reach pull_units
+// the superstep pulls and the rest of the entries is not written.  The rows
+// are copied by 8 threads each, which also take every lane's smallest active
+// distance (for the pull) into the counters.
+constexpr int BS_CBLOCK = 256;
+constexpr int64_t BS_WIDE_FROM = int64_t(1) << 20;  // mask words
+
+template <int CW>
+__global__ __launch_bounds__(BS_CBLOCK) void k_bs_compact(BsArgs a, uint32_t k, uint32_t tile) {
+    __shared__ unsigned long long s_scan[BS_CBLOCK / 64];
+    __shared__ unsigned long long s_base;
+    __shared__ uint32_t s_low[256];
+    __shared__ uint32_t s_word[BS_CBLOCK * CW], s_vg[BS_CBLOCK * CW], s_row[BS_CBLOCK * CW];
     const int tid = threadIdx.x;
     const int64_t VG = a.V * (int64_t)a.G;
     const int slot = k & 3;
@@ -72,43 +85,93 @@ __device__ __forceinline__ void bs_compact(const BsArgs &a, uint32_t k, BsShared
     if (blockIdx.x == 0 && tid == 0) {
         a.ctl->list[(k + 1) & 3] = 0;
         a.ctl->changed[(k + 1) & 3] = 0;
+        if (k > 0 && a.ctl->changed[(k - 1) & 3] == 0 && a.ctl->steps == 0) a.ctl->steps = k;
     }
-    for (int64_t base = (int64_t)blockIdx.x * BLOCK; base < VG; base += (int64_t)gridDim.x * BLOCK) {
-        const int64_t i = base + tid;
-        uint32_t word = 0, u = 0, g = 0;
-        int32_t r0 = 0, deg = 0;
-        if (i < VG) {
-            word = Mc[i];
-            Mn[i] = 0u;
-            if (word) {
-                u = (uint32_t)(i / a.G);
-                g = (uint32_t)(i % a.G);
-                r0 = a.rp[u];
-                deg = a.rp[u + 1] - r0;
-            }
-        }
-        const bool has = word && deg > 0;
-        unsigned long long mine = has ? ((1ull << 32) | (uint32_t)deg) : 0ull, total;
-        unsigned long long pre = block_excl_scan_u64(mine, &total, sh.scan);
-        if (tid == 0) sh.base64 = total ? atomicAdd(&a.ctl->list[slot], total) : 0ull;
-        __syncthreads();
-        if (has) {
-            unsigned long long pos = sh.base64 + pre;
-            uint32_t idx = (uint32_t)(pos >> 32), off = (uint32_t)pos;
-            a.list[idx] = make_uint4(off, (uint32_t)(r0 - (int32_t)off), word, g);
-            const uint4 *src = reinterpret_cast<const uint4 *>(a.D + (size_t)u * a.B + a.l0 + g * 32);
-            uint4 *dst = a.S + (size_t)idx * 8;
+    if (blockIdx.x == 0) a.ctl->inv_low[(k + 1) & 3][tid] = 0;
+    s_low[tid] = INF;
+    constexpr int64_t CHUNK = BS_CBLOCK * CW;
+    for (int64_t base = (int64_t)blockIdx.x * CHUNK; base < VG; base += (int64_t)gridDim.x * CHUNK) {
+        uint32_t word[CW], u[CW], g[CW], row[CW], any = 0;
+        int32_t r0[CW], deg[CW];
+        const int64_t i0 = base + (int64_t)tid * CW;
 #pragma unroll
-            for (int q = 0; q < 8; q++) dst[q] = src[q];
-            uint32_t t0 = (off + T - 1) / T, t1 = (off + (uint32_t)deg - 1) / T;
-            for (uint32_t t = t0; t <= t1; t++) a.tile_start[t] = idx;
+        for (int j = 0; j < CW; j++) word[j] = 0;
+#pragma unroll
+        for (int j = 0; j < CW; j++)
+            if (i0 + j < VG) {
+                word[j] = Mc[i0 + j];
+                Mn[i0 + j] = 0u;
+            }
+#pragma unroll
+        for (int j = 0; j < CW; j++) any |= word[j];
+        if (!__syncthreads_or(any != 0)) continue;
+        unsigned long long mine = 0, total;
+        u[0] = VG < (int64_t(1) << 32) ? (uint32_t)i0 / a.G : (uint32_t)(i0 / a.G);
+        g[0] = (uint32_t)(i0 - (int64_t)u[0] * a.G);
+#pragma unroll
+        for (int j = 0; j < CW; j++) {
+            if (j > 0) {
+                const bool wrap = g[j - 1] + 1 == a.G;
+                g[j] = wrap ? 0u : g[j - 1] + 1;
+                u[j] = u[j - 1] + (wrap ? 1u : 0u);
+            }
+            r0[j] = deg[j] = 0;
+            row[j] = 0;
+            if (word[j]) {
+                r0[j] = a.rp[u[j]];
+                deg[j] = a.rp[u[j] + 1] - r0[j];
+                row[j] = (uint32_t)a.slot[u[j]] * a.G + g[j];
+            }
+            if (deg[j] > 0) mine += (1ull << 32) | (uint32_t)deg[j];
         }
+        const unsigned long long pre = block_excl_scan_u64(mine, &total, s_scan);
+        if (tid == 0) s_base = total ? atomicAdd(&a.ctl->list[slot], total) : 0ull;
+        uint32_t e = (uint32_t)(pre >> 32);
+#pragma unroll
+        for (int j = 0; j < CW; j++)
+            if (deg[j] > 0) {
+                s_word[e] = word[j];
+                s_vg[e] = (uint32_t)(i0 + j - base);
+                s_row[e++] = row[j];
+            }
         __syncthreads();
+        const uint32_t n = (uint32_t)(total >> 32) * 8;
+        for (uint32_t i = tid; i < n; i += BS_CBLOCK) {
+            const uint32_t q = i & 7, w = s_word[i / 8] >> (4 * q);
+            const uint64_t vg = (uint64_t)base + s_vg[i / 8];
+            const uint64_t v = VG < (int64_t(1) << 32) ? (uint64_t)((uint32_t)vg / a.G) : vg / a.G;
+            const uint32_t gg = (uint32_t)(vg - v * a.G);
+            const uint4 x = *reinterpret_cast<const uint4 *>(a.D + (size_t)v * a.B + a.l0 + gg * 32 + q * 4);
+            a.S[(size_t)s_row[i / 8] * 8 + q] = x;
+            const uint32_t xv[4] = {x.x, x.y, x.z, x.w};
+            if (a.in_adj)
+#pragma unroll
+                for (int j = 0; j < 4; j++)
+                    if (((w >> j) & 1u) && xv[j] < s_low[gg * 32 + q * 4 + j]) atomicMin(&s_low[gg * 32 + q * 4 + j], xv[j]);
+        }
+        unsigned long long pos = s_base + pre;
+        const bool pulls = (uint32_t)(s_base + total) >= a.pull_units;
+        __syncthreads();
+        if (pulls) continue;
+#pragma unroll
+        for (int j = 0; j < CW; j++) {
+            if (deg[j] <= 0) continue;
+            const uint32_t idx = (uint32_t)(pos >> 32), off = (uint32_t)pos;
+            a.list[idx] = make_uint4(off, (uint32_t)(r0[j] - (int32_t)off), word[j], row[j]);
+            const uint32_t t0 = (off + tile - 1) / tile, t1 = (off + (uint32_t)deg[j] - 1) / tile;
+            for (uint32_t t = t0; t <= t1; t++) a.tile_start[t] = idx;
+            pos += (1ull << 32) | (uint32_t)deg[j];
+        }
+    }
+    __syncthreads();
+    if (s_low[tid] != INF) {
+        uint32_t *p = &a.ctl->inv_low[slot][tid];
+        if (~s_low[tid] > *p) atomicMax(p, ~s_low[tid]);  // (a stale read only costs an atomic)
     }
 }
 
-// Phase 2 of batched superstep k: relax the equal tiles of (entry, edge)
-// work units; `it` indexes the per-lane activation counters.
+// Push of batched superstep k: relax the equal tiles of (entry, edge) work
+// units; `it` indexes the per-lane activation counters.
 template <int BLOCK, int VT>
 __device__ __forceinline__ void bs_relax(const BsArgs &a, uint32_t k, uint32_t it, BsShared<BLOCK, VT> &sh) {
     constexpr int T = BLOCK * VT;
@@ -124,9 +187,16 @@ __device__ __forceinline__ void bs_relax(const BsArgs &a, uint32_t k, uint32_t i
         for (int q = tid; q < 256; q += BLOCK) sh.lane[q] = 0;
     __syncthreads();
     const int sub = tid & 7;
-    for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const uint32_t e0 = t * T;
+    // a small frontier has fewer tiles than the grid has workgroups: each tile
+    // is then shared by `parts` of them
+    constexpr int UB = 4;
+    const uint32_t parts = min((uint32_t)(T / (UNITS * UB)), max(1u, gridDim.x / max(1u, ntiles)));
+    for (uint32_t tp = blockIdx.x; tp < ntiles * parts; tp += gridDim.x) {
+        const uint32_t t = tp / parts, e0 = t * T;
         const int n = (int)min((uint32_t)T, EF - e0);
+        const int per = (int)((T / parts + UNITS * UB - 1) / (UNITS * UB)) * (UNITS * UB);
+        const int lo = (int)(tp % parts) * per, hi = min(n, lo + per);
+        if (lo >= n) continue;
         const uint32_t s0 = a.tile_start[t];
         const uint32_t s1 = (t + 1 < ntiles) ? a.tile_start[t + 1] : L - 1;
         const int m = (int)(s1 - s0) + 1;
@@ -136,7 +206,8 @@ __device__ __forceinline__ void bs_relax(const BsArgs &a, uint32_t k, uint32_t i
             uint4 en = a.list[s0 + q];
             sh.base[q] = en.y + e0;
             sh.mask[q] = en.z;
-            sh.g[q] = en.w;
+            sh.srow[q] = en.w;
+            sh.g[q] = en.w % a.G;
             uint32_t rel = en.x - e0;
             if (q > 0 && rel < (uint32_t)n) sh.own[rel] = q;
         }
@@ -147,23 +218,22 @@ __device__ __forceinline__ void bs_relax(const BsArgs &a, uint32_t k, uint32_t i
         // loads unconditional (units past the tile's end repeat its last
         // unit with no lanes).  The lane minima go out as atomics whose
         // results are not awaited; only the mask atomics return, once.
-        constexpr int UB = 4;
-        for (int p0 = tid >> 3; p0 < n; p0 += UNITS * UB) {
+        for (int p0 = lo + (tid >> 3); p0 < hi; p0 += UNITS * UB) {
             uint2 ed[UB];
-            uint32_t my4[UB], gq[UB], jq[UB];
+            uint32_t my4[UB], gq[UB], sq[UB];
 #pragma unroll
             for (int q = 0; q < UB; q++) {
                 const int p = min(p0 + q * UNITS, n - 1);
                 const int j = sh.own[p];
-                jq[q] = (uint32_t)j;
+                sq[q] = sh.srow[j];
                 gq[q] = sh.g[j];
-                my4[q] = (p0 + q * UNITS < n) ? (sh.mask[j] >> (sub * 4)) & 15u : 0u;
+                my4[q] = (p0 + q * UNITS < hi) ? (sh.mask[j] >> (sub * 4)) & 15u : 0u;
                 ed[q] = a.adj[sh.base[j] + (uint32_t)p];
             }
             uint4 sn[UB], cur[UB];
 #pragma unroll
             for (int q = 0; q < UB; q++) {
-                sn[q] = a.S[(size_t)(s0 + jq[q]) * 8 + sub];
+                sn[q] = a.S[(size_t)sq[q] * 8 + sub];
                 cur[q] = *reinterpret_cast<const uint4 *>(a.D + (size_t)ed[q].x * a.B + a.l0 + gq[q] * 32 + sub * 4);
             }
             uint32_t cand[UB][4], word[UB];
@@ -219,35 +289,165 @@ __device__ __forceinline__ void bs_relax(const BsArgs &a, uint32_t k, uint32_t i
     }
 }
 
-// One persistent cooperative launch runs supersteps until one activates no
-// (vertex, lane) pair or max_steps have run; grid barriers separate phases.
-template <int BLOCK, int VT>
-__global__ __launch_bounds__(BLOCK) void k_bsssp(BsArgs a) {
-    __shared__ BsShared<BLOCK, VT> sh;
-    uint32_t k = a.k0;
-    for (uint32_t it = 0; it < a.max_steps; it++, k++) {
-        bs_compact<BLOCK, VT>(a, k, sh);
-        if (!grid_sync(&a.ctl->bar, gridDim.x, &sh.flag, a.bar_ticks)) return;
-        bs_relax<BLOCK, VT>(a, k, it, sh);
-        if (!grid_sync(&a.ctl->bar, gridDim.x, &sh.flag, a.bar_ticks)) return;
-        const unsigned long long ch =
-            __hip_atomic_load(&a.ctl->changed[k & 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl->steps = it + 1;
-        if (ch == 0 && a.stop_when_idle) break;
-    }
-}
-
-// The same phases as ordinary launches (serving: several pools overlap on
-// their own streams, so no launch may rely on grid-wide co-residency).
-template <int BLOCK, int VT>
-__global__ __launch_bounds__(BLOCK) void k_bs_compact(BsArgs a, uint32_t k) {
-    __shared__ BsShared<BLOCK, VT> sh;
-    bs_compact<BLOCK, VT>(a, k, sh);
-}
 template <int BLOCK, int VT>
 __global__ __launch_bounds__(BLOCK) void k_bs_relax(BsArgs a, uint32_t k, uint32_t it) {
     __shared__ BsShared<BLOCK, VT> sh;
-    bs_relax<BLOCK, VT>(a, k, it, sh);
+    const uint32_t units = (uint32_t)a.ctl->list[k & 3];
+    if (units > 0 && units < a.pull_units) bs_relax<BLOCK, VT>(a, k, it, sh);
+}
+
+// Pull of batched superstep k.  A group of W lanes (W = 32 for one 32-lane
+// group, else 64 with LPT lanes per thread) takes the in-edges of a segment
+// of a long row or of a pack of short rows, 8 at a time: the rows of the 8
+// sources are loaded (by slot, so the rows of the vertices with the most
+// out-edges lie together), then folded in turn; an entry names its row.  A
+// finished row's improved lanes are stored and their bits, a ballot, become
+// its next mask; rows of several segments merge by atomics.  What an inactive
+// lane of a source sends was merged before and lowers nothing.  The entries
+// of a segment ascend by weight: 64 lanes of it end where none of them can
+// still fall, the smallest active distance of each lane plus the weight being
+// no smaller than the lane's best (a lane without active vertices needs
+// nothing).
+//
+// Bound by the gathered rows.  R-MAT scale 20, 256 lanes: the first pull of a
+// solve takes 2.33 ms (16 M rows of 1 KiB: 7 TB/s), the eight after it 1.73 to
+// 0.56 ms.  The solve took 97 ms when every superstep pushed, with an atomic
+// per improving lane, in one persistent launch of 8 waves per CU; 14.7 ms now.
+template <int W, int LPT>
+__global__ __launch_bounds__(256) void k_bs_pull(BsArgs a, uint32_t k, uint32_t it) {
+    if ((uint32_t)a.ctl->list[k & 3] < a.pull_units) return;
+    constexpr int NG = 64 / W, EB = LPT == 1 ? 16 : 8;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane / W;
+    const uint32_t b0 = (uint32_t)(lane % W), width = a.G * 32;
+    uint32_t *Mn = a.M[(k + 1) & 1];
+    const uint32_t *S = reinterpret_cast<const uint32_t *>(a.S);
+    uint32_t cl[LPT], cnt[LPT], low[LPT];
+    bool has[LPT];
+#pragma unroll
+    for (int i = 0; i < LPT; i++) {
+        has[i] = b0 + 64u * i < width;
+        cl[i] = min(b0 + 64u * i, width - 1);
+        cnt[i] = 0;
+        low[i] = has[i] ? ~a.ctl->inv_low[k & 3][cl[i]] : INF;
+    }
+    const int64_t total = a.nsegs + a.npacks, nwaves = (int64_t)gridDim.x * 4;
+    for (int64_t t0 = ((int64_t)blockIdx.x * 4 + wv) * NG; t0 < total; t0 += nwaves * NG) {
+        const int64_t t = W == 64 ? (int64_t)__builtin_amdgcn_readfirstlane((int)t0) : t0 + g;
+        const bool on = t < total;
+        const int64_t tq = on ? t : total - 1;
+        const bool seg = tq < a.nsegs;
+        const uint4 un = seg ? a.segs[tq] : a.packs[tq - a.nsegs];
+        const bool atomic = seg && !(un.w & 0x100u);
+        uint32_t row = seg ? un.x : 0xFFFFFFFFu, p = seg ? un.y : un.x;
+        const uint32_t end = seg ? un.z : un.y;
+        uint32_t acc[LPT], cur[LPT];
+#pragma unroll
+        for (int i = 0; i < LPT; i++) {
+            acc[i] = INF;
+            cur[i] = seg ? a.D[(size_t)un.x * a.B + a.l0 + cl[i]] : 0u;
+        }
+        auto close = [&]() {  // the row's lanes below their value
+#pragma unroll
+            for (int i = 0; i < LPT; i++) {
+                const bool imp = on && has[i] && acc[i] < cur[i];
+                const unsigned long long m = __ballot(imp);
+                uint32_t *dp = a.D + (size_t)row * a.B + a.l0 + cl[i];
+                uint32_t *mp = Mn + (size_t)row * a.G + cl[i] / 32;
+                const uint32_t word = (uint32_t)(m >> (lane & 32));
+                if (imp) {
+                    if (!atomic) {
+                        *dp = acc[i];
+                        cnt[i]++;
+                    } else {
+                        atomicMin(dp, acc[i]);
+                    }
+                }
+                if (word) {
+                    uint32_t before = 0;
+                    if (!atomic) {
+                        if ((lane & 31) == 0) *mp = word;
+                    } else {
+                        if ((lane & 31) == 0) before = atomicOr(mp, word);
+                        before = __shfl(before, lane & 32, 64);
+                        cnt[i] += ((word & ~before) >> (lane & 31)) & 1u;  // counted by the segment that set it
+                    }
+                }
+            }
+        };
+        // which of the row's 64-lane slices go on (a short row's all do)
+        bool sl[LPT], live = false;
+        auto go_on = [&](uint32_t w) {
+            live = false;
+#pragma unroll
+            for (int i = 0; i < LPT; i++) {
+                const unsigned long long m = __ballot(min(acc[i], cur[i]) > sat_add(low[i], w));
+                sl[i] = on && (W == 64 ? m != 0 : (uint32_t)(m >> (lane & 32)) != 0);
+                live |= sl[i];
+            }
+        };
+        if (seg) {
+            go_on(un.w & 0xFFu);
+        } else {
+            live = on;
+#pragma unroll
+            for (int i = 0; i < LPT; i++) sl[i] = true;
+        }
+        uint2 q[EB];  // the next entries, loaded a round ahead
+#pragma unroll
+        for (int j = 0; j < EB; j++) q[j] = a.in_adj[min(p + (uint32_t)j, end - 1)];
+        while (W == 64 ? live : __any(live)) {
+            if (live) {
+                uint32_t tw[EB], s[EB][LPT];
+#pragma unroll
+                for (int i = 0; i < LPT; i++)
+                    if (LPT == 1 || sl[i])
+#pragma unroll
+                        for (int j = 0; j < EB; j++) s[j][i] = S[(size_t)q[j].x * width + cl[i]];
+                p += EB;
+#pragma unroll
+                for (int j = 0; j < EB; j++) {
+                    tw[j] = q[j].y;
+                    q[j] = a.in_adj[min(p + (uint32_t)j, end - 1)];
+                }
+#pragma unroll
+                for (int j = 0; j < EB; j++) {
+                    const uint32_t r = seg ? row : un.z + (tw[j] >> 8);
+                    if (r != row) {  // (an entry past the end repeats the last one: the same row, the same minimum)
+                        if (row != 0xFFFFFFFFu) close();
+                        row = r;
+#pragma unroll
+                        for (int i = 0; i < LPT; i++) {
+                            acc[i] = INF;
+                            cur[i] = a.D[(size_t)row * a.B + a.l0 + cl[i]];
+                        }
+                    }
+#pragma unroll
+                    for (int i = 0; i < LPT; i++)
+                        if (LPT == 1 || sl[i]) acc[i] = min(acc[i], sat_add(s[j][i], tw[j] & 0xFFu));
+                }
+                if (p >= end) live = false;
+                else if (seg) go_on(tw[EB - 1] & 0xFFu);
+            }
+        }
+        if (row != 0xFFFFFFFFu) close();
+    }
+    // one add per workgroup to the shared counter; lane_cnt only has to tell
+    // the lanes that changed from the others
+    __shared__ uint32_t s_sum, s_lane[256];
+    if (threadIdx.x == 0) s_sum = 0;
+    s_lane[threadIdx.x] = 0;
+    __syncthreads();
+    uint32_t sum = 0;
+#pragma unroll
+    for (int i = 0; i < LPT; i++) {
+        sum += cnt[i];
+        if (has[i] && cnt[i]) s_lane[cl[i]] = 1;
+    }
+    if (sum) atomicAdd(&s_sum, sum);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_sum) atomicAdd(&a.ctl->changed[k & 3], (unsigned long long)s_sum);
+    if (a.lane_cnt && threadIdx.x < width && s_lane[threadIdx.x])
+        a.lane_cnt[(size_t)it * a.B + a.l0 + threadIdx.x] = 1;
 }
 
 __global__ __launch_bounds__(256) void k_bs_fill(uint32_t *D, size_t n, uint32_t x) {
@@ -266,11 +466,13 @@ __global__ __launch_bounds__(256) void k_bs_sources(uint32_t *D, uint32_t *M0, c
 }
 
 // Serving: re-initialise lane b (column of D over all V, its masks) and seed it.
-__global__ __launch_bounds__(256) void k_bs_lane_reset(uint32_t *D, uint32_t *Mc, uint32_t *Mn, int64_t V, uint32_t B,
-                                                       uint32_t G, uint32_t lane, int32_t src) {
+__global__ __launch_bounds__(256) void k_bs_lane_reset(uint32_t *D, uint32_t *S, const int32_t *slot, uint32_t *Mc,
+                                                       uint32_t *Mn, int64_t V, uint32_t B, uint32_t G, uint32_t lane,
+                                                       int32_t src) {
     const uint32_t bit = 1u << (lane & 31), g = lane / 32;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < V; v += (int64_t)gridDim.x * blockDim.x) {
         D[(size_t)v * B + lane] = (v == src) ? 0u : INF;
+        S[(size_t)slot[v] * G * 32 + lane] = INF;  // (the source's is written when it is compacted)
         uint32_t w = Mc[(size_t)v * G + g];
         uint32_t want = (v == src) ? (w | bit) : (w & ~bit);
         if (want != w) Mc[(size_t)v * G + g] = want;
@@ -578,26 +780,12 @@ __global__ __launch_bounds__(256) void k_lane_extract(const uint32_t *tile, int6
 
 const BsVariant *bs_variants(int *n) {
     static const BsVariant v[] = {
-        {256, 4, (const void *)k_bsssp<256, 4>},  {256, 8, (const void *)k_bsssp<256, 8>},
-        {512, 4, (const void *)k_bsssp<512, 4>},  {512, 8, (const void *)k_bsssp<512, 8>},
-        {1024, 2, (const void *)k_bsssp<1024, 2>}, {1024, 4, (const void *)k_bsssp<1024, 4>},
+        {256, 4, (const void *)k_bs_relax<256, 4>},  {256, 8, (const void *)k_bs_relax<256, 8>},
+        {512, 4, (const void *)k_bs_relax<512, 4>},  {512, 8, (const void *)k_bs_relax<512, 8>},
+        {1024, 2, (const void *)k_bs_relax<1024, 2>}, {1024, 4, (const void *)k_bs_relax<1024, 4>},
     };
     *n = (int)(sizeof v / sizeof v[0]);
     return v;
-}
-
-
-// Workgroups of a cooperative (grid-barrier) launch.  By default at most
-// max_per_cu per CU and at most half of the occupancy bound; a kernel whose
-// phases run for milliseconds (batched PPR) passes max_per_cu = 0 to use
-// the whole bound (the cooperative launch itself refuses a grid that cannot
-// be resident at once).
-int coop_grid(const void *kernel, int block, int num_cus, int want, int max_per_cu) {
-    const int occ = occupancy_per_cu(kernel, block);
-    int per_cu = max_per_cu > 0 ? std::max(1, std::min(max_per_cu, occ / 2)) : std::max(1, occ);
-    int cap = per_cu * num_cus;
-    if (want > 0) return std::min(want, cap);
-    return cap;
 }
 
 void bs_layout(const DevGraph &d, uint32_t B, Carver &c, BsWork *w) {
@@ -658,20 +846,34 @@ BpArgs bp_args_for(const DevGraph &d, const BpWork &w, float *x, uint32_t B, flo
     return a;
 }
 
-// Wall-clock ticks a grid barrier may wait: BARRIER_LIMIT_S seconds at the
-// device's constant wall-clock rate (a superstep phase of the batched
-// kernel takes milliseconds; only a grid that is not co-resident waits that
-// long).
-unsigned long long barrier_limit_ticks(int device) {
-    int khz = 0;
-    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) != hipSuccess || khz <= 0)
-        khz = 100000;  // 100 MHz, the gfx9 constant clock
-    return (unsigned long long)(BARRIER_LIMIT_S * 1e3 * (double)khz);
-}
+// A superstep pulls when its units are at least 1 / BS_PULL_PART of all
+// (edge, group) pairs: the two benchmarked batches took 720 us and 14.8 ms
+// with 1/6, 714 us and 15.4 ms with 1/3, 778 us and 15.2 ms with 1/12.
+constexpr int64_t BS_PULL_PART = 6;
 
-hipError_t launch_coop(const void *kernel, int grid, int block, void *args, hipStream_t s) {
-    void *params[] = {args};
-    return hipLaunchCooperativeKernel(kernel, dim3(grid), dim3(block), params, 0, s);
+BsArgs bs_args_for(const DevGraph &d, const BsWork &w, uint32_t *D, uint32_t B, uint32_t l0, uint32_t G) {
+    BsArgs a{};
+    a.rp = d.out_rp;
+    a.adj = d.out_adj;
+    a.in_adj = d.in_adj;
+    a.segs = d.pull_segs;
+    a.packs = d.packs;
+    a.slot = d.slot;
+    a.nsegs = d.pull_nsegs;
+    a.npacks = d.n_packs;
+    a.pull_units = d.in_adj ? (uint32_t)std::min<int64_t>(0xFFFFFFFE, d.E * (int64_t)G / BS_PULL_PART + 1) : 0xFFFFFFFFu;
+    a.V = d.V;
+    a.B = B;
+    a.l0 = l0;
+    a.G = G;
+    a.D = D;
+    a.M[0] = w.M[0];
+    a.M[1] = w.M[1];
+    a.list = w.list;
+    a.S = w.S;
+    a.tile_start = w.tile_start;
+    a.ctl = w.ctl;
+    return a;
 }
 
 }  // namespace gx
@@ -726,42 +928,26 @@ gx_status run_bsssp(gx_graph *g, const int32_t *dev_src, uint32_t B, BsWork &w, 
     const size_t n = (size_t)d.V * B;
     hipLaunchKernelGGL(k_bs_fill, dim3(std::min<size_t>(4096, (n + 255) / 256 + 1)), dim3(256), 0, s, D, n, INF);
     int64_t steps_max = 0;
-    const int grid = coop_grid(var->fn, var->block, g->num_cus, (int)tn.grid, 2);
     for (uint32_t l0 = 0; l0 < B; l0 += tn.width) {
         const uint32_t G = tn.width / 32;
         GX_CHECK_HIP(hipMemsetAsync(w.M[0], 0, (size_t)d.V * G * 4, s), g);
         GX_CHECK_HIP(hipMemsetAsync(w.M[1], 0, (size_t)d.V * G * 4, s), g);
         GX_CHECK_HIP(hipMemsetAsync(w.ctl, 0, sizeof(BsCtl), s), g);
+        const size_t ns = (size_t)d.V * tn.width;
+        hipLaunchKernelGGL(k_bs_fill, dim3(std::min<size_t>(4096, (ns + 255) / 256 + 1)), dim3(256), 0, s,
+                           reinterpret_cast<uint32_t *>(w.S), ns, INF);
         hipLaunchKernelGGL(k_bs_sources, dim3((tn.width + 255) / 256), dim3(256), 0, s, D, w.M[0], dev_src, B, l0,
                            tn.width, G);
-        BsArgs a{};
-        a.rp = d.out_rp;
-        a.adj = d.out_adj;
-        a.V = d.V;
-        a.B = B;
-        a.l0 = l0;
-        a.G = G;
-        a.D = D;
-        a.M[0] = w.M[0];
-        a.M[1] = w.M[1];
-        a.list = w.list;
-        a.S = w.S;
-        a.tile_start = w.tile_start;
-        a.ctl = w.ctl;
-        a.max_steps = (uint32_t)std::min<int64_t>(d.V + 2, 0x7FFFFFFF);
-        a.k0 = 0;
-        a.lane_cnt = nullptr;
-        a.stop_when_idle = 1;
-        a.bar_ticks = barrier_limit_ticks(g->device);
-        GX_CHECK_HIP(launch_coop(var->fn, grid, var->block, &a, s), g);
-        BsCtl ctl;
-        GX_CHECK_HIP(hipMemcpyAsync(&ctl, w.ctl, sizeof ctl, hipMemcpyDeviceToHost, s), g);
-        GX_CHECK_HIP(hipStreamSynchronize(s), g);
-        if (ctl.bar.error) {
-            set_error("grid barrier waited over %.0f s in batched SSSP (pass at lane %u, grid %d x %u)",
-                      BARRIER_LIMIT_S, l0, grid, var->block);
-            g->dev_error = true;
-            return GX_EDEVICE;
+        const BsArgs a = bs_args_for(d, w, D, B, l0, G);
+        // supersteps in groups, one readback each (one past the end costs less
+        // than the wait for a readback)
+        BsCtl ctl{};
+        for (uint32_t k = 0, n = 12; ctl.steps == 0; n = 6) {
+            for (const uint32_t to = k + n; k < to; k++)
+                GX_CHECK_HIP(bs_launch_superstep(a, k, 0, *var, (int)tn.grid, g->num_cus, s), g);
+            GX_CHECK_HIP(hipMemcpyAsync(&ctl, w.ctl, sizeof ctl, hipMemcpyDeviceToHost, s), g);
+            GX_CHECK_HIP(hipStreamSynchronize(s), g);
+            if (ctl.steps == 0 && ctl.changed[(k - 1) & 3] == 0) ctl.steps = k;
         }
         steps_max = std::max<int64_t>(steps_max, ctl.steps);
     }
@@ -790,9 +976,33 @@ gx_status run_bppr(gx_graph *g, const int32_t *dev_seed, uint32_t B, BpWork &w, 
 
 // ---- launchers of the ordinary-launch phases (serving)
 
-hipError_t bs_launch_superstep(const BsArgs &a, uint32_t k, uint32_t it, int grid, hipStream_t s) {
-    hipLaunchKernelGGL((k_bs_compact<256, 8>), dim3(grid), dim3(256), 0, s, a, k);
-    hipLaunchKernelGGL((k_bs_relax<256, 8>), dim3(grid), dim3(256), 0, s, a, k, it);
+template <int W, int LPT>
+static void bs_launch_pull(const BsArgs &a, uint32_t k, uint32_t it, int cus, hipStream_t s) {
+    const int64_t waves = (a.nsegs + a.npacks + 64 / W - 1) / (64 / W);
+    const int64_t most = (int64_t)cus * occupancy_per_cu((const void *)k_bs_pull<W, LPT>, 256);
+    hipLaunchKernelGGL((k_bs_pull<W, LPT>), dim3((unsigned)std::min(most, (waves + 3) / 4)), dim3(256), 0, s, a, k, it);
+}
+
+hipError_t bs_launch_superstep(const BsArgs &a, uint32_t k, uint32_t it, const BsVariant &v, int grid, int cus,
+                               hipStream_t s) {
+    const int64_t words = a.V * (int64_t)a.G;
+    const bool wide = words >= BS_WIDE_FROM;
+    const int64_t chunk = BS_CBLOCK * (wide ? 4 : 1);
+    hipLaunchKernelGGL(wide ? k_bs_compact<4> : k_bs_compact<1>,
+                       dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(8 * (int64_t)cus, (words + chunk - 1) / chunk))),
+                       dim3(BS_CBLOCK), 0, s, a, k, v.block * v.vt);
+    const int g = grid > 0 ? grid : cus * occupancy_per_cu(v.fn, (int)v.block);
+    BsArgs arg = a;
+    void *params[] = {&arg, &k, &it};
+    const hipError_t e = hipLaunchKernel(v.fn, dim3((unsigned)g), dim3(v.block), params, 0, s);
+    if (e != hipSuccess) return e;
+    if (a.in_adj && a.nsegs + a.npacks > 0) {
+        if (a.G == 1) bs_launch_pull<32, 1>(a, k, it, cus, s);
+        else if (a.G == 2) bs_launch_pull<64, 1>(a, k, it, cus, s);
+        else if (a.G <= 4) bs_launch_pull<64, 2>(a, k, it, cus, s);
+        else if (a.G <= 6) bs_launch_pull<64, 3>(a, k, it, cus, s);
+        else bs_launch_pull<64, 4>(a, k, it, cus, s);
+    }
     return hipGetLastError();
 }
 
@@ -828,10 +1038,10 @@ hipError_t bp_launch_superstep(const BpArgs &a, uint32_t k, int grid, hipStream_
     return hipGetLastError();
 }
 
-hipError_t bs_lane_reset(uint32_t *D, uint32_t *Mc, uint32_t *Mn, int64_t V, uint32_t B, uint32_t G, uint32_t lane,
-                         int32_t src, hipStream_t s) {
-    unsigned nb = (unsigned)std::min<int64_t>(2048, (V + 255) / 256 + 1);
-    hipLaunchKernelGGL(k_bs_lane_reset, dim3(nb), dim3(256), 0, s, D, Mc, Mn, V, B, G, lane, src);
+hipError_t bs_lane_reset(const BsArgs &a, uint32_t k, uint32_t lane, int32_t src, hipStream_t s) {
+    unsigned nb = (unsigned)std::min<int64_t>(2048, (a.V + 255) / 256 + 1);
+    hipLaunchKernelGGL(k_bs_lane_reset, dim3(nb), dim3(256), 0, s, a.D, reinterpret_cast<uint32_t *>(a.S), a.slot,
+                       a.M[k & 1], a.M[(k + 1) & 1], a.V, a.B, a.G, lane, src);
     return hipGetLastError();
 }
 

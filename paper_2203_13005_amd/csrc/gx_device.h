@@ -1,6 +1,5 @@
 // Device helpers shared by the gx kernels (block scans and reductions, the
-// saturating add of the min-plus relaxation, a bounded grid barrier for
-// cooperative persistent kernels).
+// saturating add of the min-plus relaxation).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -94,46 +93,5 @@ __device__ __forceinline__ void block_max_scan(int32_t *s, int n, int32_t *lds) 
 // The XCD (accelerator complex die) the calling wave runs on: bits 3:0 of
 // the XCC_ID hardware register.
 __device__ __forceinline__ uint32_t xcc_id() { return __builtin_amdgcn_s_getreg((3 << 11) | 20) & 15u; }
-
-// Grid-wide barrier for a cooperative launch (all workgroups co-resident).
-// Sense is a generation counter.  The wait is bounded in time: a workgroup
-// that has waited `limit_ticks` of the constant-rate wall clock
-// (wall_clock64) sets *error and leaves, and so does every workgroup that
-// finds *error set, so a grid can never spin forever; the host reports the
-// error.  Returns true when every workgroup arrived.
-struct GridBar {
-    unsigned int count;
-    unsigned int gen;
-    unsigned int error;
-    unsigned int pad;
-};
-
-__device__ __forceinline__ bool grid_sync(GridBar *b, unsigned int nblocks, unsigned int *s_flag,
-                                          unsigned long long limit_ticks) {
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned int g = __hip_atomic_load(&b->gen, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-        __threadfence();
-        unsigned int arrived = atomicAdd(&b->count, 1u);
-        if (arrived == nblocks - 1) {
-            __hip_atomic_store(&b->count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_fetch_add(&b->gen, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            const unsigned long long t0 = (unsigned long long)wall_clock64();
-            while (__hip_atomic_load(&b->gen, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) == g) {
-                __builtin_amdgcn_s_sleep(2);
-                if (__hip_atomic_load(&b->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) break;
-                if ((unsigned long long)wall_clock64() - t0 > limit_ticks) {
-                    atomicOr(&b->error, 1u);
-                    break;
-                }
-            }
-        }
-        __threadfence();
-        *s_flag = __hip_atomic_load(&b->error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    return *s_flag == 0u;
-}
 
 }  // namespace gx

@@ -173,7 +173,7 @@ struct HostImages {
     std::vector<int32_t> sym_rp;
     EdgeVec<int32_t> sym_col;
     std::vector<int32_t> in_blk;
-    std::vector<uint4> pull_segs, sym_segs;
+    std::vector<uint4> pull_segs, sym_segs, packs;
     std::vector<uint32_t> rem_out, rem_any, master, master_rep;
 };
 
@@ -424,13 +424,22 @@ static void build_in_adj(HostImages &h) {
     h.in_adj.resize(E);
     h.in_blk.assign((size_t)(V + 63) / 64 + 1, 0);
     EdgeVec<int32_t> off(V), seg(V);  // first entry (and segment) of every row
-    int32_t at = 0;
+    int32_t at = 0, from = 0;
+    auto flush = [&](int64_t v) {  // the entries up to `at` end a pack of row v's block
+        if (at > from) h.packs.push_back(make_uint4((uint32_t)from, (uint32_t)at, (uint32_t)(v & ~int64_t(63)), 0u));
+        from = at;
+    };
     for (int64_t v = 0; v < V; v++) {
-        if ((v & 63) == 0) h.in_blk[v >> 6] = at;
+        if ((v & 63) == 0) {
+            if (v > 0) flush(v - 1);
+            h.in_blk[v >> 6] = at;
+        }
         off[v] = at;
         const int32_t n = rp[v + 1] - rp[v];
         if (n <= PULL_SMALL) at += n;
+        if (at - from >= PULL_PACK) flush(v);
     }
+    if (V > 0) flush(V - 1);
     h.in_blk.back() = at;
     h.pull_segs.clear();
     for (int64_t v = 0; v < V; v++) {
@@ -453,7 +462,7 @@ static void build_in_adj(HostImages &h) {
                 if (n > PULL_SMALL) {
                     row_by_weight(&h.in_col[e0], h.slot.data(), &h.in_w[e0], n, tag, &h.in_adj[off[v]]);
                     for (int32_t e = 0, i = seg[v]; e < n; e += PULL_SEG, i++)
-                        h.pull_segs[i].w = h.in_adj[off[v] + e].y & 0xFFu;
+                        h.pull_segs[i].w = (h.in_adj[off[v] + e].y & 0xFFu) | (n <= PULL_SEG ? 0x100u : 0u);
                     continue;
                 }
                 for (int32_t i = 0; i < n; i++)
@@ -553,6 +562,7 @@ static void layout(const gx_graph_desc *desc, int64_t E_sym, Carver &c, DevGraph
         d->in_adj = c.take<uint2>(E);
         d->in_blk = c.take<int32_t>((V + 63) / 64 + 1);
         d->pull_segs = c.take<uint4>(pull_seg_cap(E));
+        d->packs = c.take<uint4>(pull_pack_cap(V, E));
     }
     if (desc->needs & GX_NEED_SYM) {
         d->sym_rp = c.take<int32_t>(V + 1);
@@ -720,6 +730,7 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
     g->d.n_cross = (int32_t)h.cross.size();
     g->d.n_cross_long = h.cross_long;
     g->d.n_dang = (int64_t)h.dang.size();
+    g->d.n_packs = (int64_t)h.packs.size();
     g->d.sym_nsegs = (int64_t)h.sym_segs.size();
     g->needs = desc->needs;
     g->arena = dev_arena;
@@ -771,6 +782,7 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
         if (e == hipSuccess) e = up.put_array((void *)d.in_adj, h.in_adj.data(), h.in_adj.size() * sizeof(uint2));
         if (e == hipSuccess)
             e = up.put_array((void *)d.pull_segs, h.pull_segs.data(), h.pull_segs.size() * sizeof(uint4));
+        if (e == hipSuccess) e = up.put_array((void *)d.packs, h.packs.data(), h.packs.size() * sizeof(uint4));
     }
     if (e == hipSuccess && d.sym_rp) {
         e = up.put_array((void *)d.sym_rp, h.sym_rp.data(), (V + 1) * 4);

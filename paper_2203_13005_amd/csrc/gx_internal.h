@@ -76,6 +76,7 @@ constexpr int PR_TILE_MAX = PR_BLOCK * 8;
 constexpr int PULL_SLICES = 8;
 constexpr int PULL_SMALL = 32;
 constexpr int PULL_SEG = 256;
+constexpr int PULL_PACK = 32;  // batched pull: a pack of short rows ends when it has this many entries
 constexpr int PULL_BLOCK = 256;     // rows a workgroup takes at a time (one per thread)
 constexpr int PULL_SEG_BLOCK = 64;  // segments (16 per wave)
 constexpr int PULL_RUN_LOG = 2;     // blocks per run (1 below PULL_RUN_FROM blocks, to reach every XCD)
@@ -87,6 +88,7 @@ constexpr int PULL_BIT_WORDS = PULL_BITS / 32;
 // Capacity of the segment table of E entries (known before the rows are: a
 // row in it has more than PULL_SMALL entries).
 inline int64_t pull_seg_cap(int64_t E) { return E / PULL_SMALL + 1; }
+inline int64_t pull_pack_cap(int64_t V, int64_t E) { return std::min(E, E / PULL_PACK + (V + 63) / 64) + 1; }
 
 // Row ends of the in-CSR (batched PPR): rows without in-edges are left out,
 // a bit per in-edge marks the last one of its row.  The in-edges are cut into
@@ -141,11 +143,16 @@ struct DevGraph {
     // 64 rows owns in_blk[b] .. in_blk[b + 1]), then the longer rows, each by
     // ascending weight; null when a weight exceeds 255 (the engine
     // then only pushes).  pull_segs: {row, first entry, end entry, first
-    // weight} of the long rows.
+    // weight, bit 8: the row's only one} of the
+    // long rows.
     const uint2 *in_adj = nullptr;
     const int32_t *in_blk = nullptr;
     const uint4 *pull_segs = nullptr;
     int64_t pull_nsegs = 0;
+    // batched pull: runs of whole short rows of one block of 64, {first entry,
+    // end entry, first row of the block, 0}
+    const uint4 *packs = nullptr;
+    int64_t n_packs = 0;
     // symmetric adjacency (CC push and pull, neighbours ascending) and the
     // segments of its long rows
     const int32_t *sym_rp = nullptr;

@@ -588,7 +588,7 @@ __device__ __forceinline__ void pull_body(const PullArgs &pa, int64_t V, const u
                 sg = pa.segs[q];
                 cur = pa.bound[sg.x];
             }
-            const int n = queue_items(it, sat_add(low, sg.w) < cur, sg.x, sg.y, sg.z, cur);
+            const int n = queue_items(it, sat_add(low, sg.w & 0xFFu) < cur, sg.x, sg.y, sg.z, cur);
             scan_items<WEIGHTED, 16, 4>(it, lds.bits, n, pa, low, snap, tgt, front_next, true);
             continue;
         }

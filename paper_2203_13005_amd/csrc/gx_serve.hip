@@ -329,6 +329,7 @@ struct gx_server {
             if (algo == GX_SSSP) {
                 const size_t VG = (size_t)d.V * (B / 32);
                 ok = hipMemsetAsync(p->D, 0xFF, (size_t)d.V * B * 4, s) == hipSuccess &&
+                     hipMemsetAsync(p->bw.S, 0xFF, VG * 32 * 4, s) == hipSuccess &&
                      hipMemsetAsync(p->bw.M[0], 0, VG * 4, s) == hipSuccess &&
                      hipMemsetAsync(p->bw.M[1], 0, VG * 4, s) == hipSuccess &&
                      hipMemsetAsync(p->bw.ctl, 0, sizeof(BsCtl), s) == hipSuccess;
@@ -352,24 +353,8 @@ struct gx_server {
     }
 
     BsArgs bs_args(Pool &p) {
-        const DevGraph &d = p.g->d;
-        BsArgs a{};
-        a.rp = d.out_rp;
-        a.adj = d.out_adj;
-        a.V = d.V;
-        a.B = p.B;
-        a.l0 = 0;
-        a.G = p.B / 32;
-        a.D = p.D;
-        a.M[0] = p.bw.M[0];
-        a.M[1] = p.bw.M[1];
-        a.list = p.bw.list;
-        a.S = p.bw.S;
-        a.tile_start = p.bw.tile_start;
-        a.ctl = p.bw.ctl;
-        a.max_steps = 1;
+        BsArgs a = bs_args_for(p.g->d, p.bw, p.D, p.B, 0, p.B / 32);
         a.lane_cnt = p.lane_cnt;
-        a.stop_when_idle = 0;
         return a;
     }
 
@@ -383,8 +368,7 @@ struct gx_server {
         const DevGraph &d = p.g->d;
         hipError_t e;
         if (p.algo == GX_SSSP) {
-            e = bs_lane_reset(p.D, p.bw.M[p.k & 1], p.bw.M[(p.k + 1) & 1], d.V, p.B, p.B / 32, lane, q.source,
-                              p.stream);
+            e = bs_lane_reset(bs_args(p), p.k, lane, q.source, p.stream);
         } else {
             // the lane runs supersteps k .. k + iterations - 1; its seed and end
             // reach the device with the next epoch's lane table
@@ -490,8 +474,9 @@ struct gx_server {
             p.epoch_len = epoch_max(GX_SSSP);
             if (hipMemsetAsync(p.lane_cnt, 0, (size_t)p.epoch_len * p.B * 4, p.stream) != hipSuccess) return false;
             BsArgs a = bs_args(p);
+            int nv = 0;
             for (uint32_t it = 0; it < p.epoch_len; it++)
-                if (bs_launch_superstep(a, p.k + it, it, grid, p.stream) != hipSuccess) return false;
+                if (bs_launch_superstep(a, p.k + it, it, bs_variants(&nv)[1], 0, p.g->num_cus, p.stream) != hipSuccess) return false;
             if (hipMemcpyAsync(p.host_cnt, p.lane_cnt, (size_t)p.epoch_len * p.B * 4, hipMemcpyDeviceToHost,
                                p.stream) != hipSuccess)
                 return false;
