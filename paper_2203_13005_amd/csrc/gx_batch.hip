@@ -801,7 +801,7 @@ void bs_layout(const DevGraph &d, uint32_t B, Carver &c, BsWork *w) {
 }
 
 void bp_layout(const DevGraph &d, uint32_t B, Carver &c, BpWork *w) {
-    const int64_t nt = std::max<int64_t>(1, rows_tiles(d.E));
+    const int64_t nt = std::max<int64_t>(1, d.bp_rows.n);
     w->c[0] = c.take<float>((size_t)d.V * B);
     w->c[1] = c.take<float>((size_t)d.V * B);
     w->head = c.take<double>(nt * B);
@@ -817,21 +817,21 @@ BpArgs bp_args_for(const DevGraph &d, const BpWork &w, float *x, uint32_t B, flo
     a.in_col = d.in_col;
     a.nz = d.nz;
     a.row_last = d.row_last;
-    a.tile_nz = d.tile_nz;
-    a.cross = d.cross;
+    a.tile_nz = d.bp_rows.tile_nz;
+    a.cross = d.bp_rows.cross;
     a.dang = d.dang;
     a.in_rp = d.in_rp;
     a.outdeg = d.outdeg;
     a.n_nz = d.n_nz;
-    a.tile = (int32_t)rows_tile(d.E);
-    a.ntiles = rows_tiles(d.E);
+    a.tile = (int32_t)d.bp_rows.T;
+    a.ntiles = d.bp_rows.n;
     a.E = d.E;
     a.n_dang = d.n_dang;
     // (few tiles of dangling vertices: their partials are added by one workgroup)
     a.dtile = (int32_t)std::max<int64_t>(a.tile, ((d.n_dang + ROWS_DANGLING - 1) / ROWS_DANGLING + 63) / 64 * 64);
     a.ndtiles = (int32_t)((d.n_dang + a.dtile - 1) / a.dtile);
-    a.n_cross = d.n_cross;
-    a.n_cross_long = d.n_cross_long;
+    a.n_cross = d.bp_rows.n_cross;
+    a.n_cross_long = d.bp_rows.n_long;
     a.B = B;
     a.Bw = B;
     a.d = damping;

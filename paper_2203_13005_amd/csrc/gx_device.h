@@ -47,8 +47,11 @@ __device__ __forceinline__ T block_sum(T v, T *lds) {
     if (lane == 0) lds[wid] = v;
     __syncthreads();
     T r = 0;
-    if (threadIdx.x == 0)
-        for (int i = 0; i < nw; i++) r += lds[i];
+    if (wid == 0) {
+        r = lane < nw ? lds[lane] : T(0);
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) r += __shfl_down(r, o, 16);
+    }
     __syncthreads();
     return r;  // valid in thread 0
 }

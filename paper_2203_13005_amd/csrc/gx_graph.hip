@@ -161,12 +161,15 @@ template <class T>
 using EdgeVec = std::vector<T, NoInit<T>>;
 
 struct HostImages {
-    std::vector<int32_t> in_rp, outdeg, tile_row, slot;
-    std::vector<int2> nz;
+    std::vector<int32_t> in_rp, outdeg, slot, nz_slot;
+    std::vector<int2> nz, ez;
     std::vector<uint64_t> row_last;
-    std::vector<int32_t> tile_nz, dang;
-    std::vector<int4> cross;
-    int32_t cross_long = 0;
+    std::vector<int32_t> dang;
+    struct Tiles {
+        std::vector<int32_t> tile_nz;
+        std::vector<int4> cross;
+        int32_t n_long = 0, n_mid = 0;
+    } pr_rows, bp_rows;
     EdgeVec<int32_t> in_col, pr_src;
     EdgeVec<uint32_t> in_w;
     EdgeVec<uint2> in_adj;
@@ -343,55 +346,54 @@ static void build_slots(const gx_graph_desc *d, HostImages &h) {
     }
 }
 
-// The rows with in-edges, where they end, the rows that cross tiles and the
-// dangling vertices with in-edges.
+// The rows with in-edges, where they end, and the other rows.
 static void build_rows(const gx_graph_desc *d, HostImages &h) {
-    const int64_t V = d->V, E = d->E, T = rows_tile(E), nt = rows_tiles(E);
-    h.row_last.assign((size_t)(E + 63) / 64 + 1, 0);
-    h.tile_nz.assign((size_t)nt + 1, 0);
-    std::vector<int4> few;
+    const int64_t V = d->V, E = d->E;
+    h.row_last.assign((size_t)(E + PR_TILE_MAX) / 64 + 1, 0);
     h.nz.reserve((size_t)std::min(V, E));
-    for (int64_t v = 0, t = 0; v < V; v++) {
+    h.nz_slot.reserve((size_t)std::min(V, E));
+    for (int64_t v = 0; v < V; v++) {
         const int32_t a = h.in_rp[v], b = h.in_rp[v + 1];
-        if (a == b) continue;
         const int32_t od = d->row_ptr[v + 1] - d->row_ptr[v];
-        const int32_t at = (int32_t)h.nz.size();
-        for (; t * T < b && t < nt; t++) h.tile_nz[t] = at;  // tiles whose first edge is in this row
+        if (a == b) {
+            h.ez.push_back(make_int2((int32_t)v, od));
+            continue;
+        }
         h.nz.push_back(make_int2((int32_t)v, od));
+        h.nz_slot.push_back(h.slot[v]);
         h.row_last[(b - 1) >> 6] |= uint64_t(1) << ((b - 1) & 63);
-        const int32_t t0 = (int32_t)(a / T), t1 = (int32_t)((b - 1) / T);
-        if (t1 - t0 >= ROWS_LONG) h.cross.push_back(make_int4((int32_t)v, od, t0, t1));
-        else if (t1 > t0) few.push_back(make_int4((int32_t)v, od, t0, t1));
         if (od == 0) h.dang.push_back((int32_t)v);
     }
-    h.cross_long = (int32_t)h.cross.size();
-    h.cross.insert(h.cross.end(), few.begin(), few.end());
 }
 
-// Pull tiles: tile t covers edges [t*T, (t+1)*T) of a CSR and owns the rows
-// whose first edge position falls in that range (the last tile also owns the
-// rows starting at E).
-static int64_t ntiles_for(int64_t E, int64_t T) { return std::max<int64_t>(1, (E + T - 1) / T); }
+// The tiles of T in-edges, and the rows that cross them.
+static void build_row_tiles(int64_t E, int64_t T, const HostImages &h, HostImages::Tiles &out) {
+    const int64_t nt = (E + T - 1) / T;
+    out.tile_nz.assign((size_t)nt + 1, 0);
+    std::vector<int4> mid, few;
+    int64_t t = 0;
+    for (size_t i = 0; i < h.nz.size(); i++) {
+        const int2 r = h.nz[i];
+        const int32_t a = h.in_rp[r.x], b = h.in_rp[r.x + 1];
+        for (; t * T < b && t < nt; t++) out.tile_nz[t] = (int32_t)i;  // tiles whose first edge is in this row
+        const int32_t t0 = (int32_t)(a / T), t1 = (int32_t)((b - 1) / T);
+        if (t1 - t0 >= ROWS_LONG) out.cross.push_back(make_int4(r.x, r.y, t0, t1));
+        else if (t1 - t0 >= ROWS_MID) mid.push_back(make_int4(r.x, r.y, t0, t1));
+        else if (t1 > t0) few.push_back(make_int4(r.x, r.y, t0, t1));
+    }
+    out.n_long = (int32_t)out.cross.size();
+    out.n_mid = (int32_t)mid.size();
+    out.cross.insert(out.cross.end(), mid.begin(), mid.end());
+    out.cross.insert(out.cross.end(), few.begin(), few.end());
+}
 
-// PageRank tile size: the caller's choice, else the largest size up to 1024
-// that still gives 2048 tiles (eight per CU), else the smallest.  (2048-edge
-// tiles measured 3% slower on the scale-25 partition and 8% slower on R-MAT
-// scale 20 than 1024, and 0.6% faster on R-MAT scale 22.)
+// PageRank workgroup tile: the caller's choice, else the largest.  Eight
+// in-edges per lane leave the fewest rows that cross tiles and the least work
+// per edge in the pull (20 supersteps of R-MAT, 2048 against 1024, 512, 256:
+// scale 12 225, 241, 228, 276 us; 14 266, 278, 285, 302; 18 574, 592, 684,
+// 972; 22 5.62, 5.86, 7.33, 10.96 ms).
 static int32_t pr_tile_for(const gx_graph_desc *d) {
-    if (d->pr_tile_edges) return (int32_t)d->pr_tile_edges;
-    for (int32_t T = PR_TILE_MAX / 2; T > PR_BLOCK; T /= 2)
-        if (ntiles_for(d->E, T) >= 2048) return T;
-    return PR_BLOCK;
-}
-
-static void build_tiles(const std::vector<int32_t> &rp, std::vector<int32_t> &tile_row, int64_t T) {
-    int64_t V = (int64_t)rp.size() - 1, E = rp.back();
-    int64_t nt = ntiles_for(E, T);
-    tile_row.resize(nt + 1);
-    for (int64_t t = 0; t < nt; t++)
-        tile_row[t] = (int32_t)(std::lower_bound(rp.begin(), rp.end() - 1, (int32_t)(t * T)) - rp.begin());
-    tile_row[0] = 0;
-    tile_row[nt] = (int32_t)V;
+    return d->pr_tile_edges ? (int32_t)d->pr_tile_edges : PR_TILE_MAX;
 }
 
 // The segments of the rows with more than PULL_SMALL entries.
@@ -544,18 +546,25 @@ static void layout(const gx_graph_desc *desc, int64_t E_sym, Carver &c, DevGraph
     if (desc->needs & (GX_NEED_IN | GX_NEED_OUT)) {
         d->in_rp = c.take<int32_t>(V + 1);
         d->pr_tile = pr_tile_for(desc);
-        d->pr_ntiles = (int32_t)ntiles_for(E, d->pr_tile);
-        d->pr_tile_row = c.take<int32_t>(d->pr_ntiles + 1);
     }
     if (desc->needs & GX_NEED_IN) {
         d->in_col = c.take<int32_t>(E + 64);  // (read in whole groups of 16)
         d->nz = c.take<int2>(std::min(V, E));
-        d->row_last = c.take<uint64_t>((E + 63) / 64 + 1);
-        d->tile_nz = c.take<int32_t>(rows_tiles(E) + 1);
-        d->cross = c.take<int4>(rows_tiles(E));
+        d->row_last = c.take<uint64_t>((E + PR_TILE_MAX) / 64 + 1);  // (whole tiles)
+        // (byte offsets of the other slots are 32 bits)
+        d->pr_hot = E >= PR_LDS_EDGES && V >= PR_LDS_SLOTS && V < (int64_t(1) << 29);
+        d->pr_rows.T = d->pr_tile / (PR_BLOCK / 64);
+        d->bp_rows.T = bp_rows_tile(E);
+        for (RowTiles *r : {&d->pr_rows, &d->bp_rows}) {
+            r->n = (E + r->T - 1) / r->T;
+            r->tile_nz = c.take<int32_t>(r->n + 1);
+            r->cross = c.take<int4>(r->n);
+        }
+        d->nz_slot = c.take<int32_t>(std::min(V, E));
+        d->ez = c.take<int2>(V);
         d->dang = c.take<int32_t>(std::min(V, E) + 64);
         d->outdeg = c.take<int32_t>(V);
-        d->pr_src = c.take<int32_t>(E);
+        d->pr_src = c.take<int32_t>(E + PR_TILE_MAX);  // (read in whole tiles)
     }
     if (desc->needs & (GX_NEED_IN | GX_NEED_OUT)) d->slot = c.take<int32_t>(V);
     if ((desc->needs & GX_NEED_OUT) && (desc->E == 0 || byte_weights(desc))) {
@@ -698,14 +707,17 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
     int32_t W = (int32_t)((desc->V + 31) / 32);
     try {
         build_in_csr(desc, h);
-        build_tiles(h.in_rp, h.tile_row, pr_tile_for(desc));
         if (desc->needs & (GX_NEED_IN | GX_NEED_OUT)) build_slots(desc, h);
         if (desc->needs & GX_NEED_IN) {
             build_rows(desc, h);
-            h.pr_src.resize(desc->E);
+            const int64_t T = pr_tile_for(desc) / (PR_BLOCK / 64);
+            build_row_tiles(desc->E, T, h, h.pr_rows);
+            build_row_tiles(desc->E, bp_rows_tile(desc->E), h, h.bp_rows);
+            h.pr_src.resize((desc->E + T - 1) / T * T);
             parallel_for(desc->E, [&](int64_t lo, int64_t hi) {
                 for (int64_t e = lo; e < hi; e++) h.pr_src[e] = h.slot[h.in_col[e]];
             });
+            std::fill(h.pr_src.begin() + desc->E, h.pr_src.end(), (int32_t)desc->V);  // (no slot)
         }
         if ((desc->needs & GX_NEED_OUT) && desc->E > 0 && byte_weights(desc)) build_in_adj(h);
         if (desc->needs & GX_NEED_SYM) {
@@ -727,8 +739,12 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
     layout(desc, (int64_t)h.sym_col.size(), c, &g->d);
     g->d.pull_nsegs = (int64_t)h.pull_segs.size();
     g->d.n_nz = (int64_t)h.nz.size();
-    g->d.n_cross = (int32_t)h.cross.size();
-    g->d.n_cross_long = h.cross_long;
+    g->d.n_ez = (int64_t)h.ez.size();
+    for (auto [r, t] : {std::pair(&g->d.pr_rows, &h.pr_rows), std::pair(&g->d.bp_rows, &h.bp_rows)}) {
+        r->n_cross = (int32_t)t->cross.size();
+        r->n_long = t->n_long;
+        r->n_mid = t->n_mid;
+    }
     g->d.n_dang = (int64_t)h.dang.size();
     g->d.n_packs = (int64_t)h.packs.size();
     g->d.sym_nsegs = (int64_t)h.sym_segs.size();
@@ -764,17 +780,20 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
     }
     if (e == hipSuccess && d.in_rp) {
         e = up.put_array((void *)d.in_rp, h.in_rp.data(), (V + 1) * 4);
-        if (e == hipSuccess) e = up.put_array((void *)d.pr_tile_row, h.tile_row.data(), h.tile_row.size() * 4);
     }
     if (e == hipSuccess && d.in_col) {
         e = up.put_array((void *)d.in_col, h.in_col.data(), E * 4);
         if (e == hipSuccess) e = up.put_array((void *)d.outdeg, g->host_outdeg.data(), V * 4);
         if (e == hipSuccess) e = up.put_array((void *)d.nz, h.nz.data(), h.nz.size() * sizeof(int2));
+        if (e == hipSuccess) e = up.put_array((void *)d.nz_slot, h.nz_slot.data(), h.nz_slot.size() * 4);
+        if (e == hipSuccess) e = up.put_array((void *)d.ez, h.ez.data(), h.ez.size() * sizeof(int2));
         if (e == hipSuccess) e = up.put_array((void *)d.row_last, h.row_last.data(), h.row_last.size() * 8);
-        if (e == hipSuccess) e = up.put_array((void *)d.tile_nz, h.tile_nz.data(), h.tile_nz.size() * 4);
-        if (e == hipSuccess) e = up.put_array((void *)d.cross, h.cross.data(), h.cross.size() * sizeof(int4));
+        for (auto [r, t] : {std::pair(&d.pr_rows, &h.pr_rows), std::pair(&d.bp_rows, &h.bp_rows)}) {
+            if (e == hipSuccess) e = up.put_array((void *)r->tile_nz, t->tile_nz.data(), t->tile_nz.size() * 4);
+            if (e == hipSuccess) e = up.put_array((void *)r->cross, t->cross.data(), t->cross.size() * sizeof(int4));
+        }
         if (e == hipSuccess) e = up.put_array((void *)d.dang, h.dang.data(), h.dang.size() * 4);
-        if (e == hipSuccess) e = up.put_array((void *)d.pr_src, h.pr_src.data(), E * 4);
+        if (e == hipSuccess) e = up.put_array((void *)d.pr_src, h.pr_src.data(), h.pr_src.size() * 4);
     }
     if (e == hipSuccess && d.slot) e = up.put_array((void *)d.slot, h.slot.data(), V * 4);
     if (e == hipSuccess && d.in_adj && !h.in_adj.empty()) {

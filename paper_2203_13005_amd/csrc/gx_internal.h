@@ -68,6 +68,14 @@ constexpr int PR_BLOCK = 256;
 // past (on R-MAT graphs they are the sources of 70 to 93% of the in-edges).
 constexpr int64_t HOT_SLOTS = int64_t(1) << 19;
 constexpr int PR_TILE_MAX = PR_BLOCK * 8;
+// The PageRank pull of a graph with at least PR_LDS_EDGES edges keeps the
+// contributions of the first slots in LDS (120 KiB, one workgroup per CU).
+// 20 supersteps without and with: R-MAT scale 16 (1 M edges) 312 and 363 us,
+// 17 (2 M) 375 and 373, 18 (4 M) 566 and 506, 20 1.74 and 1.29 ms, 22 7.70 and
+// 5.63 ms; uniform, 4 M edges: 2^15 vertices 550 and 423 us, 2^17 644 and 586;
+// 2^22 vertices, 67 M edges (where it holds 1 % of the sources) 18.6 and 18.3 ms.
+constexpr int32_t PR_LDS_SLOTS = 30720;
+constexpr int64_t PR_LDS_EDGES = int64_t(1) << 22;
 // Row pull of SSSP / CC: rows of at most PULL_SMALL entries are taken in
 // blocks, longer ones in segments of at most PULL_SEG entries from a table
 // built at load.  The rows (and the segments) are dealt to PULL_SLICES slices
@@ -90,14 +98,25 @@ constexpr int PULL_BIT_WORDS = PULL_BITS / 32;
 inline int64_t pull_seg_cap(int64_t E) { return E / PULL_SMALL + 1; }
 inline int64_t pull_pack_cap(int64_t V, int64_t E) { return std::min(E, E / PULL_PACK + (V + 63) / 64) + 1; }
 
-// Row ends of the in-CSR (batched PPR): rows without in-edges are left out,
+// Row ends of the in-CSR (PageRank, batched PPR): rows without in-edges are left out,
 // a bit per in-edge marks the last one of its row.  The in-edges are cut into
-// tiles of rows_tile(E) edges; rows that cross tiles are listed.
+// tiles, rows that cross tiles are listed.
 constexpr int ROWS_PIECES = 16;     // a sum of at least ROWS_LONG partials is cut into this many pieces
 constexpr int ROWS_LONG = 64;
+constexpr int ROWS_MID = 4;         // (PageRank: summed by sixteen lanes)
+struct RowTiles {
+    int64_t T = 0, n = 0;              // in-edges per tile, tiles
+    const int32_t *tile_nz = nullptr;  // per tile: position in nz of the row its first edge belongs to
+    const int4 *cross = nullptr;       // rows crossing tiles: {row, out-degree, first tile, last tile},
+    int32_t n_cross = 0;               // those with at least ROWS_LONG further tiles first, then those
+    int32_t n_long = 0, n_mid = 0;     // with at least ROWS_MID
+};
+// Batched PPR, a lane group's tile: a graph of few edges has too few longer
+// ones to occupy the chip (100003 vertices, 1.6 M edges, 5 lanes: 1.7 ms with
+// 64, 2.2 with 128, 2.8 with 256); a large one saves partials (scale 20,
+// 64 lanes: 37.6, 35.8 and 34.0 ms).
+inline int64_t bp_rows_tile(int64_t E) { return E >= (int64_t(1) << 22) ? 256 : 64; }
 constexpr int ROWS_DANGLING = 512;  // tiles of dangling vertices at most
-inline int64_t rows_tile(int64_t E) { return E >= (int64_t(1) << 22) ? 128 : 64; }
-inline int64_t rows_tiles(int64_t E) { return (E + rows_tile(E) - 1) / rows_tile(E); }
 
 // Label propagation: vertices are grouped by the number of distinct
 // neighbours d.  Classes 0..4 take d <= 4, 8, 16, 32, 64 and run as lane
@@ -127,17 +146,16 @@ struct DevGraph {
     const int32_t *pr_src = nullptr;
     const int32_t *slot = nullptr;
     const int2 *nz = nullptr;          // {row, out-degree} of the rows with in-edges, ascending
+    const int32_t *nz_slot = nullptr;  // their slots
     int64_t n_nz = 0;
+    const int2 *ez = nullptr;          // {row, out-degree} of the other rows
+    int64_t n_ez = 0;
     const uint64_t *row_last = nullptr;  // bit e: in-edge e is its row's last
-    const int32_t *tile_nz = nullptr;  // per tile: position in nz of the row its first edge belongs to
-    const int4 *cross = nullptr;       // rows crossing tiles: {row, out-degree, first tile, last tile},
-    int32_t n_cross = 0;               // those with at least ROWS_LONG further tiles
-    int32_t n_cross_long = 0;          // first
+    RowTiles pr_rows, bp_rows;         // of PageRank's tiles and of the batched PPR's
     const int32_t *dang = nullptr;     // vertices with in-edges and without out-edges
     int64_t n_dang = 0;
-    int32_t pr_tile = PR_TILE_MAX;  // in-edges per PageRank tile
-    int32_t pr_ntiles = 0;
-    const int32_t *pr_tile_row = nullptr;  // [pr_ntiles + 1]
+    int32_t pr_tile = PR_TILE_MAX;  // in-edges per PageRank workgroup tile (PR_BLOCK / 64 wave tiles)
+    bool pr_hot = false;            // the PageRank pull keeps the first PR_LDS_SLOTS contributions in LDS
     // in-edges of the SSSP pull, {source slot, (destination mod 64) << 8 | weight}:
     // the entries of the rows of at most PULL_SMALL, in row order (block b of
     // 64 rows owns in_blk[b] .. in_blk[b + 1]), then the longer rows, each by
@@ -281,11 +299,13 @@ struct gx_state {
     float *contrib[2] = {nullptr, nullptr};
     uint32_t *synced = nullptr;
     double *head = nullptr, *tailp = nullptr;
-    int32_t *spill_row = nullptr;
     double *dpart = nullptr;
-    uint32_t *cpart = nullptr;   // per-tile changed counts (PageRank)
+    uint32_t *cpart = nullptr;   // per-wave changed counts (PageRank)
     double *Dval = nullptr;
+    int pr_grid = 1;                  // workgroups of k_pr_pull
+    int pr_parts = 1;                 // its waves (entries of dpart and cpart)
     int pr_fix_grid = 1;              // workgroups of k_pr_fix
+    int pr_fix_block = 256;           // and their threads
     double *fix_d = nullptr;          // their dangling-mass partials
     unsigned long long *fix_c = nullptr;  // and changed counts
     uint32_t *fix_done = nullptr;     // workgroups finished (the last resets it)

@@ -34,14 +34,14 @@
 //               & Management") under the balanced objective of Section
 //               "Workload Balancing".
 // PageRank superstep:
-//   k_pr_pull : equal in-edge tiles; contributions are gathered into LDS and
-//               summed per destination row in a fixed order; rows that
-//               cross a tile boundary leave fixed partials.
-//   k_pr_fix  : completes the crossing rows (each by one thread, in tile
-//               order) and reduces the dangling mass for the next superstep:
-//               per-workgroup partials, then the last workgroup to finish
-//               sums them in workgroup order.  No floating-point atomics:
-//               results are bitwise reproducible.
+//   k_pr_pull : a wave per tile of consecutive in-edges; the contributions
+//               are gathered and summed per destination row in a fixed order;
+//               rows that cross a tile boundary leave fixed partials.
+//   k_pr_fix  : completes the crossing rows (a thread each, in tile order;
+//               a wave for those of many tiles) and reduces the dangling mass
+//               for the next superstep: per-workgroup partials, then the last
+//               workgroup to finish sums them in workgroup order.  No
+//               floating-point atomics: results are bitwise reproducible.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -673,26 +673,16 @@ __global__ __launch_bounds__(1024) void k_reduce_D(const double *__restrict__ pa
 
 struct PrApply {
     double base, d, dD;  // x' = base + d * acc + dD, with dD = d * D / V
-    const int32_t *outdeg;
     const float *x_in;
     float *x_out, *c_out;
-    const int32_t *slot;  // contribution slot of each vertex (hottest sources first)
-    static constexpr bool kRows = true;  // the pull stages outdeg, slot and x_in of its rows in LDS
-    __device__ __forceinline__ void load_row(int32_t r, int32_t &od, int32_t &sl, float &xi) const {
-        od = outdeg[r];
-        sl = slot[r];
-        xi = x_in[r];
-    }
+    static constexpr bool kRows = true;  // reads out-degree, slot and old rank
     __device__ __forceinline__ void row(int32_t r, double acc, int32_t od, int32_t sl, float xi, double &dsum,
                                         int &chg) const {
         float xn = (float)(base + d * acc + dD);
         x_out[r] = xn;
-        c_out[sl] = od > 0 ? xn / (float)od : 0.0f;
-        if (od == 0) dsum += (double)xn;
+        if (od > 0) c_out[sl] = xn / (float)od;  // (a slot without out-edges is not gathered)
+        else dsum += (double)xn;
         chg += __float_as_uint(xn) != __float_as_uint(xi);
-    }
-    __device__ __forceinline__ void operator()(int32_t r, double acc, double &dsum, int &chg) const {
-        row(r, acc, outdeg[r], slot[r], x_in[r], dsum, chg);
     }
 };
 
@@ -702,273 +692,338 @@ struct PrStore {
     double d, dD;  // (unused)
     double *acc;
     static constexpr bool kRows = false;
-    __device__ __forceinline__ void load_row(int32_t, int32_t &, int32_t &, float &) const {}
+    static constexpr const float *x_in = nullptr;
     __device__ __forceinline__ void row(int32_t r, double total, int32_t, int32_t, float, double &, int &) const {
         acc[r] = total;
     }
-    __device__ __forceinline__ void operator()(int32_t r, double total, double &, int &) const { acc[r] = total; }
 };
 
-template <int VT, class AP>
-__global__ __launch_bounds__(PR_BLOCK) void k_pr_pull(const int32_t *__restrict__ in_rp,
-                                                      const int32_t *__restrict__ in_col,
-                                                      const int32_t *__restrict__ tile_row, int64_t E,
-                                                      const float *__restrict__ c_in, AP ap,
-                                                      const double *__restrict__ Dp, double inv_V,
-                                                      double *__restrict__ head, double *__restrict__ tailp,
-                                                      int32_t *__restrict__ spill_row, double *__restrict__ dpart,
-                                                      uint32_t *__restrict__ cpart) {
-    constexpr int TILE = PR_BLOCK * VT;
-    constexpr int RPT = 2;                    // rows per thread whose data is staged in LDS
-    constexpr int ROWS = RPT * PR_BLOCK;
-    __shared__ float s_val[TILE];
-    __shared__ int32_t s_own[TILE];
-    __shared__ double s_last[PR_BLOCK];
-    __shared__ double s_wy[PR_BLOCK / 64];
-    __shared__ int s_wf[PR_BLOCK / 64];
-    __shared__ int32_t s_red[4];
-    __shared__ double s_d[4];
-    __shared__ unsigned long long s_c[4];
-    __shared__ int32_t s_re[ROWS];            // end of row r_lo + i (in_rp[r + 1])
-    __shared__ int32_t s_od[AP::kRows ? ROWS : 1], s_sl[AP::kRows ? ROWS : 1];
-    __shared__ float s_xi[AP::kRows ? ROWS : 1];
-    const int tid = threadIdx.x;
-    const int32_t t = blockIdx.x;
-    const int64_t e0 = (int64_t)t * TILE;
-    const int n = (int)max((int64_t)0, min((int64_t)TILE, E - e0));
-    const int32_t r_lo = tile_row[t], r_hi = tile_row[t + 1];
-    ap.dD = ap.d * (*Dp) * inv_V;
-    if (tid == 0) spill_row[t] = -1;
-    // Every load that depends only on the tile is issued at once: the edges'
-    // sources, the row pointers of the tile's first ROWS rows and what the
-    // apply reads of them; then the gathers of the contributions.
-    int32_t u[VT];
-    float cv[VT];
-    int32_t ra[RPT], rb[RPT], od[RPT], sl[RPT];
-    float xi[RPT];
-#pragma unroll
-    for (int i = 0; i < VT; i++)  // (the in-edges stream by once: kept out of the caches' way)
-        u[i] = n > 0 ? __builtin_nontemporal_load(&in_col[e0 + min(tid + i * PR_BLOCK, n - 1)]) : 0;
-#pragma unroll
-    for (int k = 0; k < RPT; k++) {
-        const int32_t r = r_lo + tid + k * PR_BLOCK;
-        ra[k] = rb[k] = 0;
-        od[k] = sl[k] = 0;
-        xi[k] = 0.f;
-        if (r < r_hi) {
-            ra[k] = in_rp[r];
-            rb[k] = in_rp[r + 1];
-            ap.load_row(r, od[k], sl[k], xi[k]);
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < VT; i++) cv[i] = n > 0 ? c_in[u[i]] : 0.f;
-#pragma unroll
-    for (int i = 0; i < VT; i++) {
-        const int p = tid + i * PR_BLOCK;
-        if (p < n) {
-            s_val[p] = cv[i];
-            s_own[p] = 0;
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < RPT; k++) {
-        const int i = tid + k * PR_BLOCK;
-        if (r_lo + i < r_hi) {
-            s_re[i] = rb[k];
-            if (AP::kRows) {
-                s_od[i] = od[k];
-                s_sl[i] = sl[k];
-                s_xi[i] = xi[k];
-            }
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < RPT; k++) {
-        const int32_t r = r_lo + tid + k * PR_BLOCK;
-        if (r < r_hi && rb[k] > ra[k]) s_own[ra[k] - e0] = r - r_lo + 1;
-    }
-    for (int32_t r = r_lo + ROWS + tid; r < r_hi; r += PR_BLOCK) {  // rows past the staged ones
-        int32_t a = in_rp[r], b = in_rp[r + 1];
-        if (b > a) s_own[a - e0] = r - r_lo + 1;
-    }
-    __syncthreads();
-    block_max_scan<VT>(s_own, n, s_red);
+struct PrArgs {
+    const int32_t *src;        // slot of every in-edge's source
+    const uint8_t *row_last;   // a bit per in-edge: the last of its row
+    const int32_t *tile_nz;
+    const int2 *nz, *ez;
+    const int32_t *nz_slot, *slot;
+    const int4 *cross;
+    int32_t n_cross, n_cross_long, n_cross_mid;
+    int64_t V, E, n_nz, n_ez;
+    int32_t ntiles;
+    const float *c_in;
+    double *Dp;
+    double inv_V;
+    double *head, *tailp, *dpart;
+    uint32_t *cpart;
+    int nparts;
+};
 
-    // a row's apply, from its staged data when it has some
-    auto apply_row = [&](int32_t r, double total, double &dsum, int &chg) {
-        const int i = r - r_lo;
-        if (i < ROWS)
-            ap.row(r, total, s_od[AP::kRows ? i : 0], s_sl[AP::kRows ? i : 0], s_xi[AP::kRows ? i : 0], dsum, chg);
-        else
-            ap(r, total, dsum, chg);
-    };
-    auto row_end = [&](int32_t r) { return r - r_lo < ROWS ? s_re[r - r_lo] : in_rp[r + 1]; };
+// A wave takes tiles of 64 * VT consecutive in-edges, lane l the VT edges from
+// l * VT on: it loads their source slots and row-end bits, gathers all their
+// contributions, and a segmented scan over the lanes gives each the sum that
+// the lanes before it leave open for its first row.  The sums of the rows that
+// end in the tile go through LDS, so that the rows' slots, old ranks and new
+// values are read and written by consecutive lanes.  A row that began in an
+// earlier tile leaves its sum in head, one that goes on in tailp.  Rows
+// without in-edges come last, four per lane.
+//
+// HOT: the contributions of the first slots (the sources of the most edges)
+// are staged in LDS, and only the other gathers go to memory: the staged
+// slots' offsets lie past the buffer, which fetches nothing.
+//
+// Bound by the gathers that reach an L2, about one per in-edge without the LDS
+// table; with it, 0.48 of the edges of R-MAT scale 22 (65 M in-edges).  There
+// the pull takes 262 us: 115 without any gather, 210 if all of them hit an L2,
+// 235 without the sums; the gathers' requests run at about 150 G/s whatever
+// the lanes' order.  A workgroup per tile, with every value staged in LDS and
+// a search for the row of each edge, took 483 us.
+// Inclusive sums over the lanes: within 16, within a half, over the wave.  Of
+// the lanes before this one, the nearest `from` belong to its segment.
+__device__ __forceinline__ double dpp_scan(double x, int from, int lane) {
+    const int at = lane & 15;
+#define GX_SCAN_STEP(CTRL, ROWS, TAKE)                                                                        \
+    {                                                                                                         \
+        const long long b = __double_as_longlong(x);                                                          \
+        const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);                        \
+        const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);                \
+        const bool take = TAKE;                                                                               \
+        x += __longlong_as_double(((long long)(take ? hi : 0) << 32) | (uint32_t)(take ? lo : 0));            \
+    }
+    GX_SCAN_STEP(0x111, 0xf, from >= 1)  // row_shr
+    GX_SCAN_STEP(0x112, 0xf, from >= 2)
+    GX_SCAN_STEP(0x114, 0xf, from >= 4)
+    GX_SCAN_STEP(0x118, 0xf, from >= 8)
+    GX_SCAN_STEP(0x142, 0xa, from > at)         // lane 15 of the row before (row_bcast:15)
+    GX_SCAN_STEP(0x143, 0xc, from > lane - 32)  // lane 31 (row_bcast:31)
+#undef GX_SCAN_STEP
+    return x;
+}
+__device__ __forceinline__ int dpp_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
 
-    // Per-thread contiguous chunk: sequential sums per destination row.
+template <int VT, bool HOT, class AP>
+__global__ __launch_bounds__(HOT ? 1024 : PR_BLOCK) void k_pr_pull(PrArgs a, AP ap) {
+    constexpr int NW = (HOT ? 1024 : PR_BLOCK) / 64, T = 64 * VT, SUMS = T < 256 ? T : 256;
+    constexpr int NEAR = HOT ? PR_LDS_SLOTS : 0;
+    __shared__ double s_sum[NW][SUMS];
+    __shared__ float s_hot[NEAR + 4];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    // from slot NEAR on; the staged slots' offsets wrap round and lie past the buffer, as does the padding's
+    const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(a.c_in) + NEAR, (short)0, (int)(uint32_t)((a.V - NEAR) * 4), 0x00020000);
+    if (HOT) {
+        for (int i = threadIdx.x; i < NEAR / 4; i += 1024)
+            reinterpret_cast<float4 *>(s_hot)[i] = reinterpret_cast<const float4 *>(a.c_in)[i];
+        if (threadIdx.x == 0) s_hot[NEAR] = 0.f;
+        __syncthreads();
+    }
+    ap.dD = ap.d * (*a.Dp) * a.inv_V;
+    double *sums = s_sum[wv];
     double dsum = 0.0;
     int chg = 0;
-    const int c0 = tid * VT, c1 = min(c0 + VT, n);
-    int own = -1;
-    bool started = false, first = true;
-    double sum = 0.0, first_sum = 0.0;
-    int first_own = -1;
-    bool defer_first = false, defer_ends_tile = false;
-    auto finish = [&](int o, double total, bool ends_tile) {
-        if (o == 0) {
-            head[t] = total;  // row continued from an earlier tile
-            return;
-        }
-        int32_t r = r_lo + o - 1;
-        if (ends_tile && row_end(r) > e0 + n) {
-            tailp[t] = total;  // row continues into later tiles
-            spill_row[t] = r;
-            return;
-        }
-        apply_row(r, total, dsum, chg);
+    const int gw = (int)blockIdx.x * NW + wv, nw = (int)gridDim.x * NW;
+    // Three tiles are in the works: the sources, row ends and rows of the one
+    // after next are loaded, the contributions and old ranks of the next one
+    // gathered, and this one is summed.
+    struct Rows {
+        uint32_t bits = 0;
+        int2 r = {0, 0};
+        int32_t ord = 0, sl = 0;
+        bool head = false;
     };
-    for (int p = c0; p < c1; p++) {
-        int o = s_own[p];
-        if (o != own) {
-            if (own >= 0) {  // run `own` ended at p-1 inside this chunk
-                if (first && !started) {
-                    defer_first = true;
-                    first_sum = sum;
-                    first_own = own;
-                } else {
-                    finish(own, sum, false);
+    const auto load = [&](int64_t t, int32_t(&u)[VT], Rows &q) {
+        const int64_t e0 = t * T, e1 = e0 + lane * VT;
+        // (the in-edges stream by once: kept out of the caches' way)
+        constexpr int LW = VT < 4 ? VT : 4;
+        typedef int32_t Wide __attribute__((ext_vector_type(LW)));
+#pragma unroll
+        for (int j = 0; j < VT; j += LW) {
+            const Wide x = __builtin_nontemporal_load(reinterpret_cast<const Wide *>(&a.src[e1 + j]));
+#pragma unroll
+            for (int i = 0; i < LW; i++) u[j + i] = x[i];
+        }
+        q.bits = (a.row_last[e1 >> 3] >> (e1 & 7)) & ((1u << VT) - 1u);
+        q.head = e0 > 0 && !((a.row_last[(e0 - 1) >> 3] >> 7) & 1u);
+        q.ord = a.tile_nz[t];
+        const int32_t i = min(q.ord + lane, (int32_t)a.n_nz - 1);
+        q.r = a.nz[i];
+        q.sl = AP::kRows ? a.nz_slot[i] : 0;
+    };
+    const auto gather = [&](const int32_t(&u)[VT], const Rows &q, float(&cv)[VT], float &xi) {
+        xi = AP::kRows ? ap.x_in[q.r.x] : 0.f;
+#pragma unroll
+        for (int j = 0; j < VT; j++)
+            cv[j] = HOT ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(crs, ((uint32_t)u[j] - NEAR) * 4u, 0, 0))
+                        : a.c_in[u[j]];
+    };
+    int32_t u[VT], un[VT];
+    float cv[VT], xi = 0.f;
+    Rows q, qn;
+    if (gw < a.ntiles) {
+        load(gw, u, q);
+        if (gw + nw < a.ntiles) load(gw + nw, un, qn);
+        gather(u, q, cv, xi);
+    }
+    for (int64_t t = gw; t < a.ntiles; t += nw) {
+        int32_t us[VT];
+        float cn[VT], xn = 0.f;
+        Rows qs;
+        if (t + 2 * nw < a.ntiles) load(t + 2 * nw, us, qs);
+        if (t + nw < a.ntiles) gather(un, qn, cn, xn);
+        if (HOT)
+#pragma unroll
+            for (int j = 0; j < VT; j++) cv[j] += s_hot[min((uint32_t)u[j], (uint32_t)NEAR)];  // (one of them is 0)
+        else if ((t + 1) * T > a.E)
+#pragma unroll
+            for (int j = 0; j < VT; j++) cv[j] = t * T + lane * VT + j < a.E ? cv[j] : 0.f;
+        const int n = __popc(q.bits);
+        const int upto = dpp_scan(n), ends = __builtin_amdgcn_readlane(upto, 63);
+        const unsigned long long has = __ballot(n > 0) & (~0ull >> (63 - lane));
+        // what each lane leaves open, and what the lanes before it carry into its first row
+        double open = 0.0;
+#pragma unroll
+        for (int j = 0; j < VT; j++) open += (double)(q.bits < (1u << j) ? cv[j] : 0.f);
+        open = dpp_scan(open, has ? lane - 63 + __clzll(has) : lane, lane);
+        const long long ob = __double_as_longlong(open);
+        const int clo = __builtin_amdgcn_update_dpp(0, (int)ob, 0x138, 0xf, 0xf, false);  // wave_shr:1
+        const int chi = __builtin_amdgcn_update_dpp(0, (int)(ob >> 32), 0x138, 0xf, 0xf, false);
+        const double carry = __longlong_as_double(((long long)chi << 32) | (uint32_t)clo);
+        if (lane == 63) {  // what is open at the end of the tile
+            if (ends > 0 || !q.head) a.tailp[t] = open;
+            else a.head[t] = open;
+        }
+        for (int base = 0; base < ends; base += SUMS) {
+            __builtin_amdgcn_wave_barrier();
+            double sum = carry;
+            int p = upto - n - base;
+#pragma unroll
+            for (int j = 0; j < VT; j++) {
+                sum += (double)cv[j];
+                if ((q.bits >> j) & 1u) {
+                    if (T == SUMS || (uint32_t)p < (uint32_t)SUMS) sums[p] = sum;
+                    p++;
+                    sum = 0.0;
                 }
-                first = false;
             }
-            own = o;
-            sum = 0.0;
-            started = (p == 0) ? (o != 0) : (p > c0 || s_own[p - 1] != o);
-        }
-        sum += (double)s_val[p];
-    }
-    bool last_ends_here = false;
-    if (own >= 0) {
-        last_ends_here = (c1 == n) || (s_own[c1] != own);
-        if (last_ends_here) {
-            if (first && !started) {
-                defer_first = true;
-                defer_ends_tile = (c1 == n);
-                first_sum = sum;
-                first_own = own;
-            } else {
-                finish(own, sum, c1 == n);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (base == 0) {
+                if (q.head && lane == 0) a.head[t] = sums[0];
+                if (lane >= (q.head ? 1 : 0) && lane < ends) ap.row(q.r.x, sums[lane], q.r.y, q.sl, xi, dsum, chg);
+            }
+            for (int i = base + lane + (base ? 0 : 64); i < min(ends, base + SUMS); i += 64) {
+                const int2 r = a.nz[q.ord + i];
+                ap.row(r.x, sums[i - base], r.y, AP::kRows ? a.nz_slot[q.ord + i] : 0, AP::kRows ? ap.x_in[r.x] : 0.f,
+                       dsum, chg);
             }
         }
-    }
-    // Pieces of rows that run past a chunk: an inclusive segmented scan over
-    // the threads, a segment starting at the thread where a row's trailing
-    // piece starts (or where a row ends).  Fixed order: a shuffle scan inside
-    // each wave, then the wave totals folded in wave order; a deferred first
-    // piece then adds the scan value of the thread before it.
-    {
-        double y = (own >= 0 && !last_ends_here) ? sum : 0.0;
-        int f = (own < 0 || started || last_ends_here) ? 1 : 0;
-        const int lane = tid & 63, wv = tid >> 6;
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const double yp = __shfl_up(y, d, 64);
-            const int fp = __shfl_up(f, d, 64);
-            if (lane >= d) {
-                if (!f) y = yp + y;
-                f |= fp;
-            }
+        for (int j = 0; j < VT; j++) {
+            u[j] = un[j];
+            un[j] = us[j];
+            cv[j] = cn[j];
         }
-        if (lane == 63) {
-            s_wy[wv] = y;
-            s_wf[wv] = f;
-        }
-        __syncthreads();
-        if (!f) {
-            double c = 0.0;
-            for (int v = 0; v < wv; v++) c = s_wf[v] ? s_wy[v] : c + s_wy[v];
-            y = c + y;
-        }
-        s_last[tid] = y;
+        xi = xn;
+        q = qn;
+        qn = qs;
     }
-    __syncthreads();
-    if (defer_first) finish(first_own, tid > 0 ? first_sum + s_last[tid - 1] : first_sum, defer_ends_tile);
-    // Rows of this tile without in-edges.
+    // rows without in-edges
+    for (int64_t i0 = (int64_t)gw * 256; i0 < a.n_ez; i0 += (int64_t)nw * 256) {
+        int2 r[4];
+        int32_t sl[4];
+        float xi[4];
 #pragma unroll
-    for (int k = 0; k < RPT; k++) {
-        const int32_t r = r_lo + tid + k * PR_BLOCK;
-        if (r < r_hi && rb[k] == ra[k]) apply_row(r, 0.0, dsum, chg);
+        for (int j = 0; j < 4; j++) r[j] = a.ez[min(i0 + 64 * j + lane, a.n_ez - 1)];
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            sl[j] = AP::kRows && r[j].y > 0 ? a.slot[r[j].x] : 0;
+            xi[j] = AP::kRows ? ap.x_in[r[j].x] : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+            if (i0 + 64 * j + lane < a.n_ez) ap.row(r[j].x, 0.0, r[j].y, sl[j], xi[j], dsum, chg);
     }
-    for (int32_t r = r_lo + ROWS + tid; r < r_hi; r += PR_BLOCK)
-        if (in_rp[r + 1] == in_rp[r]) ap(r, 0.0, dsum, chg);
-    double td = block_sum<double>(dsum, s_d);
-    unsigned long long tc = block_sum<unsigned long long>((unsigned long long)chg, s_c);
-    if (tid == 0) {  // per-tile partials, summed by k_pr_fix (no atomics on one shared counter)
-        dpart[t] = td;
-        cpart[t] = (uint32_t)tc;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        dsum += __shfl_down(dsum, o, 64);
+        chg += __shfl_down(chg, o, 64);
+    }
+    if (lane == 0) {  // per-wave partials, summed by k_pr_fix (no atomics on one shared counter)
+        a.dpart[gw] = dsum;
+        a.cpart[gw] = (uint32_t)chg;
     }
 }
 
-// Completes the rows that cross tile boundaries (each by one thread, adding
-// the row's partials in tile order) and reduces the dangling mass of the new
-// ranks for the next superstep: every workgroup leaves its partial sums, and
-// the last one to finish adds them up in workgroup order, so the result does
-// not depend on timing.  The kernel boundary makes every pull workgroup's
-// partials visible here; *Dp (the old mass) is read by every workgroup
+// Completes the rows that cross tile boundaries and reduces the dangling mass
+// of the new ranks for the next superstep: every workgroup leaves its partial
+// sums, and the last one to finish adds them up in workgroup order, so the
+// result does not depend on timing (a single workgroup is done with its own).
+// A chain of dependent accesses bounds it, so each wave has one kind of work:
+// R-MAT scale 22 43 us with a thread or sixteen lanes per row one after the
+// other in 1024 workgroups of 256, whose returning atomics on one counter
+// queue, 21 us in workgroups of 1024; 20 supersteps of scale 14 take 329 us with
+// the kinds one after the other, 278 us so (tiles of 1024).  The kernel boundary makes every pull
+// wave's partials visible here; *Dp (the old mass) is read by every workgroup
 // before the last one overwrites it.
-constexpr int PR_FIX_BLOCK = 256;
-constexpr int PR_FIX_MAX_GRID = 1024;
+constexpr int PR_FIX_BLOCK = 1024;  // (at most)
+constexpr int PR_FIX_MAX_GRID = 512;
+
+// The work of a k_pr_fix wave, in this order; each bound is the first unit of
+// the next kind.
+struct PrFixUnits {
+    int wave, mid, few, all;
+    __host__ __device__ PrFixUnits(int n_cross, int n_long, int n_mid, int nparts)
+        : wave(n_long), mid(wave + (n_mid + 3) / 4), few(mid + (n_cross - n_long - n_mid + 63) / 64),
+          all(few + (nparts + 255) / 256) {}
+};
 
 template <class AP>
-__global__ __launch_bounds__(PR_FIX_BLOCK) void k_pr_fix(const int32_t *__restrict__ in_rp, int32_t ntiles,
-                                                         int32_t tile, const double *__restrict__ head,
-                                                         const double *__restrict__ tailp,
-                                                         const int32_t *__restrict__ spill_row,
-                                                         const double *__restrict__ dpart,
-                                                         const uint32_t *__restrict__ cpart, AP ap, double *Dp,
-                                                         double inv_V, DevStep *__restrict__ step,
+__global__ __launch_bounds__(PR_FIX_BLOCK) void k_pr_fix(PrArgs a, AP ap, DevStep *__restrict__ step,
                                                          DevStep *__restrict__ next_step, double *fix_d,
                                                          unsigned long long *fix_c, uint32_t *fix_done) {
     __shared__ double s_d[PR_FIX_BLOCK / 64];
     __shared__ unsigned long long s_c[PR_FIX_BLOCK / 64];
     __shared__ int s_last;
-    ap.dD = ap.d * (*Dp) * inv_V;
+    ap.dD = ap.d * (*a.Dp) * a.inv_V;
     double dsum = 0.0;
     int chg = 0;
     unsigned long long csum = 0;
-    for (int32_t t = blockIdx.x * PR_FIX_BLOCK + threadIdx.x; t < ntiles; t += gridDim.x * PR_FIX_BLOCK) {
-        const int32_t r = spill_row[t];
-        if (r >= 0) {
-            double total = tailp[t];
-            const int32_t t_end = (in_rp[r + 1] - 1) / tile;
-            for (int32_t t2 = t + 1; t2 <= t_end; t2++) total += head[t2];
-            ap(r, total, dsum, chg);
+    const int lane = threadIdx.x & 63, sub = lane & 15, waves = (int)(gridDim.x * blockDim.x) / 64;
+    const PrFixUnits n(a.n_cross, a.n_cross_long, a.n_cross_mid, a.nparts);
+    for (int w = (int)(blockIdx.x * blockDim.x + threadIdx.x) / 64; w < n.all; w += waves) {
+        if (w >= n.few) {  // the pull's partials, four per lane
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const int i = (w - n.few) * 256 + 64 * k + lane;
+                if (i < a.nparts) {
+                    dsum += a.dpart[i];
+                    csum += a.cpart[i];
+                }
+            }
+            continue;
         }
-        dsum += dpart[t];
-        csum += cpart[t];
+        // a row of many tiles takes the wave (a contiguous piece of them per
+        // lane, then a fixed tree), one of some tiles sixteen lanes, one of
+        // few a thread
+        const int width = w < n.wave ? 64 : w < n.mid ? 16 : 1;
+        const int j = w < n.wave ? w : w < n.mid ? a.n_cross_long + (w - n.wave) * 4 + lane / 16
+                                                 : a.n_cross_long + a.n_cross_mid + (w - n.mid) * 64 + lane;
+        const bool on = j < (w < n.mid ? a.n_cross_long + a.n_cross_mid : a.n_cross);
+        if (width > 1) {
+            const int4 q = on ? a.cross[j] : make_int4(0, 0, 0, -1);
+            const int32_t sl = AP::kRows ? a.slot[q.x] : 0;
+            const float xi = AP::kRows ? ap.x_in[q.x] : 0.f;
+            const int at = width == 64 ? lane : sub;
+            double s = on && at == 0 ? a.tailp[q.z] : 0.0;
+            const int64_t m = q.w - q.z;
+            for (int64_t i = m * at / width; i < m * (at + 1) / width; i++) s += a.head[q.z + 1 + i];
+            if (width == 64) {
+                s += __shfl_down(s, 32, 64);
+                s += __shfl_down(s, 16, 64);
+            }
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+            if (on && at == 0) ap.row(q.x, s, q.y, sl, xi, dsum, chg);
+        } else if (on) {
+            const int4 q = a.cross[j];
+            const int32_t sl = AP::kRows ? a.slot[q.x] : 0;
+            const float xi = AP::kRows ? ap.x_in[q.x] : 0.f;
+            double s = a.tailp[q.z];
+            for (int32_t t = q.z + 1; t <= q.w; t++) s += a.head[t];
+            ap.row(q.x, s, q.y, sl, xi, dsum, chg);
+        }
     }
     const double td = block_sum<double>(dsum, s_d);
     const unsigned long long tc = block_sum<unsigned long long>(csum + (unsigned long long)chg, s_c);
-    if (threadIdx.x == 0) {
+    if (gridDim.x > 1 && threadIdx.x == 0) {
         fix_d[blockIdx.x] = td;
         fix_c[blockIdx.x] = tc;
         // release this workgroup's partials; acquire the others' if last
         const uint32_t before = __hip_atomic_fetch_add(fix_done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
         s_last = before == gridDim.x - 1;
     }
-    __syncthreads();
-    if (!s_last) return;
-    __threadfence();
-    double d = 0.0;
-    unsigned long long c = 0;
-    for (uint32_t b = threadIdx.x; b < gridDim.x; b += PR_FIX_BLOCK) {
-        d += fix_d[b];
-        c += fix_c[b];
+    double D = td;
+    unsigned long long C = tc;
+    if (gridDim.x > 1) {
+        __syncthreads();
+        if (!s_last) return;
+        __threadfence();
+        double d = 0.0;
+        unsigned long long c = 0;
+        for (uint32_t b = threadIdx.x; b < gridDim.x; b += blockDim.x) {
+            d += fix_d[b];
+            c += fix_c[b];
+        }
+        D = block_sum<double>(d, s_d);
+        C = block_sum<unsigned long long>(c, s_c);
     }
-    const double D = block_sum<double>(d, s_d);
-    const unsigned long long C = block_sum<unsigned long long>(c, s_c);
     if (threadIdx.x == 0) {
-        *Dp = D;  // dangling mass of x_{t+1}
+        *a.Dp = D;  // dangling mass of x_{t+1}
         step->changed = C;
         step->frontier = 0;
         *next_step = DevStep{};
@@ -1331,6 +1386,56 @@ static void launch_compact(gx_state *s, hipStream_t hs, const uint8_t *front, ui
                        s->hot[0] ? d.slot : nullptr, s->hot[k & 1], s->hot[(k + 1) & 1]);
 }
 
+// The pull of this graph's tiles (and the fewest workgroups that hold every
+// wave the CUs can, or every tile).
+template <class AP>
+static auto pr_pull_for(const DevGraph &d) {
+    if (d.pr_hot)
+        return d.pr_tile == 256 ? k_pr_pull<1, true, AP> : d.pr_tile == 512 ? k_pr_pull<2, true, AP>
+             : d.pr_tile == 1024 ? k_pr_pull<4, true, AP> : k_pr_pull<8, true, AP>;
+    return d.pr_tile == 256 ? k_pr_pull<1, false, AP> : d.pr_tile == 512 ? k_pr_pull<2, false, AP>
+         : d.pr_tile == 1024 ? k_pr_pull<4, false, AP> : k_pr_pull<8, false, AP>;
+}
+
+static int pr_grid_for(gx_graph *g, const gx_params *p) {
+    const DevGraph &d = g->d;
+    if (d.pr_hot) return g->num_cus;
+    const int64_t items = std::max(d.pr_rows.n, (d.n_ez + 255) / 256), waves = PR_BLOCK / 64;
+    const int resident = p->phases ? persistent_grid(g, pr_pull_for<PrStore>(d), PR_BLOCK)
+                                   : persistent_grid(g, pr_pull_for<PrApply>(d), PR_BLOCK);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(resident, (items + waves - 1) / waves));
+}
+
+static PrArgs pr_args(const gx_state *s, const float *c_in, double *Dp, double inv_V) {
+    const DevGraph &d = s->g->d;
+    PrArgs a{};
+    a.src = d.pr_src;
+    a.row_last = reinterpret_cast<const uint8_t *>(d.row_last);
+    a.tile_nz = d.pr_rows.tile_nz;
+    a.nz = d.nz;
+    a.ez = d.ez;
+    a.nz_slot = d.nz_slot;
+    a.slot = d.slot;
+    a.cross = d.pr_rows.cross;
+    a.n_cross = d.pr_rows.n_cross;
+    a.n_cross_long = d.pr_rows.n_long;
+    a.n_cross_mid = d.pr_rows.n_mid;
+    a.V = d.V;
+    a.E = d.E;
+    a.n_nz = d.n_nz;
+    a.n_ez = d.n_ez;
+    a.ntiles = (int32_t)d.pr_rows.n;
+    a.c_in = c_in;
+    a.Dp = Dp;
+    a.inv_V = inv_V;
+    a.head = s->head;
+    a.tailp = s->tailp;
+    a.dpart = s->dpart;
+    a.cpart = s->cpart;
+    a.nparts = s->pr_parts;
+    return a;
+}
+
 static size_t state_layout(gx_graph *g, const gx_params *p, Carver &c, gx_state *s) {
     const DevGraph &d = g->d;
     int64_t V = d.V;
@@ -1338,19 +1443,22 @@ static size_t state_layout(gx_graph *g, const gx_params *p, Carver &c, gx_state 
     if (p->algo == GX_LP) {
         lp_layout(g, c, s);
     } else if (p->algo == GX_PAGERANK) {
-        int32_t nt = d.pr_ntiles;
+        const int64_t nt = std::max<int64_t>(1, d.pr_rows.n);
         s->x[0] = c.take<float>(V);
         s->x[1] = c.take<float>(V);
-        s->contrib[0] = c.take<float>(V);
-        s->contrib[1] = c.take<float>(V);
+        s->contrib[0] = c.take<float>(V + 1);  // (the last tile's padding reads one past the slots)
+        s->contrib[1] = c.take<float>(V + 1);
         s->synced = c.take<uint32_t>(V);
         s->head = c.take<double>(nt);
         s->tailp = c.take<double>(nt);
-        s->spill_row = c.take<int32_t>(nt);
-        s->dpart = c.take<double>(std::max<int64_t>(nt, grid_for<int64_t>(V, 256)));
-        s->cpart = c.take<uint32_t>(std::max<int64_t>(nt, 1));
+        s->pr_grid = pr_grid_for(g, p);
+        s->pr_parts = s->pr_grid * (d.pr_hot ? 16 : PR_BLOCK / 64);
+        s->dpart = c.take<double>(std::max<int64_t>(s->pr_parts, grid_for<int64_t>(V, 256)));
+        s->cpart = c.take<uint32_t>(s->pr_parts);
         s->Dval = c.take<double>(1);
-        s->pr_fix_grid = (int)std::min<int64_t>(PR_FIX_MAX_GRID, std::max<int64_t>(1, (nt + PR_FIX_BLOCK - 1) / PR_FIX_BLOCK));
+        const int units = PrFixUnits(d.pr_rows.n_cross, d.pr_rows.n_long, d.pr_rows.n_mid, s->pr_parts).all;
+        s->pr_fix_block = units <= PR_FIX_BLOCK / 64 || units >= 1024 ? PR_FIX_BLOCK : 256;
+        s->pr_fix_grid = std::min(PR_FIX_MAX_GRID, (units * 64 + s->pr_fix_block - 1) / s->pr_fix_block);
         s->fix_d = c.take<double>(s->pr_fix_grid);
         s->fix_c = c.take<unsigned long long>(s->pr_fix_grid);
         s->fix_done = c.take<uint32_t>(1);
@@ -1641,20 +1749,14 @@ static gx_status enqueue_superstep(gx_state *s, hipStream_t hs) {
     } else if (p.algo == GX_PAGERANK) {
         int cur = (int)(s->k & 1);
         double dd = p.damping;
-        PrApply ap{(1.0 - dd) / (double)d.V, dd, 0.0, d.outdeg, s->x[cur], s->x[cur ^ 1], s->contrib[cur ^ 1],
-                   d.slot};
-        double inv_V = d.V > 0 ? 1.0 / (double)d.V : 0.0;
+        const PrApply ap{(1.0 - dd) / (double)d.V, dd, 0.0, s->x[cur], s->x[cur ^ 1], s->contrib[cur ^ 1]};
         if (d.V > 0) {
+            const PrArgs a = pr_args(s, s->contrib[cur], s->Dval, 1.0 / (double)d.V);
             if (e0) (void)hipEventRecord(e0, hs);
-            auto pull = d.pr_tile == 256 ? k_pr_pull<1, PrApply> : d.pr_tile == 512 ? k_pr_pull<2, PrApply>
-                      : d.pr_tile == 1024 ? k_pr_pull<4, PrApply> : k_pr_pull<8, PrApply>;
-            hipLaunchKernelGGL(pull, dim3(d.pr_ntiles), dim3(PR_BLOCK), 0, hs, d.in_rp, d.pr_src, d.pr_tile_row,
-                               d.E, s->contrib[cur], ap, s->Dval, inv_V, s->head, s->tailp, s->spill_row, s->dpart,
-                               s->cpart);
+            hipLaunchKernelGGL(pr_pull_for<PrApply>(d), dim3(s->pr_grid), dim3(d.pr_hot ? 1024 : PR_BLOCK), 0, hs, a, ap);
             if (e1) (void)hipEventRecord(e1, hs);
-            hipLaunchKernelGGL(k_pr_fix<PrApply>, dim3(s->pr_fix_grid), dim3(PR_FIX_BLOCK), 0, hs, d.in_rp, d.pr_ntiles,
-                               d.pr_tile, s->head, s->tailp, s->spill_row, s->dpart, s->cpart, ap, s->Dval, inv_V,
-                               step, next, s->fix_d, s->fix_c, s->fix_done);
+            hipLaunchKernelGGL(k_pr_fix<PrApply>, dim3(s->pr_fix_grid), dim3(s->pr_fix_block), 0, hs, a, ap, step, next,
+                               s->fix_d, s->fix_c, s->fix_done);
         }
     } else {
         // superstep k: relax A_k (list built by the previous compaction), then
@@ -2122,15 +2224,10 @@ extern "C" gx_status gx_msg_merge(gx_state *s, void *stream) {
     if (d.V > 0) {
         if (s->p.algo == GX_PAGERANK) {
             const PrStore ap{(double)s->p.damping, 0.0, s->acc_d};
-            const double inv_V = 1.0 / (double)d.V;
-            auto pull = d.pr_tile == 256 ? k_pr_pull<1, PrStore> : d.pr_tile == 512 ? k_pr_pull<2, PrStore>
-                      : d.pr_tile == 1024 ? k_pr_pull<4, PrStore> : k_pr_pull<8, PrStore>;
-            hipLaunchKernelGGL(pull, dim3(d.pr_ntiles), dim3(PR_BLOCK), 0, hs, d.in_rp, d.pr_src, d.pr_tile_row, d.E,
-                               s->contrib[0], ap, s->Dscratch, inv_V, s->head, s->tailp, s->spill_row, s->dpart,
-                               s->cpart);
-            hipLaunchKernelGGL(k_pr_fix<PrStore>, dim3(s->pr_fix_grid), dim3(PR_FIX_BLOCK), 0, hs, d.in_rp,
-                               d.pr_ntiles, d.pr_tile, s->head, s->tailp, s->spill_row, s->dpart, s->cpart, ap,
-                               s->Dscratch, inv_V, s->ph_steps, s->ph_steps + 1, s->fix_d, s->fix_c, s->fix_done);
+            const PrArgs a = pr_args(s, s->contrib[0], s->Dscratch, 1.0 / (double)d.V);
+            hipLaunchKernelGGL(pr_pull_for<PrStore>(d), dim3(s->pr_grid), dim3(d.pr_hot ? 1024 : PR_BLOCK), 0, hs, a, ap);
+            hipLaunchKernelGGL(k_pr_fix<PrStore>, dim3(s->pr_fix_grid), dim3(s->pr_fix_block), 0, hs, a, ap, s->ph_steps,
+                               s->ph_steps + 1, s->fix_d, s->fix_c, s->fix_done);
         } else {
             // the relaxation of the fused superstep, against the accumulator:
             // it combines the messages by minimum and changes no vertex value
