@@ -178,6 +178,7 @@ struct HostImages {
     std::vector<int32_t> in_blk;
     std::vector<uint4> pull_segs, sym_segs, packs;
     std::vector<uint32_t> rem_out, rem_any, master, master_rep;
+    std::vector<int32_t> part_list;
 };
 
 static gx_status validate(const gx_graph_desc *d) {
@@ -528,6 +529,8 @@ static void build_flags(const gx_graph_desc *d, int32_t W, HostImages &h) {
         if (f & GX_FLAG_REMOTE_ANY) h.rem_any[v >> 5] |= bit;
         if (f & GX_FLAG_MASTER) h.master[v >> 5] |= bit;
         if ((f & GX_FLAG_MASTER) && (f & GX_FLAG_REMOTE_ANY)) h.master_rep[v >> 5] |= bit;
+        if (d->outdeg_global && !(f & GX_FLAG_MASTER) && (f & GX_FLAG_REMOTE_ANY) && h.in_rp[v + 1] > h.in_rp[v])
+            h.part_list.push_back((int32_t)v);
     }
 }
 
@@ -582,6 +585,7 @@ static void layout(const gx_graph_desc *desc, int64_t E_sym, Carver &c, DevGraph
     if (desc->outdeg_global) {
         d->outdeg_g = c.take<int32_t>(V);
         d->V_global = desc->V_global;
+        if (desc->flags) d->part_list = c.take<int32_t>(V);
     }
     if (desc->flags) {
         d->remote_out = c.take<uint32_t>(d->W);
@@ -740,6 +744,7 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
     g->d.pull_nsegs = (int64_t)h.pull_segs.size();
     g->d.n_nz = (int64_t)h.nz.size();
     g->d.n_ez = (int64_t)h.ez.size();
+    g->d.n_part = (int64_t)h.part_list.size();
     for (auto [r, t] : {std::pair(&g->d.pr_rows, &h.pr_rows), std::pair(&g->d.bp_rows, &h.bp_rows)}) {
         r->n_cross = (int32_t)t->cross.size();
         r->n_long = t->n_long;
@@ -815,6 +820,7 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
         e = up.put_array((void *)d.remote_out, h.rem_out.data(), (size_t)W * 4);
         if (e == hipSuccess) e = up.put_array((void *)d.remote_any, h.rem_any.data(), (size_t)W * 4);
         if (e == hipSuccess) e = up.put_array((void *)d.master, h.master.data(), (size_t)W * 4);
+        if (e == hipSuccess && d.part_list) e = up.put_array((void *)d.part_list, h.part_list.data(), h.part_list.size() * 4);
         if (e == hipSuccess) e = up.put_array((void *)d.master_rep, h.master_rep.data(), (size_t)W * 4);
     }
     if (e == hipSuccess) e = up.finish(s);

@@ -180,6 +180,8 @@ struct DevGraph {
     // partition metadata
     const int32_t *l2g = nullptr;          // nullptr = identity
     const uint32_t *remote_out = nullptr;  // bitmaps of W words (nullptr = none remote)
+    const int32_t *part_list = nullptr;  // replicas with in-edges whose master is elsewhere (PageRank over parts)
+    int64_t n_part = 0;
     const uint32_t *remote_any = nullptr;
     const uint32_t *master = nullptr;      // this part holds the master copy
     const uint32_t *master_rep = nullptr;  // ... of a vertex another part holds a replica of
@@ -333,13 +335,11 @@ struct gx_state {
     double *Dscratch = nullptr;      // dangling-mass slot the merge's fix-up writes (never read)
     gx::DevStep *ph_steps = nullptr; // counter slots the merge's fix-up writes (never read)
     int ph_p = 0;                    // front8[ph_p] collects the vertices the next MSGGen sends from
-    double D_host = 0.0;             // staging of gx_dangling_set (lives as long as the state)
     bool ph_msgs = false, ph_merged = false;
     // shared
     gx::DevStep *steps = nullptr;
     uint32_t *blk_cnt = nullptr;
-    uint32_t *delta_total = nullptr;
-    int delta_blocks = 0;
+    int delta_blocks = 0, delta_words = 0;
     // edge-kernel timing
     std::vector<hipEvent_t> ev_pool;
     struct Pending {

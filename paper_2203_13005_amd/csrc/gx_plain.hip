@@ -1035,85 +1035,43 @@ __global__ __launch_bounds__(PR_FIX_BLOCK) void k_pr_fix(PrArgs a, AP ap, DevSte
 
 __device__ __forceinline__ bool bit_of(const uint32_t *bm, int64_t v) { return (bm[v >> 5] >> (v & 31)) & 1u; }
 
-// Replicas this part sends its merged messages for: held elsewhere too, the
-// master elsewhere, and with at least one in-edge here (else the sum is 0).
-__device__ __forceinline__ uint32_t partial_word(int32_t w, int64_t V, const uint32_t *remote_any,
-                                                 const uint32_t *master, const int32_t *in_rp) {
-    const uint32_t valid = (int64_t)(w + 1) * 32 <= V ? 0xFFFFFFFFu : ((1u << (V - (int64_t)w * 32)) - 1u);
-    const uint32_t cand = remote_any[w] & ~master[w] & valid;
-    uint32_t out = 0;
-    for (uint32_t m = cand; m; m &= m - 1) {
-        const int b = __ffs(m) - 1;
-        const int64_t v = (int64_t)w * 32 + b;
-        if (in_rp[v + 1] > in_rp[v]) out |= 1u << b;
-    }
-    return out;
+// The replicas whose merged sums another part's master needs are known with
+// the graph (ascending local, hence global ids): (gid, sum) of each.  Counting
+// and selecting them from the bit maps on every call, 32 vertices per thread,
+// took 29 us for a part of R-MAT scale 18 (one of four), this 3 us.
+__global__ __launch_bounds__(256) void k_part_emit(const int32_t *__restrict__ part_list, uint32_t n,
+                                                   const int32_t *__restrict__ l2g, const double *__restrict__ acc,
+                                                   int32_t *__restrict__ gid_out, double *__restrict__ val_out) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int32_t v = part_list[i];
+    gid_out[i] = l2g[v];
+    val_out[i] = acc[v];
 }
 
-__global__ __launch_bounds__(256) void k_part_count(int32_t W, int64_t V, const uint32_t *remote_any,
-                                                    const uint32_t *master, const int32_t *in_rp, uint32_t *blk_cnt) {
-    __shared__ unsigned long long s[4];
-    const int32_t w = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t c = w < W ? __popc(partial_word(w, V, remote_any, master, in_rp)) : 0u;
-    const unsigned long long t = block_sum<unsigned long long>(c, s);
-    if (threadIdx.x == 0) blk_cnt[blockIdx.x] = (uint32_t)t;
+// Local id of a global one (-1: not held): a search over 256 samples of the
+// ascending map in LDS, then over one 256th of the map.  The chain of
+// dependent reads bounds it: the whole search in global memory took 7.2 us
+// for a part of R-MAT scale 18 (one of four; a launch alone about 3), 6.4 us so.
+constexpr int MAP_SAMPLES = 256;
+__device__ __forceinline__ void sample_map(const int32_t *__restrict__ l2g, int64_t V, int32_t *s_top) {
+    const int64_t end = (threadIdx.x + 1) * V / MAP_SAMPLES;  // (256 threads)
+    s_top[threadIdx.x] = end > 0 ? l2g[end - 1] : -1;
+    __syncthreads();
 }
-
-// (gid, merged sum) of the selected replicas in ascending gid; positions from
-// the block counts as in the sync set.
-__global__ __launch_bounds__(256) void k_part_emit(int32_t W, int64_t V, const uint32_t *remote_any,
-                                                   const uint32_t *master, const int32_t *in_rp,
-                                                   const int32_t *l2g, const double *__restrict__ acc,
-                                                   const uint32_t *__restrict__ blk_cnt, int nblk, uint32_t cap,
-                                                   int32_t *gid_out, double *val_out, uint32_t *total_out) {
-    __shared__ unsigned long long s_scan[4];
-    __shared__ unsigned long long s_pre[4], s_all[4];
-    const int tid = threadIdx.x;
-    unsigned long long pre = 0, all_ = 0;
-    for (int b = tid; b < nblk; b += blockDim.x) {
-        const unsigned long long c = blk_cnt[b];
-        all_ += c;
-        if (b < (int)blockIdx.x) pre += c;
-    }
-    {
-        const int lane = tid & 63, wid = tid >> 6;
+__device__ __forceinline__ int64_t local_of(const int32_t *__restrict__ l2g, int64_t V, const int32_t *s_top, int32_t g) {
+    int p = 0;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            pre += __shfl_down(pre, o, 64);
-            all_ += __shfl_down(all_, o, 64);
-        }
-        if (lane == 0) {
-            s_pre[wid] = pre;
-            s_all[wid] = all_;
-        }
-        __syncthreads();
-        pre = s_pre[0] + s_pre[1] + s_pre[2] + s_pre[3];
-        all_ = s_all[0] + s_all[1] + s_all[2] + s_all[3];
-        __syncthreads();
-    }
-    if (blockIdx.x == 0 && tid == 0) *total_out = (uint32_t)all_;
-    const int32_t w = blockIdx.x * blockDim.x + tid;
-    const uint32_t bits = w < W ? partial_word(w, V, remote_any, master, in_rp) : 0u;
-    unsigned long long tot;
-    unsigned long long pos = pre + block_excl_scan_u64(__popc(bits), &tot, s_scan);
-    for (uint32_t m = bits; m; m &= m - 1) {
-        const int64_t v = (int64_t)w * 32 + __ffs(m) - 1;
-        if (pos < cap) {
-            gid_out[pos] = l2g[v];
-            val_out[pos] = acc[v];
-        }
-        pos++;
-    }
-}
-
-__device__ __forceinline__ int64_t local_of(const int32_t *__restrict__ l2g, int64_t V, int32_t g) {
-    int64_t lo = 0, hi = V;
+    for (int step = MAP_SAMPLES / 2; step > 0; step /= 2)
+        if (s_top[p + step - 1] < g) p += step;
+    if (s_top[p] < g) return -1;  // beyond the last
+    int64_t lo = p * V / MAP_SAMPLES, hi = (p + 1) * V / MAP_SAMPLES;
     while (lo < hi) {
         const int64_t mid = (lo + hi) / 2;
         if (l2g[mid] < g) lo = mid + 1;
         else hi = mid;
     }
-    return (lo < V && l2g[lo] == g) ? lo : -1;
+    return l2g[lo] == g ? lo : -1;
 }
 
 // A master adds another part's merged sum for it (one pair per vertex per
@@ -1121,9 +1079,12 @@ __device__ __forceinline__ int64_t local_of(const int32_t *__restrict__ l2g, int
 __global__ __launch_bounds__(256) void k_part_add(const int32_t *__restrict__ gid, const double *__restrict__ vals,
                                                   uint32_t n, const int32_t *__restrict__ l2g, int64_t V,
                                                   const uint32_t *__restrict__ master, double *__restrict__ acc) {
+    __shared__ int32_t s_top[MAP_SAMPLES];
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int32_t g = i < n ? gid[i] : -1;
+    sample_map(l2g, V, s_top);
     if (i >= n) return;
-    const int64_t x = local_of(l2g, V, gid[i]);
+    const int64_t x = local_of(l2g, V, s_top, g);
     if (x >= 0 && bit_of(master, x)) acc[x] += vals[i];
 }
 
@@ -1131,55 +1092,83 @@ __global__ __launch_bounds__(256) void k_part_add(const int32_t *__restrict__ gi
 __global__ __launch_bounds__(256) void k_replica_set(const int32_t *__restrict__ gid, const uint32_t *__restrict__ vals,
                                                      uint32_t n, const int32_t *__restrict__ l2g, int64_t V,
                                                      const uint32_t *__restrict__ master, uint32_t *__restrict__ x) {
+    __shared__ int32_t s_top[MAP_SAMPLES];
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int32_t g = i < n ? gid[i] : -1;
+    sample_map(l2g, V, s_top);
     if (i >= n) return;
-    const int64_t v = local_of(l2g, V, gid[i]);
+    const int64_t v = local_of(l2g, V, s_top, g);
     if (v >= 0 && !bit_of(master, v)) x[v] = vals[i];
 }
 
 // ------------------------------------------------------------ sync set
 
-__device__ __forceinline__ uint32_t delta_word(int32_t w, int64_t V, const uint32_t *remote, bool all,
-                                               const uint8_t *dirty, const uint32_t *vals,
-                                               const uint32_t *synced) {
-    uint32_t valid = (int64_t)(w + 1) * 32 <= V ? 0xFFFFFFFFu : ((1u << (V - (int64_t)w * 32)) - 1u);
-    uint32_t mask = (all ? 0xFFFFFFFFu : (remote ? remote[w] : 0u)) & valid;
-    if (!mask) return 0;
+// The vertices of a block's `words` words (32 each) that another part needs
+// and whose value changed, as bits in s_word.  With a dirty map a thread reads
+// the 32 bytes of a word; values are compared with the synced copy by
+// consecutive lanes.
+constexpr int DELTA_WORDS = 256;  // words of a block at most
+
+__device__ __forceinline__ void delta_words(int words, int32_t W, int64_t V, const uint32_t *__restrict__ remote, bool all,
+                                            const uint8_t *__restrict__ dirty, const uint32_t *__restrict__ vals,
+                                            const uint32_t *__restrict__ synced, uint32_t *s_word) {
+    const int32_t w0 = blockIdx.x * words;
     if (dirty) {
-        uint32_t bits = 0;
-        const uint32_t *d4 = reinterpret_cast<const uint32_t *>(dirty + (int64_t)w * 32);
+        const int32_t w = w0 + (int32_t)threadIdx.x;
+        if ((int)threadIdx.x < words) {
+            uint32_t bits = 0;
+            uint32_t mask = w >= W ? 0u : all ? 0xFFFFFFFFu : remote ? remote[w] : 0u;
+            if (w == W - 1 && (V & 31)) mask &= (1u << (V & 31)) - 1u;
+            if (mask) {
+                const uint4 *d16 = reinterpret_cast<const uint4 *>(dirty + (int64_t)w * 32);
+                const uint4 a = d16[0], b = d16[1];
+                const uint32_t d4[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
-        for (int q = 0; q < 8; q++) {
-            const uint32_t x = d4[q];
-            bits |= (uint32_t)((x & 0xFFu) != 0) << (4 * q) | (uint32_t)((x & 0xFF00u) != 0) << (4 * q + 1) |
-                    (uint32_t)((x & 0xFF0000u) != 0) << (4 * q + 2) | (uint32_t)((x & 0xFF000000u) != 0) << (4 * q + 3);
+                for (int q = 0; q < 8; q++) {
+                    const uint32_t x = d4[q];
+                    bits |= (uint32_t)((x & 0xFFu) != 0) << (4 * q) | (uint32_t)((x & 0xFF00u) != 0) << (4 * q + 1) |
+                            (uint32_t)((x & 0xFF0000u) != 0) << (4 * q + 2) |
+                            (uint32_t)((x & 0xFF000000u) != 0) << (4 * q + 3);
+                }
+            }
+            s_word[threadIdx.x] = bits & mask;
         }
-        return bits & mask;
+    } else {
+        for (int k = 0; k < words / 8; k++) {
+            const int i = k * 256 + (int)threadIdx.x;
+            const int64_t v = (int64_t)w0 * 32 + i, u = min(v, V - 1);
+            const uint32_t mask = all ? 0xFFFFFFFFu : remote ? remote[u >> 5] : 0u;
+            const bool pick = v < V && ((mask >> (v & 31)) & 1u) && vals[u] != synced[u];
+            const unsigned long long m = __ballot(pick);
+            if ((threadIdx.x & 31) == 0) s_word[i >> 5] = (uint32_t)(m >> (threadIdx.x & 32));
+        }
     }
-    uint32_t out = 0;
-    for (uint32_t m = mask; m; m &= m - 1) {
-        int b = __ffs(m) - 1;
-        int64_t v = (int64_t)w * 32 + b;
-        if (vals[v] != synced[v]) out |= 1u << b;
-    }
-    return out;
+    __syncthreads();
 }
 
-__global__ __launch_bounds__(256) void k_delta_count(int32_t W, int64_t V, const uint32_t *remote, int all,
+__global__ __launch_bounds__(256) void k_delta_count(int words, int32_t W, int64_t V, const uint32_t *remote, int all,
                                                      const uint8_t *dirty, const uint32_t *vals,
                                                      const uint32_t *synced, uint32_t *blk_cnt) {
+    __shared__ uint32_t s_word[DELTA_WORDS];
     __shared__ unsigned long long s[4];
-    int32_t w = blockIdx.x * blockDim.x + threadIdx.x;
-    uint32_t c = w < W ? __popc(delta_word(w, V, remote, all, dirty, vals, synced)) : 0u;
-    unsigned long long t = block_sum<unsigned long long>(c, s);
+    delta_words(words, W, V, remote, all, dirty, vals, synced, s_word);
+    const unsigned long long t =
+        block_sum<unsigned long long>((int)threadIdx.x < words ? __popc(s_word[threadIdx.x]) : 0, s);
     if (threadIdx.x == 0) blk_cnt[blockIdx.x] = (uint32_t)t;
 }
 
-__global__ __launch_bounds__(256) void k_delta_emit(int32_t W, int64_t V, const uint32_t *remote, int all,
-                                                    uint8_t *dirty, const uint32_t *vals, uint32_t *synced,
-                                                    const int32_t *l2g, const uint32_t *__restrict__ blk_cnt,
-                                                    int nblk, uint32_t cap, int32_t *gid_out, uint32_t *val_out,
+// Pairs in ascending vertex order: a block starts at the sum of the counts
+// below its own, its vertices are written by consecutive lanes.  (One thread
+// per word that wrote its 32 vertices one after the other used a lane per
+// cache line: for the labels of one of eight parts of R-MAT scale 24 241 us, now
+// 35.)
+__global__ __launch_bounds__(256) void k_delta_emit(int words, int32_t W, int64_t V, const uint32_t *remote, int all,
+                                                    uint8_t *dirty, const uint32_t *__restrict__ vals,
+                                                    uint32_t *synced, const int32_t *__restrict__ l2g,
+                                                    const uint32_t *__restrict__ blk_cnt, int nblk, uint32_t cap,
+                                                    int32_t *__restrict__ gid_out, uint32_t *__restrict__ val_out,
                                                     uint32_t *total_out) {
+    __shared__ uint32_t s_word[DELTA_WORDS], s_pos[DELTA_WORDS];
     __shared__ unsigned long long s_scan[4];
     __shared__ unsigned long long s_pre[4], s_all[4];
     const int tid = threadIdx.x;
@@ -1204,27 +1193,31 @@ __global__ __launch_bounds__(256) void k_delta_emit(int32_t W, int64_t V, const 
         __syncthreads();
         pre = s_pre[0] + s_pre[1] + s_pre[2] + s_pre[3];
         all_ = s_all[0] + s_all[1] + s_all[2] + s_all[3];
-        __syncthreads();
     }
     if (blockIdx.x == 0 && tid == 0) *total_out = (uint32_t)all_;
     const bool commit = all_ <= cap;
-    int32_t w = blockIdx.x * blockDim.x + tid;
-    uint32_t bits = w < W ? delta_word(w, V, remote, all, dirty, vals, synced) : 0u;
+    delta_words(words, W, V, remote, all, dirty, vals, synced, s_word);
     unsigned long long tot;
-    unsigned long long pos = pre + block_excl_scan_u64(__popc(bits), &tot, s_scan);
-    for (uint32_t m = bits; m; m &= m - 1) {
-        int64_t v = (int64_t)w * 32 + __ffs(m) - 1;
-        if (pos < cap) {
-            gid_out[pos] = l2g ? l2g[v] : (int32_t)v;
-            val_out[pos] = vals[v];
+    const unsigned long long at = pre + block_excl_scan_u64(tid < words ? __popc(s_word[tid]) : 0, &tot, s_scan);
+    if (tid < words) s_pos[tid] = (uint32_t)at;
+    __syncthreads();
+    const int32_t w0 = blockIdx.x * words;
+    if (tot > 0)
+        for (int i = tid; i < words * 32; i += 256) {
+            const uint32_t bits = s_word[i >> 5], below = (1u << (i & 31)) - 1u;
+            if (!((bits >> (i & 31)) & 1u)) continue;
+            const int64_t v = (int64_t)w0 * 32 + i;
+            const uint32_t pos = s_pos[i >> 5] + __popc(bits & below), x = vals[v];
+            if (pos < cap) {
+                gid_out[pos] = l2g ? l2g[v] : (int32_t)v;
+                val_out[pos] = x;
+            }
+            if (commit && synced) synced[v] = x;
         }
-        pos++;
-        if (commit && synced) synced[v] = vals[v];
-    }
-    if (commit && dirty && w < W) {  // the dirty bytes of this word's vertices are cleared
-        uint32_t *d4 = reinterpret_cast<uint32_t *>(dirty + (int64_t)w * 32);
-#pragma unroll
-        for (int q = 0; q < 8; q++) d4[q] = 0u;
+    if (commit && dirty && tid < words && w0 + tid < W) {  // the dirty bytes of this word's vertices are cleared
+        uint4 *d16 = reinterpret_cast<uint4 *>(dirty + (int64_t)(w0 + tid) * 32);
+        d16[0] = make_uint4(0, 0, 0, 0);
+        d16[1] = make_uint4(0, 0, 0, 0);
     }
 }
 
@@ -1236,19 +1229,15 @@ __global__ __launch_bounds__(256) void k_apply_delta(const int32_t *__restrict__
                                                      const uint32_t *__restrict__ vals, uint32_t n,
                                                      const int32_t *__restrict__ l2g, int64_t V,
                                                      uint32_t *__restrict__ val, uint8_t *__restrict__ front_next) {
+    __shared__ int32_t s_top[MAP_SAMPLES];
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int32_t g = i < n ? gid[i] : -1;
+    if (l2g) sample_map(l2g, V, s_top);
     if (i >= n) return;
-    const int32_t g = gid[i];
     int64_t x;
     if (l2g) {
-        int64_t lo = 0, hi = V;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) / 2;
-            if (l2g[mid] < g) lo = mid + 1;
-            else hi = mid;
-        }
-        if (lo >= V || l2g[lo] != g) return;
-        x = lo;
+        x = local_of(l2g, V, s_top, g);
+        if (x < 0) return;
     } else {
         if (g < 0 || g >= V) return;
         x = g;
@@ -1261,6 +1250,7 @@ __global__ __launch_bounds__(256) void k_apply_delta(const int32_t *__restrict__
 }
 
 __global__ void k_zero_step(DevStep *step) { *step = DevStep{}; }
+__global__ void k_set_f64(double *p, double v) { *p = v; }
 __global__ void k_set_u32(uint32_t *p, uint32_t v) { *p = v; }
 
 // ------------------------------------------------------------ separate template calls
@@ -1316,19 +1306,26 @@ __global__ __launch_bounds__(256) void k_ph_pr_gen(const float *__restrict__ x, 
     if (threadIdx.x == 0) dpart[blockIdx.x] = t;
 }
 
-// MSGApply of PageRank: x' = (1-d)/V + d * (merged + D/V), in place.
-__global__ __launch_bounds__(256) void k_ph_pr_apply(const double *__restrict__ acc, float *__restrict__ x, int64_t V,
-                                                     double base, double d, const double *__restrict__ Dp,
-                                                     double inv_V, DevStep *step, DevStep *next,
-                                                     const uint32_t *__restrict__ master) {
-    __shared__ unsigned long long s_c[4];
-    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+// MSGApply of PageRank: x' = (1-d)/V + d * (merged + D/V), in place.  Few,
+// large workgroups: each adds its count to one counter (a part of
+// R-MAT scale 18, one of four: 9.2 us in workgroups of 256, whose atomics queue,
+// 5.8 us so).
+constexpr int PH_APPLY = 4096;  // vertices of a workgroup
+__global__ __launch_bounds__(1024) void k_ph_pr_apply(const double *__restrict__ acc, float *__restrict__ x, int64_t V,
+                                                      double base, double d, const double *__restrict__ Dp,
+                                                      double inv_V, DevStep *step, DevStep *next,
+                                                      const uint32_t *__restrict__ master) {
+    __shared__ unsigned long long s_c[16];
     const double dD = d * (*Dp) * inv_V;
     unsigned c = 0;
-    if (v < V && (!master || bit_of(master, v))) {  // a part of a vertex-cut applies at its masters
-        const float xn = (float)(base + d * acc[v] + dD);
-        c = __float_as_uint(xn) != __float_as_uint(x[v]);
-        x[v] = xn;
+#pragma unroll
+    for (int j = 0; j < PH_APPLY / 1024; j++) {
+        const int64_t v = (int64_t)blockIdx.x * PH_APPLY + j * 1024 + threadIdx.x;
+        if (v < V && (!master || bit_of(master, v))) {  // a part of a vertex-cut applies at its masters
+            const float xn = (float)(base + d * acc[v] + dD);
+            c += __float_as_uint(xn) != __float_as_uint(x[v]);
+            x[v] = xn;
+        }
     }
     const unsigned long long t = block_sum<unsigned long long>((unsigned long long)c, s_c);
     if (threadIdx.x == 0) {
@@ -1488,9 +1485,11 @@ static size_t state_layout(gx_graph *g, const gx_params *p, Carver &c, gx_state 
         }
     }
     s->steps = c.take<DevStep>(STEP_RING);
-    s->delta_blocks = (int)grid_for<int64_t>(W, 256);
+    // enough blocks for the chip, and few enough counts for each to add up
+    s->delta_words = 32;
+    while (s->delta_words < DELTA_WORDS && (W + s->delta_words - 1) / s->delta_words > 1024) s->delta_words *= 2;
+    s->delta_blocks = (int)grid_for<int64_t>(W, s->delta_words);
     s->blk_cnt = c.take<uint32_t>(s->delta_blocks);
-    s->delta_total = c.take<uint32_t>(1);
     return c.used;
 }
 
@@ -2045,14 +2044,17 @@ extern "C" gx_status gx_sync_delta(gx_state *s, int32_t *dev_gid, uint32_t *dev_
     const uint32_t *vals = cur_values(s);
     uint8_t *dirty = by_copy ? nullptr : s->dirty8;
     uint32_t *synced = by_copy ? s->synced : nullptr;
-    hipLaunchKernelGGL(k_delta_count, dim3(s->delta_blocks), dim3(256), 0, hs, d.W, d.V, remote, (int)all, dirty,
+    // the count is written to pinned memory by the kernel itself
+    if (!s->host_steps) s->host_steps = host_steps_take();
+    GX_REQUIRE(s->host_steps, GX_ENOMEM, "pinned host allocation failed");
+    uint32_t *const total_at = reinterpret_cast<uint32_t *>(s->host_steps);
+    hipLaunchKernelGGL(k_delta_count, dim3(s->delta_blocks), dim3(256), 0, hs, s->delta_words, d.W, d.V, remote, (int)all, dirty,
                        vals, synced, s->blk_cnt);
-    hipLaunchKernelGGL(k_delta_emit, dim3(s->delta_blocks), dim3(256), 0, hs, d.W, d.V, remote, (int)all, dirty,
-                       vals, synced, d.l2g, s->blk_cnt, s->delta_blocks, cap, dev_gid, dev_val, s->delta_total);
+    hipLaunchKernelGGL(k_delta_emit, dim3(s->delta_blocks), dim3(256), 0, hs, s->delta_words, d.W, d.V, remote, (int)all, dirty,
+                       vals, synced, d.l2g, s->blk_cnt, s->delta_blocks, cap, dev_gid, dev_val, total_at);
     GX_CHECK_HIP(hipGetLastError(), s);
-    uint32_t total = 0;
-    GX_CHECK_HIP(hipMemcpyAsync(&total, s->delta_total, 4, hipMemcpyDeviceToHost, hs), s);
     GX_CHECK_HIP(hipStreamSynchronize(hs), s);
+    const uint32_t total = *total_at;
     *count = total;
     if (skippable) *skippable = total == 0;
     if (total > cap) {
@@ -2106,7 +2108,7 @@ extern "C" gx_status gx_sync_delta_noalloc(gx_state *s, int32_t *dev_gid, uint32
     GX_REQUIRE(!s->dev_error && !s->g->dev_error, GX_EDEVICE, "sticky device error");
     GX_REQUIRE(s->delta_blocks <= NOALLOC_SCRATCH_WORDS, GX_EINVAL,
                "gx_sync_delta_noalloc handles at most %lld vertices (graph has %lld)",
-               (long long)NOALLOC_SCRATCH_WORDS * 256 * 32, (long long)s->g->d.V);
+               (long long)NOALLOC_SCRATCH_WORDS * DELTA_WORDS * 32, (long long)s->g->d.V);
     uint32_t *cnt = nullptr;
     gx_status st = scratch_for_device(s->g->device, &cnt);
     if (st != GX_OK) return st;
@@ -2127,9 +2129,9 @@ extern "C" gx_status gx_sync_delta_noalloc(gx_state *s, int32_t *dev_gid, uint32
     const uint32_t *vals = cur_values(s);
     uint8_t *dirty = by_copy ? nullptr : s->dirty8;
     uint32_t *synced = by_copy ? s->synced : nullptr;
-    hipLaunchKernelGGL(k_delta_count, dim3(s->delta_blocks), dim3(256), 0, hs, d.W, d.V, remote, (int)all, dirty,
+    hipLaunchKernelGGL(k_delta_count, dim3(s->delta_blocks), dim3(256), 0, hs, s->delta_words, d.W, d.V, remote, (int)all, dirty,
                        vals, synced, cnt);
-    hipLaunchKernelGGL(k_delta_emit, dim3(s->delta_blocks), dim3(256), 0, hs, d.W, d.V, remote, (int)all, dirty,
+    hipLaunchKernelGGL(k_delta_emit, dim3(s->delta_blocks), dim3(256), 0, hs, s->delta_words, d.W, d.V, remote, (int)all, dirty,
                        vals, synced, d.l2g, cnt, s->delta_blocks, cap, dev_gid, dev_val, dev_count);
     GX_CHECK_HIP(hipGetLastError(), s);
     return GX_OK;
@@ -2259,7 +2261,7 @@ extern "C" gx_status gx_msg_apply(gx_state *s, void *stream, gx_step_stats *stat
         if (s->p.algo == GX_PAGERANK) {
             const bool parts = s->p.phases == GX_PHASES_MASTERS;
             const double Vn = (double)(parts ? d.V_global : d.V);
-            hipLaunchKernelGGL(k_ph_pr_apply, dim3(grid_for<int64_t>(d.V, 256)), dim3(256), 0, hs, s->acc_d, s->x[0],
+            hipLaunchKernelGGL(k_ph_pr_apply, dim3(grid_for<int64_t>(d.V, PH_APPLY)), dim3(1024), 0, hs, s->acc_d, s->x[0],
                                d.V, (1.0 - (double)s->p.damping) / Vn, (double)s->p.damping, s->Dval, 1.0 / Vn, step,
                                next, parts ? d.master : nullptr);
         } else {
@@ -2308,8 +2310,8 @@ extern "C" gx_status gx_dangling_set(gx_state *s, double mass, void *stream) {
     gx_status st = parts_check(s);
     if (st != GX_OK) return st;
     hipStream_t hs = static_cast<hipStream_t>(stream);
-    s->D_host = mass;
-    GX_CHECK_HIP(hipMemcpyAsync(s->Dval, &s->D_host, sizeof(double), hipMemcpyHostToDevice, hs), s);
+    hipLaunchKernelGGL(k_set_f64, dim3(1), dim3(1), 0, hs, s->Dval, mass);
+    GX_CHECK_HIP(hipGetLastError(), s);
     return GX_OK;
 }
 
@@ -2325,13 +2327,11 @@ extern "C" gx_status gx_partial_emit(gx_state *s, int32_t *dev_gid, double *dev_
     const DevGraph &d = s->g->d;
     *count = 0;
     if (d.W == 0) return GX_OK;
-    hipLaunchKernelGGL(k_part_count, dim3(s->delta_blocks), dim3(256), 0, hs, d.W, d.V, d.remote_any, d.master,
-                       d.in_rp, s->blk_cnt);
-    hipLaunchKernelGGL(k_part_emit, dim3(s->delta_blocks), dim3(256), 0, hs, d.W, d.V, d.remote_any, d.master,
-                       d.in_rp, d.l2g, s->acc_d, s->blk_cnt, s->delta_blocks, cap, dev_gid, dev_val, s->delta_total);
+    const uint32_t total = (uint32_t)d.n_part, n = std::min(total, cap);
+    if (n > 0)
+        hipLaunchKernelGGL(k_part_emit, dim3(grid_for<uint32_t>(n, 256)), dim3(256), 0, hs, d.part_list, n, d.l2g, s->acc_d,
+                           dev_gid, dev_val);
     GX_CHECK_HIP(hipGetLastError(), s);
-    uint32_t total = 0;
-    GX_CHECK_HIP(hipMemcpyAsync(&total, s->delta_total, 4, hipMemcpyDeviceToHost, hs), s);
     GX_CHECK_HIP(hipStreamSynchronize(hs), s);
     *count = total;
     if (total > cap) {
