@@ -147,14 +147,22 @@ __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ 
     __shared__ int s_nf[CBLOCK / 64];
     __shared__ uint32_t s_min[CBLOCK / 64];
     const int tid = threadIdx.x;
-    if (blockIdx.x == 0 && tid == 0) *next_step = DevStep{};
-    if (blockIdx.x == 0 && prev != nullptr) check_rotations(prev, rot, nrot);
+    // The last workgroup has no vertices: its chain of reads runs beside the
+    // others', which on a small graph are no longer (scale-12 solve: 228 us
+    // with both in the first workgroup and the frontier read after the
+    // counter, 218 us so).
+    if (blockIdx.x == gridDim.x - 1) {
+        if (tid == 0) *next_step = DevStep{};
+        if (prev != nullptr) check_rotations(prev, rot, nrot);
+        return;
+    }
     // The previous superstep had no active vertex: nothing was relaxed, the
     // map read here is still the cleared one and the map cleared here is
     // empty, so A_{k+1} is empty without a sweep (its counters stay zero).
-    if (prev != nullptr && prev->frontier == 0) return;
+    // (A small graph's map is read as fast as the counter.)
+    if (CVT == COMPACT_WIDE && prev != nullptr && prev->frontier == 0) return;
     if (slot != nullptr)  // the bits of the superstep after the one compacted here
-        for (int64_t i = (int64_t)blockIdx.x * CBLOCK + tid; i < PULL_BIT_WORDS; i += (int64_t)gridDim.x * CBLOCK)
+        for (int64_t i = (int64_t)blockIdx.x * CBLOCK + tid; i < PULL_BIT_WORDS; i += (int64_t)(gridDim.x - 1) * CBLOCK)
             hot_clear[i] = 0u;
     const int64_t u0 = ((int64_t)blockIdx.x * CBLOCK + tid) * CVT;
     uint32_t actmask = 0;
@@ -1376,7 +1384,7 @@ static void launch_compact(gx_state *s, hipStream_t hs, const uint8_t *front, ui
     const int64_t k = s->k + ahead;
     const bool wide = d.V >= COMPACT_WIDE_FROM;
     auto kern = wide ? k_compact<COMPACT_WIDE> : k_compact<4>;
-    hipLaunchKernelGGL(kern, dim3(grid_for<int64_t>(d.V, CBLOCK * (wide ? COMPACT_WIDE : 4))), dim3(CBLOCK), 0, hs, front,
+    hipLaunchKernelGGL(kern, dim3(grid_for<int64_t>(d.V, CBLOCK * (wide ? COMPACT_WIDE : 4)) + 1), dim3(CBLOCK), 0, hs, front,
                        clear, s->p.algo == GX_CC ? d.sym_rp : d.out_rp, s->val, s->snap, d.V, s->list, s->tile_start,
                        s->steps + (k % STEP_RING), s->steps + ((k + 1) % STEP_RING),
                        (int)(s->pull_edges != 0xFFFFFFFFu), prev, dirty, s->pull_edges, s->rot, s->relax_grid,
