@@ -63,7 +63,7 @@ struct BpArgs {
     const int32_t *dang;
     const int32_t *in_rp, *outdeg;
     int64_t n_nz, ntiles, E, n_dang;
-    int32_t tile, dtile, ndtiles, n_cross, n_cross_long;
+    int32_t tile, dtile, ndtiles, n_cross, n_cross_long, n_cross_wide;
     uint32_t B;   // lane stride of the tiles
     uint32_t Bw;  // lanes processed (0..Bw-1); the rest keep their values untouched
     float d;

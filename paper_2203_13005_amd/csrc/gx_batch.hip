@@ -636,15 +636,16 @@ __global__ __launch_bounds__(256) void k_bp_pull(BpArgs a, uint32_t k) {
     }
 }
 
-// s plus p[i * stride] over i = 0 .. n-1 in index order; the loads go out 16
+// s plus p[i * stride] over i = 0 .. n-1 in index order; the loads go out AT
 // at a time, the adds stay in order.
+template <int AT>
 __device__ __forceinline__ double ordered_sum(double s, const double *p, int64_t stride, int64_t n) {
-    for (int64_t i0 = 0; i0 < n; i0 += 16) {
-        double v[16];
+    for (int64_t i0 = 0; i0 < n; i0 += AT) {
+        double v[AT];
 #pragma unroll
-        for (int j = 0; j < 16; j++) v[j] = p[std::min<int64_t>(i0 + j, n - 1) * stride];
+        for (int j = 0; j < AT; j++) v[j] = p[std::min<int64_t>(i0 + j, n - 1) * stride];
 #pragma unroll
-        for (int j = 0; j < 16; j++)
+        for (int j = 0; j < AT; j++)
             if (i0 + j < n) s += v[j];
     }
     return s;
@@ -659,7 +660,7 @@ __device__ __forceinline__ double pieces_sum(double s, const double *p, uint32_t
     const uint32_t b = col + (uint32_t)lane;
     const int64_t lo = n * wv / ROWS_PIECES, hi = n * (wv + 1) / ROWS_PIECES;
     __syncthreads();
-    s_p[wv][lane] = b < Bw ? ordered_sum(0.0, p + lo * B + b, B, hi - lo) : 0.0;
+    s_p[wv][lane] = b < Bw ? ordered_sum<16>(0.0, p + lo * B + b, B, hi - lo) : 0.0;
     __syncthreads();
     if (wv == 0)
         for (int i = 0; i < ROWS_PIECES; i++) s += s_p[i][lane];
@@ -667,7 +668,10 @@ __device__ __forceinline__ double pieces_sum(double s, const double *p, uint32_t
 }
 
 // Rows crossing tiles: the first tile's tail and the later tiles' heads in
-// tile order.  One workgroup per long row, a lane group per other row.
+// tile order.  One workgroup per long row, a lane group per other row, with
+// 16 loads in flight for the rows of several tiles (the chain of loads bounds
+// the kernel: 100003 vertices, 1.6 M edges, 5 lanes: 9.1 us with 4
+// for all rows, 7.6 us so).
 constexpr int BP_FIX_BLOCK = 64 * ROWS_PIECES;
 
 template <int W, int LPT>
@@ -700,16 +704,9 @@ __global__ __launch_bounds__(BP_FIX_BLOCK) void k_bp_fix(BpArgs a, uint32_t k) {
             const uint32_t b = b0 + 64u * i;
             acc[i] = 0.0;
             if (b >= a.Bw) continue;
-            double s = a.tailp[(int64_t)q.z * a.B + b];
-            for (int32_t t = q.z + 1; t <= q.w; t += 4) {
-                double v[4];
-#pragma unroll
-                for (int u = 0; u < 4; u++) v[u] = a.head[(int64_t)min(t + u, q.w) * a.B + b];
-#pragma unroll
-                for (int u = 0; u < 4; u++)
-                    if (t + u <= q.w) s += v[u];
-            }
-            acc[i] = s;
+            const double s = a.tailp[(int64_t)q.z * a.B + b];
+            const double *p = a.head + (int64_t)(q.z + 1) * a.B + b;
+            acc[i] = j < a.n_cross_wide ? ordered_sum<16>(s, p, a.B, q.w - q.z) : ordered_sum<ROWS_MID>(s, p, a.B, q.w - q.z);
         }
         ppr_apply<LPT>(a, q.x, q.y, acc, L, c_out, b0);
     }
@@ -832,6 +829,7 @@ BpArgs bp_args_for(const DevGraph &d, const BpWork &w, float *x, uint32_t B, flo
     a.ndtiles = (int32_t)((d.n_dang + a.dtile - 1) / a.dtile);
     a.n_cross = d.bp_rows.n_cross;
     a.n_cross_long = d.bp_rows.n_long;
+    a.n_cross_wide = d.bp_rows.n_long + d.bp_rows.n_mid;
     a.B = B;
     a.Bw = B;
     a.d = damping;
