@@ -942,7 +942,7 @@ def summarize_pmc(fetch_dir, write_dir, solves):
         rows = load(d, counter)
         copy = [float(r["Counter_Value"]) for r in rows if "copy" in r["Kernel_Name"].lower() and
                 float(r["Counter_Value"]) > 500_000]
-        relax = [float(r["Counter_Value"]) for r in rows if "k_relax" in r["Kernel_Name"] or "k_fixup" in r["Kernel_Name"]]
+        relax = [float(r["Counter_Value"]) for r in rows if "k_relax" in r["Kernel_Name"]]
         if not copy or not relax:
             raise SystemExit(f"{counter}: no calibration copy or no relaxation dispatches in {d}")
         factor = (1 << 30) / 1024.0 / max(copy)  # KiB of a 1 GiB copy / measured
@@ -1093,7 +1093,7 @@ def bench_sssp(args, gx, torch, np, gen):
             "ms_per_solve_mean": float(np.mean(src_ms)), "ms_per_solve_min": min(src_ms),
             "ms_per_solve_max": max(src_ms), "gteps": src_msgs / (sum(src_ms) / 1e3) / 1e9,
             "supersteps": src_steps},
-        "load": {"what": "gx_graph_load: host validation and packaging (out-CSR, in-edge records), "
+        "load": {"what": "gx_graph_load: host validation and packaging (out-CSR, rows of in-edges), "
                          "16 MiB blocks through three rotating pinned buffers on a copy stream",
                  "seconds": load_s, "device_bytes": load_bytes, "GBps": load_bytes / load_s / 1e9,
                  "host_link_GBps": link_gbps,
@@ -1101,7 +1101,7 @@ def bench_sssp(args, gx, torch, np, gen):
                           f"{load_bytes / link_gbps / 1e9 * 1e3:.0f} ms of the {load_s * 1e3:.0f} ms at the link's rate)"},
         "roofline": {
             "bound": "hbm",
-            "kernel": "relaxation: k_relax<true> (push or pull as the frontier decides) + k_fixup, per superstep",
+            "kernel": "relaxation: k_relax<true> (push or pull as the frontier decides), per superstep",
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",

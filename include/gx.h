@@ -66,7 +66,7 @@ typedef enum {
 } gx_algo;
 
 /* Which device images gx_graph_load builds (bitmask). */
-#define GX_NEED_OUT 1u  /* out-CSR (dst, weight) + in-edge records (dst, src, weight): SSSP push and pull */
+#define GX_NEED_OUT 1u  /* out-CSR (dst, weight) + rows of in-edges (source, weight): SSSP push and pull */
 #define GX_NEED_IN  2u  /* in-CSR (sources ascending) + out-degree: PageRank, PPR */
 #define GX_NEED_SYM 4u  /* symmetric deduplicated adjacency: CC */
 
@@ -117,7 +117,7 @@ typedef struct gx_params {
     uint32_t delta_mode;      /* GX_DELTA_REMOTE or GX_DELTA_ALL */
     uint32_t timing;          /* nonzero: time the edge kernels of every superstep with HIP events */
     float    pull_fraction;   /* SSSP/CC: a superstep whose active out-edges exceed this fraction of
-                                 all edges pulls (one sweep over every in-edge record) instead of
+                                 all edges pulls (over the rows of in-edges) instead of
                                  pushing; 0 = default (0.3), >= 1 = always push */
     uint32_t phases;          /* GX_PHASES_LOCAL or GX_PHASES_MASTERS (PageRank, SSSP, CC): the state
                                  is driven by the separate template calls gx_msg_gen / gx_msg_merge /
@@ -135,7 +135,7 @@ typedef struct gx_step_stats {
     int64_t frontier;      /* |F_k|: active vertices (PageRank: V) */
     int64_t edges;         /* messages generated: out-edges of F_k (PageRank: E) */
     int64_t changed;       /* vertices whose value changed (|F_{k+1}| for SSSP/CC) */
-    int64_t pulled;        /* 1 if the superstep ran as a pull over all in-edge records */
+    int64_t pulled;        /* 1 if the superstep ran as a pull over the rows of in-edges */
     double  kernel_ms;     /* with gx_params.timing: HIP-event time of its edge kernels, else 0 */
 } gx_step_stats;
 
@@ -207,7 +207,7 @@ gx_status gx_release_cached(void);
  * requestGen() -> requestMerge() -> requestApply() in BSP order: one
  * superstep.  SSSP/CC: relax the active list (built with start-of-superstep
  * snapshots by the previous call or by gx_state_init) over equal tiles of
- * active out-edges (push) or as one sweep over all in-edge records (pull,
+ * active out-edges (push) or over the rows of in-edges (pull,
  * for large frontiers; the device picks), merge by integer min, mark
  * changed vertices in the next frontier and the dirty map, then compact the
  * next frontier.  PageRank: pull over the

@@ -407,8 +407,8 @@ static void build_segs(const std::vector<int32_t> &rp, std::vector<uint4> &segs)
     }
 }
 
-// A row of the SSSP pull by ascending weight, weights of at most 8 bits: counted over the 256 weights (rows here are longer than
-// PULL_SMALL).
+// A row of the SSSP pull by ascending weight, weights of at most 8 bits:
+// counted over the 256 weights (rows here are longer than PULL_SMALL).
 static void row_by_weight(const int32_t *src, const int32_t *slot, const uint32_t *w, int32_t n, uint32_t tag,
                           uint2 *out) {
     int32_t at[257] = {};

@@ -98,12 +98,12 @@ constexpr int PULL_BIT_WORDS = PULL_BITS / 32;
 inline int64_t pull_seg_cap(int64_t E) { return E / PULL_SMALL + 1; }
 inline int64_t pull_pack_cap(int64_t V, int64_t E) { return std::min(E, E / PULL_PACK + (V + 63) / 64) + 1; }
 
-// Row ends of the in-CSR (PageRank, batched PPR): rows without in-edges are left out,
-// a bit per in-edge marks the last one of its row.  The in-edges are cut into
+// Row ends of the in-CSR (PageRank, batched PPR): rows without in-edges are
+// left out, a bit per in-edge marks the last one of its row.  The in-edges are cut into
 // tiles, rows that cross tiles are listed.
 constexpr int ROWS_PIECES = 16;     // a sum of at least ROWS_LONG partials is cut into this many pieces
 constexpr int ROWS_LONG = 64;
-constexpr int ROWS_MID = 4;         // (PageRank: summed by sixteen lanes)
+constexpr int ROWS_MID = 4;         // (a single step of loads covers fewer)
 struct RowTiles {
     int64_t T = 0, n = 0;              // in-edges per tile, tiles
     const int32_t *tile_nz = nullptr;  // per tile: position in nz of the row its first edge belongs to
@@ -120,8 +120,8 @@ constexpr int ROWS_DANGLING = 512;  // tiles of dangling vertices at most
 
 // Label propagation: vertices are grouped by the number of distinct
 // neighbours d.  Classes 0..4 take d <= 4, 8, 16, 32, 64 and run as lane
-// groups of that width; class 5 (d <= LP_MID_MAX) runs one workgroup per
-// vertex with a hash table of labels in LDS; class 6 (hubs) counts in hash
+// groups of that width; class 5 (d <= LP_MID_MAX) runs one wave or workgroup
+// per vertex with a hash table of labels in LDS; class 6 (hubs) counts in hash
 // tables in device memory, cut into chunks of LP_HUB_CHUNK neighbours.
 constexpr int LP_CLASSES = 7;
 constexpr int LP_MID_MAX = 2048;
@@ -135,8 +135,7 @@ struct DevGraph {
     // out-CSR (SSSP push): row_ptr + interleaved (dst, weight)
     const int32_t *out_rp = nullptr;
     const uint2 *out_adj = nullptr;
-    // in-CSR: sources only (PageRank pull) and interleaved (source, weight)
-    // (SSSP pull); out-degree; equal in-edge tiles shared by both pulls
+    // in-CSR and out-degree; its row ends and tiles (PageRank, batched PPR)
     const int32_t *in_rp = nullptr;
     const int32_t *in_col = nullptr;
     const int32_t *outdeg = nullptr;
@@ -159,10 +158,9 @@ struct DevGraph {
     // in-edges of the SSSP pull, {source slot, (destination mod 64) << 8 | weight}:
     // the entries of the rows of at most PULL_SMALL, in row order (block b of
     // 64 rows owns in_blk[b] .. in_blk[b + 1]), then the longer rows, each by
-    // ascending weight; null when a weight exceeds 255 (the engine
-    // then only pushes).  pull_segs: {row, first entry, end entry, first
-    // weight, bit 8: the row's only one} of the
-    // long rows.
+    // ascending weight; null when a weight exceeds 255 (the engine then only
+    // pushes).  pull_segs: {row, first entry, end entry, first weight, bit 8:
+    // the row's only one} of the long rows.
     const uint2 *in_adj = nullptr;
     const int32_t *in_blk = nullptr;
     const uint4 *pull_segs = nullptr;
