@@ -55,8 +55,9 @@ struct BsVariant {
 };
 
 struct BpArgs {
-    const int32_t *in_col;
+    const int32_t *src;  // slot of every in-edge's source
     const int2 *nz;
+    const int32_t *nz_slot, *slot;
     const uint64_t *row_last;
     const int32_t *tile_nz;
     const int4 *cross;
@@ -71,7 +72,7 @@ struct BpArgs {
     const int32_t *end;   // per lane: first superstep it no longer runs (NULL: every lane's is `last`)
     uint32_t last;
     float *x;             // ranks, written in a lane's last superstep
-    float *c[2];          // contributions x / out-degree (x itself where that is 0), c[k & 1] read by superstep k
+    float *c[2];          // contributions x / out-degree (x itself where that is 0) by slot, c[k & 1] read by superstep k
     double *head, *tailp, *dpart, *seed_acc;
 };
 

@@ -514,14 +514,14 @@ struct PprLanes {
 // A finished row sum: the contribution, the rank if it is the lane's last,
 // and the sum itself where the seed kernel goes on with it.
 template <int LPT>
-__device__ __forceinline__ void ppr_apply(const BpArgs &a, int32_t r, int od, const double (&acc)[LPT],
+__device__ __forceinline__ void ppr_apply(const BpArgs &a, int32_t r, int32_t sl, int od, const double (&acc)[LPT],
                                           const PprLanes<LPT> &L, float *__restrict__ c_out, uint32_t b0) {
 #pragma unroll
     for (int i = 0; i < LPT; i++) {
         if (!L.live[i]) continue;
         const uint32_t b = b0 + 64u * i;
         const float xn = (float)((double)a.d * acc[i]);
-        c_out[(size_t)r * a.B + b] = od > 0 ? xn / (float)od : xn;
+        c_out[(size_t)(uint32_t)sl * a.B + b] = od > 0 ? xn / (float)od : xn;
         if (L.last[i]) a.x[(size_t)r * a.B + b] = xn;
         if (L.seed[i] == r) a.seed_acc[b] = acc[i];
     }
@@ -540,14 +540,17 @@ __device__ __forceinline__ void ppr_apply(const BpArgs &a, int32_t r, int od, co
 // edges, 4.1 GB gathered per superstep): one wave per 256-edge tile that
 // also closed every empty row, walked the 16 loaded rows once per ending row
 // and wrote ranks every superstep took 2360 us (2500 us with the other three
-// launches); this one takes 675 us (722 us with the other two), 6.1 TB/s of
-// gathered rows.
+// launches); this one takes 520 us (555 us with the other two), 7.9 TB/s of
+// gathered rows.  Contributions are stored by slot: by vertex number the hubs
+// of R-MAT (numbers with few bits set) lay power-of-two strides apart and the
+// superstep took 680 us, and with 256 lanes 3.05 ms where it takes 2.16 now.
 __device__ __forceinline__ double *bp_partial(double *p, int64_t t, uint32_t B, uint32_t b) { return p + t * B + b; }
 
 template <int W, int LPT>
 __global__ __launch_bounds__(256) void k_bp_pull(BpArgs a, uint32_t k) {
     constexpr int NG = 64 / W, EB = 16;
     __shared__ int2 s_nz[4][NG][64];
+    __shared__ int32_t s_sl[4][NG][64];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane / W;
     const uint32_t b0 = (uint32_t)(lane % W);
     const float *__restrict__ c_in = a.c[k & 1];
@@ -564,7 +567,7 @@ __global__ __launch_bounds__(256) void k_bp_pull(BpArgs a, uint32_t k) {
         const int tile = dng ? a.dtile : a.tile;
         const int64_t e0 = t * tile;
         const int n = (int)min((int64_t)tile, (dng ? a.n_dang : a.E) - e0);
-        const int32_t *__restrict__ ids = (dng ? a.dang : a.in_col) + e0;
+        const int32_t *__restrict__ ids = (dng ? a.dang : a.src) + e0;
         int32_t ord = dng ? 0 : a.tile_nz[t];
         bool head = !dng && e0 > 0 && !((a.row_last[(e0 - 1) >> 6] >> ((e0 - 1) & 63)) & 1ull);
         bool open = true;  // the sum in acc has not been written
@@ -578,7 +581,10 @@ __global__ __launch_bounds__(256) void k_bp_pull(BpArgs a, uint32_t k) {
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
             for (int q = 0; q < 64; q += W)
-                if (q + (int)b0 < ends) s_nz[wv][g][q + b0] = a.nz[ord + q + (int)b0];
+                if (q + (int)b0 < ends) {
+                    s_nz[wv][g][q + b0] = a.nz[ord + q + (int)b0];
+                    s_sl[wv][g][q + b0] = a.nz_slot[ord + q + (int)b0];
+                }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
             int idx = 0;
@@ -609,7 +615,8 @@ __global__ __launch_bounds__(256) void k_bp_pull(BpArgs a, uint32_t k) {
 #pragma unroll
                     for (int i = 0; i < LPT; i++) acc[i] += add ? (double)v[j][i] : 0.0;
                     if ((mm >> j) & 1u) {  // the row ends with this edge
-                        const int2 rw = s_nz[wv][g][idx++];
+                        const int2 rw = s_nz[wv][g][idx];
+                        const int32_t sl = s_sl[wv][g][idx++];
                         if (head) {
                             head = false;
                             if (on)
@@ -617,7 +624,7 @@ __global__ __launch_bounds__(256) void k_bp_pull(BpArgs a, uint32_t k) {
                                 for (int i = 0; i < LPT; i++)
                                     if (b0 + 64u * i < a.Bw) *bp_partial(a.head, t, a.B, b0 + 64u * i) = acc[i];
                         } else if (on) {
-                            ppr_apply<LPT>(a, rw.x, rw.y, acc, L, c_out, b0);
+                            ppr_apply<LPT>(a, rw.x, sl, rw.y, acc, L, c_out, b0);
                         }
 #pragma unroll
                         for (int i = 0; i < LPT; i++) acc[i] = 0.0;
@@ -681,6 +688,7 @@ __global__ __launch_bounds__(BP_FIX_BLOCK) void k_bp_fix(BpArgs a, uint32_t k) {
     float *c_out = a.c[(k + 1) & 1];
     if ((int)blockIdx.x < a.n_cross_long) {
         const int4 q = a.cross[blockIdx.x];
+        const int32_t sl = a.slot[q.x];
         const PprLanes<LPT> L(a, k, (uint32_t)lane);
         double acc[LPT];
 #pragma unroll
@@ -689,7 +697,7 @@ __global__ __launch_bounds__(BP_FIX_BLOCK) void k_bp_fix(BpArgs a, uint32_t k) {
             const double s = b < a.Bw ? a.tailp[(int64_t)q.z * a.B + b] : 0.0;
             acc[i] = pieces_sum(s, a.head + (int64_t)(q.z + 1) * a.B, a.B, 64u * i, a.Bw, q.w - q.z, s_p);
         }
-        if (threadIdx.x < 64) ppr_apply<LPT>(a, q.x, q.y, acc, L, c_out, (uint32_t)lane);
+        if (threadIdx.x < 64) ppr_apply<LPT>(a, q.x, sl, q.y, acc, L, c_out, (uint32_t)lane);
         return;
     }
     const uint32_t b0 = (uint32_t)(lane % W);
@@ -698,6 +706,7 @@ __global__ __launch_bounds__(BP_FIX_BLOCK) void k_bp_fix(BpArgs a, uint32_t k) {
     for (int64_t j = a.n_cross_long + (int64_t)(blockIdx.x - a.n_cross_long) * groups + threadIdx.x / W; j < a.n_cross;
          j += (int64_t)(gridDim.x - a.n_cross_long) * groups) {
         const int4 q = a.cross[j];
+        const int32_t sl = a.slot[q.x];
         double acc[LPT];
 #pragma unroll
         for (int i = 0; i < LPT; i++) {
@@ -708,7 +717,7 @@ __global__ __launch_bounds__(BP_FIX_BLOCK) void k_bp_fix(BpArgs a, uint32_t k) {
             const double *p = a.head + (int64_t)(q.z + 1) * a.B + b;
             acc[i] = j < a.n_cross_wide ? ordered_sum<16>(s, p, a.B, q.w - q.z) : ordered_sum<ROWS_MID>(s, p, a.B, q.w - q.z);
         }
-        ppr_apply<LPT>(a, q.x, q.y, acc, L, c_out, b0);
+        ppr_apply<LPT>(a, q.x, sl, q.y, acc, L, c_out, b0);
     }
 }
 
@@ -722,29 +731,30 @@ __global__ __launch_bounds__(BP_FIX_BLOCK) void k_bp_seed(BpArgs a, uint32_t k) 
     const uint32_t end = a.end ? (uint32_t)a.end[b] : a.last;
     if (r < 0 || (int32_t)(end - k) <= 0) return;
     const int od = a.outdeg[r];
-    const size_t at = (size_t)r * a.B + b;
+    const size_t at = (size_t)r * a.B + b, at_c = (size_t)(uint32_t)a.slot[r] * a.B + b;
     const bool no_in = a.in_rp[r + 1] == a.in_rp[r];
-    if (od == 0 && no_in) D += (double)a.c[k & 1][at];  // a seed that no list of dangling vertices holds
+    if (od == 0 && no_in) D += (double)a.c[k & 1][at_c];  // a seed that no list of dangling vertices holds
     const double v = (double)a.d * (no_in ? 0.0 : a.seed_acc[b]) + ((1.0 - (double)a.d) + (double)a.d * D);
     const float xn = (float)v;
-    a.c[(k + 1) & 1][at] = od > 0 ? xn / (float)od : xn;
+    a.c[(k + 1) & 1][at_c] = od > 0 ? xn / (float)od : xn;
     if (end == k + 1) a.x[at] = xn;
 }
 
 // Superstep 0: ranks e_seed (in the contributions; in x too if there are no
 // supersteps), 0 in every row no superstep writes.
 __global__ __launch_bounds__(256) void k_bp_init(float *x, float *c0, float *c1, const int32_t *seed,
-                                                 const int32_t *in_rp, const int32_t *outdeg, int64_t V, uint32_t B,
-                                                 uint32_t iters) {
+                                                 const int32_t *in_rp, const int32_t *outdeg, const int32_t *slot,
+                                                 int64_t V, uint32_t B, uint32_t iters) {
     const size_t n = (size_t)V * B;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
         const int64_t v = (int64_t)(i / B);
         const uint32_t b = (uint32_t)(i % B);
         const bool here = seed[b] == v;
         const int od = outdeg[v];
-        c0[i] = !here ? 0.0f : od > 0 ? 1.0f / (float)od : 1.0f;
+        const size_t at = (size_t)(uint32_t)slot[v] * B + b;
+        c0[at] = !here ? 0.0f : od > 0 ? 1.0f / (float)od : 1.0f;
         if (iters == 0 || in_rp[v + 1] == in_rp[v]) {
-            c1[i] = 0.0f;
+            c1[at] = 0.0f;
             x[i] = here && iters == 0 ? 1.0f : 0.0f;
         }
     }
@@ -754,15 +764,15 @@ __global__ __launch_bounds__(256) void k_bp_init(float *x, float *c0, float *c1,
 // this lane's old values: rows with in-edges are rewritten before they are
 // read, so only the old seed's (perhaps without in-edges) are cleared.
 __global__ __launch_bounds__(256) void k_bp_lane_reset(float *x, float *c, float *c_other, double *seed_acc,
-                                                       const int32_t *outdeg, int64_t V, uint32_t B, uint32_t lane,
-                                                       int32_t seed, int32_t old) {
+                                                       const int32_t *outdeg, const int32_t *slot, int64_t V,
+                                                       uint32_t B, uint32_t lane, int32_t seed, int32_t old) {
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < V; v += (int64_t)gridDim.x * blockDim.x) {
         const int od = outdeg[v];
-        c[(size_t)v * B + lane] = v != seed ? 0.0f : od > 0 ? 1.0f / (float)od : 1.0f;
+        c[(size_t)(uint32_t)slot[v] * B + lane] = v != seed ? 0.0f : od > 0 ? 1.0f / (float)od : 1.0f;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         seed_acc[lane] = 0.0;
-        if (old >= 0) c_other[(size_t)old * B + lane] = x[(size_t)old * B + lane] = 0.0f;
+        if (old >= 0) c_other[(size_t)(uint32_t)slot[old] * B + lane] = x[(size_t)old * B + lane] = 0.0f;
     }
 }
 
@@ -811,8 +821,10 @@ void bp_layout(const DevGraph &d, uint32_t B, Carver &c, BpWork *w) {
 
 BpArgs bp_args_for(const DevGraph &d, const BpWork &w, float *x, uint32_t B, float damping) {
     BpArgs a{};
-    a.in_col = d.in_col;
+    a.src = d.pr_src;
     a.nz = d.nz;
+    a.nz_slot = d.nz_slot;
+    a.slot = d.slot;
     a.row_last = d.row_last;
     a.tile_nz = d.bp_rows.tile_nz;
     a.cross = d.bp_rows.cross;
@@ -960,7 +972,7 @@ gx_status run_bppr(gx_graph *g, const int32_t *dev_seed, uint32_t B, BpWork &w, 
         GX_CHECK_HIP(hipMemcpyAsync(w.seed, dev_seed, B * 4, hipMemcpyDeviceToDevice, s), g);
     const size_t n = (size_t)d.V * B;
     hipLaunchKernelGGL(k_bp_init, dim3((unsigned)std::min<size_t>(8192, (n + 255) / 256 + 1)), dim3(256), 0, s, out,
-                       w.c[0], w.c[1], w.seed, d.in_rp, d.outdeg, d.V, B, iters);
+                       w.c[0], w.c[1], w.seed, d.in_rp, d.outdeg, d.slot, d.V, B, iters);
     BpArgs a = bp_args_for(d, w, out, B, d_);
     a.last = iters;
     // ordinary launches (measured faster than one persistent kernel with grid
@@ -1046,7 +1058,7 @@ hipError_t bs_lane_reset(const BsArgs &a, uint32_t k, uint32_t lane, int32_t src
 hipError_t bp_lane_reset(const BpArgs &a, uint32_t k, int64_t V, uint32_t lane, int32_t seed, int32_t old, hipStream_t s) {
     unsigned nb = (unsigned)std::min<int64_t>(2048, (V + 255) / 256 + 1);
     hipLaunchKernelGGL(k_bp_lane_reset, dim3(nb), dim3(256), 0, s, a.x, a.c[k & 1], a.c[(k + 1) & 1], a.seed_acc, a.outdeg,
-                       V, a.B, lane, seed, old);
+                       a.slot, V, a.B, lane, seed, old);
     return hipGetLastError();
 }
 

@@ -363,7 +363,7 @@ static void build_rows(const gx_graph_desc *d, HostImages &h) {
         h.nz.push_back(make_int2((int32_t)v, od));
         h.nz_slot.push_back(h.slot[v]);
         h.row_last[(b - 1) >> 6] |= uint64_t(1) << ((b - 1) & 63);
-        if (od == 0) h.dang.push_back((int32_t)v);
+        if (od == 0) h.dang.push_back(h.slot[v]);
     }
 }
 
@@ -551,7 +551,6 @@ static void layout(const gx_graph_desc *desc, int64_t E_sym, Carver &c, DevGraph
         d->pr_tile = pr_tile_for(desc);
     }
     if (desc->needs & GX_NEED_IN) {
-        d->in_col = c.take<int32_t>(E + 64);  // (read in whole groups of 16)
         d->nz = c.take<int2>(std::min(V, E));
         d->row_last = c.take<uint64_t>((E + PR_TILE_MAX) / 64 + 1);  // (whole tiles)
         // (byte offsets of the other slots are 32 bits)
@@ -786,9 +785,8 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
     if (e == hipSuccess && d.in_rp) {
         e = up.put_array((void *)d.in_rp, h.in_rp.data(), (V + 1) * 4);
     }
-    if (e == hipSuccess && d.in_col) {
-        e = up.put_array((void *)d.in_col, h.in_col.data(), E * 4);
-        if (e == hipSuccess) e = up.put_array((void *)d.outdeg, g->host_outdeg.data(), V * 4);
+    if (e == hipSuccess && d.pr_src) {
+        e = up.put_array((void *)d.outdeg, g->host_outdeg.data(), V * 4);
         if (e == hipSuccess) e = up.put_array((void *)d.nz, h.nz.data(), h.nz.size() * sizeof(int2));
         if (e == hipSuccess) e = up.put_array((void *)d.nz_slot, h.nz_slot.data(), h.nz_slot.size() * 4);
         if (e == hipSuccess) e = up.put_array((void *)d.ez, h.ez.data(), h.ez.size() * sizeof(int2));

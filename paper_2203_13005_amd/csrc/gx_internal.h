@@ -62,8 +62,8 @@ struct Carver {
 // Edge tile of the PageRank pull (in-edges per workgroup tile): PR_BLOCK
 // threads times 1, 2, 4 or 8 edges, chosen per graph at load.
 constexpr int PR_BLOCK = 256;
-// What is gathered per in-edge from its source (PageRank contributions, SSSP
-// values) lives in slots: the HOT_SLOTS vertices with the most out-edges
+// What is gathered per in-edge from its source (contributions, SSSP values)
+// lives in slots: the HOT_SLOTS vertices with the most out-edges
 // first, 2 MiB of 4-byte values that an L2 keeps while the in-edges stream
 // past (on R-MAT graphs they are the sources of 70 to 93% of the in-edges).
 constexpr int64_t HOT_SLOTS = int64_t(1) << 19;
@@ -114,7 +114,7 @@ struct RowTiles {
 // Batched PPR, a lane group's tile: a graph of few edges has too few longer
 // ones to occupy the chip (100003 vertices, 1.6 M edges, 5 lanes: 1.7 ms with
 // 64, 2.2 with 128, 2.8 with 256); a large one saves partials (scale 20,
-// 64 lanes: 37.6, 35.8 and 34.0 ms).
+// 64 lanes: 37.6, 35.8 and 34.0 ms, contributions by vertex then).
 inline int64_t bp_rows_tile(int64_t E) { return E >= (int64_t(1) << 22) ? 256 : 64; }
 constexpr int ROWS_DANGLING = 512;  // tiles of dangling vertices at most
 
@@ -137,7 +137,6 @@ struct DevGraph {
     const uint2 *out_adj = nullptr;
     // in-CSR and out-degree; its row ends and tiles (PageRank, batched PPR)
     const int32_t *in_rp = nullptr;
-    const int32_t *in_col = nullptr;
     const int32_t *outdeg = nullptr;
     // slot[v]: where vertex v's gathered values live, the HOT_SLOTS vertices
     // with the most out-edges first (by out-degree, then id), every other
@@ -151,7 +150,7 @@ struct DevGraph {
     int64_t n_ez = 0;
     const uint64_t *row_last = nullptr;  // bit e: in-edge e is its row's last
     RowTiles pr_rows, bp_rows;         // of PageRank's tiles and of the batched PPR's
-    const int32_t *dang = nullptr;     // vertices with in-edges and without out-edges
+    const int32_t *dang = nullptr;     // slots of the vertices with in-edges and without out-edges
     int64_t n_dang = 0;
     int32_t pr_tile = PR_TILE_MAX;  // in-edges per PageRank workgroup tile (PR_BLOCK / 64 wave tiles)
     bool pr_hot = false;            // the PageRank pull keeps the first PR_LDS_SLOTS contributions in LDS
