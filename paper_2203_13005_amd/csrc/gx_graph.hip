@@ -175,6 +175,7 @@ struct HostImages {
     EdgeVec<uint2> in_adj;
     std::vector<int32_t> sym_rp;
     EdgeVec<int32_t> sym_col;
+    bool sym_ascending = true;
     std::vector<int32_t> in_blk;
     std::vector<uint4> pull_segs, sym_segs, packs;
     std::vector<uint32_t> rem_out, rem_any, master, master_rep;
@@ -511,9 +512,19 @@ static void build_sym(const gx_graph_desc *d, HostImages &h) {
     });
     for (int64_t v = 0; v < V; v++) h.sym_rp[v + 1] += h.sym_rp[v];
     h.sym_col.resize(h.sym_rp[V]);
+    // Out-rows that the caller did not sort leave rows that do not ascend and
+    // may hold a neighbour twice: no one neighbour then stands for a row.
+    std::atomic<bool> ascending{true};
     parallel_for(V, [&](int64_t lo, int64_t hi) {
-        for (int64_t u = lo; u < hi; u++) merge_row(u, h.sym_col.data() + h.sym_rp[u]);
+        bool up = true;
+        for (int64_t u = lo; u < hi; u++) {
+            int32_t *row = h.sym_col.data() + h.sym_rp[u];
+            const int32_t n = merge_row(u, row);
+            for (int32_t i = 1; i < n; i++) up &= row[i - 1] < row[i];
+        }
+        if (!up) ascending = false;
     });
+    h.sym_ascending = ascending;
 }
 
 static void build_flags(const gx_graph_desc *d, int32_t W, HostImages &h) {
@@ -752,6 +763,7 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
     g->d.n_dang = (int64_t)h.dang.size();
     g->d.n_packs = (int64_t)h.packs.size();
     g->d.sym_nsegs = (int64_t)h.sym_segs.size();
+    g->d.sym_ascending = h.sym_ascending;
     g->needs = desc->needs;
     g->arena = dev_arena;
     g->arena_bytes = arena_bytes;

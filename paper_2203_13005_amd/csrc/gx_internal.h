@@ -168,10 +168,11 @@ struct DevGraph {
     // end entry, first row of the block, 0}
     const uint4 *packs = nullptr;
     int64_t n_packs = 0;
-    // symmetric adjacency (CC push and pull, neighbours ascending) and the
+    // symmetric adjacency (CC push and pull, label propagation) and the
     // segments of its long rows
     const int32_t *sym_rp = nullptr;
     const int32_t *sym_col = nullptr;
+    bool sym_ascending = true;  // every row's neighbours ascend (rows of the host CSR that do not are merged as they are)
     const uint4 *sym_segs = nullptr;
     int64_t sym_nsegs = 0;
     // partition metadata

@@ -25,8 +25,9 @@
 // Counts are exact integers and the winner is the unique maximum of
 // (count, ~label), so the result does not depend on the order of the atomics.
 //
-// Superstep 0 needs no counting: the labels are the (distinct) global ids, so
-// every count is 1 and the winner is the first neighbour's.  After that only
+// Superstep 0 needs no counting where every row's neighbours ascend: the
+// labels are the (distinct) global ids, so every count is 1 and the winner is
+// the first neighbour's (other rows are counted).  After that only
 // the vertices with a neighbour whose label changed can change: when the
 // changed vertices' edges are a small part of all (LP_DENSE), their
 // neighbours are marked and only the marked are recomputed; a vertex that
@@ -71,7 +72,10 @@ struct LpStep {
     DevStep *step;
     const DevStep *prev;
     int64_t E_sym;
-    __device__ __forceinline__ bool full() const { return (int64_t)(uint32_t)prev->list * LP_DENSE > E_sym; }
+    bool first;  // superstep 0: there is no superstep before it
+    __device__ __forceinline__ bool full() const {
+        return first || (int64_t)(uint32_t)prev->list * LP_DENSE > E_sym;
+    }
 };
 
 // The changed vertices of a workgroup, kept in LDS so that each workgroup
@@ -157,8 +161,8 @@ __global__ __launch_bounds__(LP_BLOCK) void k_lp_mark(LpStep a, DevStep *next, u
         *next = DevStep{};
         *log_n = 0;
     }
-    const unsigned long long le = a.prev->list;
     if (a.full()) return;
+    const unsigned long long le = a.prev->list;
     const uint32_t n = (uint32_t)(le >> 32), gl = threadIdx.x & 15;
     for (uint32_t i = (blockIdx.x * LP_BLOCK + threadIdx.x) / 16; i < n; i += gridDim.x * (LP_BLOCK / 16)) {
         const uint2 q = a.changed[i];
@@ -718,8 +722,9 @@ void lp_enqueue(gx_state *s, hipStream_t hs, DevStep *step, DevStep *next) {
     const int cur = (int)(s->k & 1);
     const int64_t *off = s->lp_off;
     const DevStep *prev = s->steps + ((s->k + STEP_RING - 1) % STEP_RING);
-    const LpStep a{d.sym_rp, d.sym_col, s->lab[cur], s->lab[cur ^ 1], s->lp_touch, s->lp_changed, step, prev, d.E_sym};
-    if (s->k == 0) {
+    const LpStep a{d.sym_rp,     d.sym_col,     s->lab[cur], s->lab[cur ^ 1], s->lp_touch,
+                   s->lp_changed, step,          prev,        d.E_sym,         s->k == 0};
+    if (s->k == 0 && d.sym_ascending) {
         hipLaunchKernelGGL(k_lp_first, dim3(blocks_for<int64_t>(d.V, LP_BLOCK)), dim3(LP_BLOCK), 0, hs, a, d.V, next);
         return;
     }

@@ -1366,12 +1366,13 @@ static int relax_grid_for(gx_graph *g, const gx_params *p) {
 
 // What the pull of `s` reads; `bound`: the vertex values.  CC labels ascend
 // with the neighbour ids until the first superstep ran or another part's
-// labels were merged, so that superstep reads one neighbour per vertex.
+// labels were merged, so that superstep reads one neighbour per vertex (if
+// the neighbours of every row ascend).
 static PullArgs pull_args(const gx_state *s) {
     const DevGraph &d = s->g->d;
     if (s->p.algo == GX_CC)
-        return {d.sym_rp, d.sym_col, d.sym_segs, d.sym_nsegs, s->k == 0 && !s->merged, s->acc != nullptr, s->val,
-                nullptr};
+        return {d.sym_rp, d.sym_col, d.sym_segs, d.sym_nsegs, s->k == 0 && !s->merged && d.sym_ascending,
+                s->acc != nullptr, s->val, nullptr};
     return {d.in_blk, d.in_adj, d.pull_segs, d.pull_nsegs, 0, s->acc != nullptr, s->val, s->hot[s->k & 1]};
 }
 
