@@ -459,7 +459,8 @@ gx_status gx_balance_split(const double *c, int32_t m, double D, double *d_out);
 typedef struct gx_tune {
     uint32_t block;   /* threads per workgroup (64..1024, multiple of 64); 0 = default */
     uint32_t tile;    /* edges per work tile; 0 = default */
-    uint32_t width;   /* lanes per pass (32, 64, 128 or 256, <= B); 0 = default */
+    uint32_t width;   /* lanes per pass (32, 64, 128 or 256, <= B); 0 = default.  On a graph of 2^29 edges
+                         or more a pass takes fewer where edges * width / 32 would not fit 32 bits */
     uint32_t grid;    /* workgroups of the push; 0 = as many as are resident */
 } gx_tune;
 

@@ -4,6 +4,7 @@
 
 #include "gx_device.h"
 #include "gx_internal.h"
+#include "gx_limits.h"
 
 namespace gx {
 

@@ -791,6 +791,7 @@ const BsVariant *bs_variants(int *n) {
         {512, 4, (const void *)k_bs_relax<512, 4>},  {512, 8, (const void *)k_bs_relax<512, 8>},
         {1024, 2, (const void *)k_bs_relax<1024, 2>}, {1024, 4, (const void *)k_bs_relax<1024, 4>},
     };
+    static_assert(BS_MAX_TILE >= 1024 * 4 && BS_MAX_TILE >= 512 * 8, "the largest tile above");
     *n = (int)(sizeof v / sizeof v[0]);
     return v;
 }
@@ -938,16 +939,17 @@ gx_status run_bsssp(gx_graph *g, const int32_t *dev_src, uint32_t B, BsWork &w, 
     const size_t n = (size_t)d.V * B;
     hipLaunchKernelGGL(k_bs_fill, dim3(std::min<size_t>(4096, (n + 255) / 256 + 1)), dim3(256), 0, s, D, n, INF);
     int64_t steps_max = 0;
-    for (uint32_t l0 = 0; l0 < B; l0 += tn.width) {
-        const uint32_t G = tn.width / 32;
+    const uint32_t width = bs_pass_width(d.E, tn.width);
+    for (uint32_t l0 = 0; l0 < B; l0 += width) {
+        const uint32_t G = width / 32;
         GX_CHECK_HIP(hipMemsetAsync(w.M[0], 0, (size_t)d.V * G * 4, s), g);
         GX_CHECK_HIP(hipMemsetAsync(w.M[1], 0, (size_t)d.V * G * 4, s), g);
         GX_CHECK_HIP(hipMemsetAsync(w.ctl, 0, sizeof(BsCtl), s), g);
-        const size_t ns = (size_t)d.V * tn.width;
+        const size_t ns = (size_t)d.V * width;
         hipLaunchKernelGGL(k_bs_fill, dim3(std::min<size_t>(4096, (ns + 255) / 256 + 1)), dim3(256), 0, s,
                            reinterpret_cast<uint32_t *>(w.S), ns, INF);
-        hipLaunchKernelGGL(k_bs_sources, dim3((tn.width + 255) / 256), dim3(256), 0, s, D, w.M[0], dev_src, B, l0,
-                           tn.width, G);
+        hipLaunchKernelGGL(k_bs_sources, dim3((width + 255) / 256), dim3(256), 0, s, D, w.M[0], dev_src, B, l0, width,
+                           G);
         const BsArgs a = bs_args_for(d, w, D, B, l0, G);
         // supersteps in groups, one readback each (one past the end costs less
         // than the wait for a readback)

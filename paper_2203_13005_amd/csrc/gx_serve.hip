@@ -511,11 +511,13 @@ struct gx_server {
 
     // Lanes for a new pool of a pair: enough for the pair's waiting queries,
     // in multiples of 32, at most lanes_per_pool (a pair with steady demand
-    // adds pools; one with little demand holds little memory).
+    // adds pools; one with little demand holds little memory), and as many as
+    // a batched superstep can count.
     uint32_t pool_lanes(int32_t graph, int32_t algo) const {
         uint32_t n = 0;
         for (auto &q : queue) n += q.graph == graph && q.algo == algo;
-        return std::min<uint32_t>(cfg.lanes_per_pool, std::max<uint32_t>(32, (n + 31) / 32 * 32));
+        const uint32_t most = algo == GX_SSSP ? 32 * bs_groups_max(graphs[graph]->d.E) : 256;
+        return std::min({cfg.lanes_per_pool, most, std::max<uint32_t>(32, (n + 31) / 32 * 32)});
     }
 
     // Picks the contiguous stretch of the arena, made of free ranges and
