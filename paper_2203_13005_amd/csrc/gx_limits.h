@@ -5,7 +5,20 @@
 #include <algorithm>
 #include <cstdint>
 
+#ifdef __HIPCC__
+#define GX_LIMIT_FN __host__ __device__ inline
+#else
+#define GX_LIMIT_FN inline
+#endif
+
 namespace gx {
+
+// End of the chunk of at most `chunk` entries that starts at `begin` in a row
+// that ends at `end`.  Entries of the symmetric image go up to 2^31 - 513, so
+// begin + chunk may not fit 32 bits.
+GX_LIMIT_FN int32_t chunk_end(int32_t begin, int32_t end, int32_t chunk) {
+    return end - begin < chunk ? end : begin + chunk;
+}
 
 // Batched SSSP counts a superstep's (edge, 32-lane group) units in 32 bits,
 // beside the entries in the other half of one 64-bit counter, and rounds the

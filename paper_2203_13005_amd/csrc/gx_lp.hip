@@ -43,6 +43,7 @@
 
 #include "gx_device.h"
 #include "gx_internal.h"
+#include "gx_limits.h"
 
 using namespace gx;
 
@@ -166,7 +167,7 @@ __global__ __launch_bounds__(LP_BLOCK) void k_lp_mark(LpStep a, DevStep *next, u
     const uint32_t n = (uint32_t)(le >> 32), gl = threadIdx.x & 15;
     for (uint32_t i = (blockIdx.x * LP_BLOCK + threadIdx.x) / 16; i < n; i += gridDim.x * (LP_BLOCK / 16)) {
         const uint2 q = a.changed[i];
-        const int32_t b = a.rp[q.x] + (int32_t)q.y * LP_CHANGED_CHUNK, e = min(a.rp[q.x + 1], b + LP_CHANGED_CHUNK);
+        const int32_t b = a.rp[q.x] + (int32_t)q.y * LP_CHANGED_CHUNK, e = chunk_end(b, a.rp[q.x + 1], LP_CHANGED_CHUNK);
         if (q.y == 0 && gl == 0) a.nxt[q.x] = a.lab[q.x];
         for (int32_t p = b + (int32_t)gl; p < e; p += 64) {
             int32_t u[4];

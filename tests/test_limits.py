@@ -40,3 +40,12 @@ def test_batched_units_fit_32_bits(tmp_path, E):
         else:  # as wide as fits
             wider = [g for g in range(got + 32, width, 32) if width % g == 0]
             assert all(E * (g // 32) + tile > (1 << 32) - 1 for g in wider)
+
+
+@pytest.mark.parametrize("chunk", [1, 1024])
+def test_chunk_ends_at_the_last_entries(tmp_path, chunk):
+    last = (1 << 31) - 513  # entries of the largest symmetric image
+    cases = [(b, e) for e in (last, last - 1, 5000, 1, 0) for b in (e, e - 1, e - 511, e - 512, e - 1023, e - 1024, e - 1025)
+             if 0 <= b]
+    body = "".join(f'std::printf("%d\\n", chunk_end({b}, {e}, {chunk}));' for b, e in cases)
+    assert [r[0] for r in run_cpp(tmp_path, body)] == [min(e, b + chunk) for b, e in cases]
