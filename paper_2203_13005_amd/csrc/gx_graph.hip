@@ -170,6 +170,7 @@ struct HostImages {
         std::vector<int4> cross;
         int32_t n_long = 0, n_mid = 0;
     } pr_rows, bp_rows;
+    int64_t lds_edges = 0;  // edges whose source has one of the first PR_LDS_SLOTS slots
     EdgeVec<int32_t> in_col, pr_src;
     EdgeVec<uint32_t> in_w;
     EdgeVec<uint2> in_adj;
@@ -345,6 +346,7 @@ static void build_slots(const gx_graph_desc *d, HostImages &h) {
     for (int64_t v = 0; v < V; v++) {
         const int64_t s = at[deg(v)]++;
         h.slot[v] = (int32_t)(s < K ? s : next++);
+        if (s < PR_LDS_SLOTS) h.lds_edges += deg(v);
     }
 }
 
@@ -751,6 +753,7 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
     GX_REQUIRE(g, GX_ENOMEM, "host allocation failed");
     Carver c(dev_arena, arena_bytes);
     layout(desc, (int64_t)h.sym_col.size(), c, &g->d);
+    g->d.pr_hot = g->d.pr_hot && h.lds_edges * PR_LDS_PART >= desc->E;
     g->d.pull_nsegs = (int64_t)h.pull_segs.size();
     g->d.n_nz = (int64_t)h.nz.size();
     g->d.n_ez = (int64_t)h.ez.size();

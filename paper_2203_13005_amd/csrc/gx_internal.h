@@ -68,14 +68,21 @@ constexpr int PR_BLOCK = 256;
 // past (on R-MAT graphs they are the sources of 70 to 93% of the in-edges).
 constexpr int64_t HOT_SLOTS = int64_t(1) << 19;
 constexpr int PR_TILE_MAX = PR_BLOCK * 8;
-// The PageRank pull of a graph with at least PR_LDS_EDGES edges keeps the
+// The PageRank pull of a graph with at least PR_LDS_EDGES edges may keep the
 // contributions of the first slots in LDS (120 KiB, one workgroup per CU).
 // 20 supersteps without and with: R-MAT scale 16 (1 M edges) 312 and 363 us,
 // 17 (2 M) 375 and 373, 18 (4 M) 566 and 506, 20 1.74 and 1.29 ms, 22 7.70 and
-// 5.63 ms; uniform, 4 M edges: 2^15 vertices 550 and 423 us, 2^17 644 and 586;
-// 2^22 vertices, 67 M edges (where it holds 1 % of the sources) 18.6 and 18.3 ms.
+// 5.63 ms; uniform, 4 M edges: 2^15 vertices 550 and 423 us, 2^17 644 and 586.
+// Those slots must also be the sources of 1 in PR_LDS_PART in-edges: where they
+// are of few, one workgroup per CU is only fewer waves.  10 supersteps without
+// and with, uniform graphs of 8 M edges: 125 000 vertices 544 and 476 us, 500 000
+// (11 % of the edges) 586 and 566, 1 M (6 %) 681 and 676, 2 M (4 %) 1036 and 1077;
+// of 4.3 M edges and 2 M vertices 666 and 787; of 5 M and 8 M 1.52 and 1.65 ms;
+// R-MAT, whose slots hold hubs: scale 22 with 1 edge per vertex 563 and 556 us,
+// with 2 806 and 706.
 constexpr int32_t PR_LDS_SLOTS = 30720;
 constexpr int64_t PR_LDS_EDGES = int64_t(1) << 22;
+constexpr int64_t PR_LDS_PART = 16;
 // Row pull of SSSP / CC: rows of at most PULL_SMALL entries are taken in
 // blocks, longer ones in segments of at most PULL_SEG entries from a table
 // built at load.  The rows (and the segments) are dealt to PULL_SLICES slices

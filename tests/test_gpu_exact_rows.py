@@ -1,8 +1,8 @@
 """Rows of exactly the lengths where the pulls change their split, each checked
 on the graph as built: PageRank tiles that are full, all but full or hold one
 edge, rows that cross few, some and many tiles, both sides of the edge and
-vertex counts from which contributions are kept in LDS (every tile size, fused
-and separate calls); batched SSSP rows around the short-row and segment limits;
+vertex counts and of the share of edges from which contributions are kept in
+LDS (every tile size, fused and separate calls); batched SSSP rows around the short-row and segment limits;
 personalised ranks of both tile sizes.
 
 Ranks are compared with the float64 oracle at the engine's own damping (0.85
@@ -117,6 +117,23 @@ def test_pagerank_contributions_in_lds(gx, V, E, tile):
     g = rows_graph(V, lengths, 5)
     assert g.E == E  # (on its side of HOT_E)
     check_pagerank(gx, g, tile, 4, separate=True)
+
+
+@pytest.mark.parametrize("hub_edges", [0, 200_000])
+def test_pagerank_first_slots_of_few_edges(gx, hub_edges):
+    """2^22 edges over two million vertices: the first 30720 slots are the sources
+    of fewer than one edge in 16 (none kept in LDS), or of more, with hubs."""
+    V, E = 2_000_000, HOT_E + 77
+    rng = np.random.default_rng(hub_edges)
+    src, dst = rng.integers(0, V, E), rng.integers(0, V, E)
+    src[:hub_edges] %= 40
+    g = gen.from_edges(V, src, dst)
+    dst = (np.arange(V) + 1) % V  # made up to E with edges that are not there yet
+    more = np.setdiff1d(np.arange(V, dtype=np.int64) * V + dst, g.src.astype(np.int64) * V + g.col)[:E - g.E]
+    g = gen.from_edges(V, np.r_[g.src, more // V], np.r_[g.col, more % V])
+    first = np.sort(g.outdeg())[::-1][:HOT_V].sum()
+    assert g.E == E and (first * 16 >= E) == (hub_edges > 0)
+    check_pagerank(gx, g, 0, 3, separate=True)
 
 
 LENGTHS = [1, 31, 32, 33, 64, 65, 255, 256, 257, 512, 513, 1025]
