@@ -5,12 +5,14 @@
 // next buffer; pointers rotate instead of data being copied between stages).
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <condition_variable>
 #include <cstdarg>
 #include <cstdio>
 #include <functional>
 #include <map>
 #include <mutex>
+#include <queue>
 #include <memory>
 #include <thread>
 #include <tuple>
@@ -179,6 +181,12 @@ struct HostImages {
     bool sym_ascending = true;
     std::vector<int32_t> in_blk;
     std::vector<uint4> pull_segs, sym_segs, packs;
+    struct SweepRecs {
+        EdgeVec<uint2> rec;
+        std::vector<uint4> units;
+        std::vector<uint32_t> recs;  // of every unit
+        int64_t uoff[PULL_SLICES + 1] = {};
+    } sweep_in, sweep_sym;
     std::vector<uint32_t> rem_out, rem_any, master, master_rep;
     std::vector<int32_t> part_list;
 };
@@ -491,6 +499,126 @@ static bool byte_weights(const gx_graph_desc *d) {
 
 // Symmetric adjacency: sorted union of out- and in-neighbours, self
 // excluded, duplicates removed (needs the in-CSR).
+// Whether SSSP and CC sweep on this graph.  From a million vertices on an L2
+// no longer holds all values, and what counts is the share of the edges whose
+// source is among the PULL_BITS vertices with the most out-edges: the row pull
+// gains with it, the sweep does not, and a larger or denser graph needs more.
+// The lines are fitted to whole solves on 75 graphs of 2^19 to 2^23 vertices and
+// degrees 1 to 64, made as R-MAT is with a = 0.25 (uniform) to 0.57.  Row pull
+// against sweep, ms:
+//   SSSP, 2^22 vertices of degree 16, shares 0.05, 0.11, 0.21, 0.27: 9.7, 6.8, 4.2,
+//     3.7 and 6.3, 5.2, 4.4, 3.9; 2^21 of degree 4, shares 0.13, 0.33, 0.39: 1.29,
+//     1.34, 1.21 and 1.19, 1.23, 1.16; 2^23 of degree 8, shares 0.03, 0.14, 0.19:
+//     10.8, 7.6, 6.1 and 7.0, 6.7, 6.3; degree 2, 2^22, share 0.09: 1.82 and 1.87;
+//     2^20 of degree 4, 16, 64, share 0.2: 0.81, 1.44, 3.4 and 0.87, 1.33, 2.7;
+//   CC, 2^22 of degree 16, the same shares: 7.2, 4.6, 2.6, 1.9 and 4.4, 3.1, 2.2, 2.0;
+//     2^22 of degree 4, share 0.07: 3.6 and 4.0; 2^20 of degree 8, 16, share 0.2:
+//     0.62, 0.88 and 0.68, 0.79.
+struct SweepRule {
+    bool in = false, sym = false;
+};
+static SweepRule sweep_rule(const gx_graph_desc *d) {
+    SweepRule r;
+    const int64_t V = d->V, E = d->E;
+    if (!(d->needs & (GX_NEED_OUT | GX_NEED_SYM)) || V < SWEEP_V_MIN || V > SWEEP_V_MAX || E < V ||
+        sweep_groups(V) * SWEEP_VT > E)
+        return r;
+    // the edges of the PULL_BITS largest out-degrees (fewer than that many have FAR or more)
+    constexpr int32_t FAR = 1 << 16;
+    std::unique_ptr<int32_t[]> count(new (std::nothrow) int32_t[FAR]());
+    if (!count) return r;
+    int64_t left = PULL_BITS, edges = 0;
+    for (int64_t v = 0; v < V; v++) {
+        const int32_t n = d->row_ptr[v + 1] - d->row_ptr[v];
+        if (n < FAR) count[n]++;
+        else edges += n, left--;
+    }
+    for (int32_t x = FAR - 1; x > 0 && left > 0; x--) {
+        const int64_t n = std::min<int64_t>(left, count[x]);
+        edges += n * x;
+        left -= n;
+    }
+    const double share = (double)edges / (double)E;
+    const double mv = (double)V / (double)SWEEP_V_MIN, degree = (double)E / (double)V;
+    const bool large = mv >= 1.5;  // (below, the values nearly fit)
+    r.in = (d->needs & GX_NEED_OUT) && degree >= (large ? 3 : 12) && share * share * std::sqrt(degree) * mv < 0.8;
+    r.sym = (d->needs & GX_NEED_SYM) && degree >= (large ? 6 : 12) && share * std::cbrt(mv) < 0.38;
+    return r;
+}
+
+// The sweep's records from a CSR over destinations (rows) listing sources.
+// Destinations are taken in blocks of 2^SWEEP_SLICE_SHIFT and dealt to the
+// bins greedily, heaviest in-edge count first, each to the lightest bin so far.
+// Bin j belongs to slice j mod PULL_SLICES; an XCD sweeps its bins one after
+// another.  Weighted records are {dst, (src mod SWEEP_BAND) << 8 | w} (the unit
+// names the band); with `w` null they are {dst, src mod SWEEP_BAND}, alike.
+static void build_sweep(const std::vector<int32_t> &rp, const int32_t *src, const uint32_t *w,
+                        HostImages::SweepRecs &out) {
+    const int64_t V = (int64_t)rp.size() - 1;
+    const int64_t nb = (V >> SWEEP_BAND_BITS) + 1;
+    const int64_t nbin = sweep_bins(V), S = nbin / PULL_SLICES;
+    const int64_t nblk = (V + (1 << SWEEP_SLICE_SHIFT) - 1) >> SWEEP_SLICE_SHIFT;
+    std::vector<int64_t> bcnt((size_t)nblk, 0);
+    for (int64_t b = 0; b < nblk; b++)
+        bcnt[b] = rp[std::min(V, (b + 1) << SWEEP_SLICE_SHIFT)] - rp[b << SWEEP_SLICE_SHIFT];
+    std::vector<int64_t> order((size_t)nblk);
+    for (int64_t i = 0; i < nblk; i++) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) { return bcnt[a] > bcnt[b]; });
+    // group index of block b's bin: slices are contiguous, their bins in order
+    std::vector<int32_t> group((size_t)nblk, 0);
+    std::vector<std::vector<int32_t>> blocks((size_t)PULL_SLICES);  // each slice's blocks, ascending
+    using Bin = std::pair<int64_t, int64_t>;  // in-edges so far, bin
+    std::priority_queue<Bin, std::vector<Bin>, std::greater<Bin>> lightest;
+    for (int64_t j = 0; j < nbin; j++) lightest.push({0, j});
+    for (int64_t b : order) {
+        const auto [n, j] = lightest.top();
+        lightest.pop();
+        lightest.push({n + bcnt[b], j});
+        group[b] = (int32_t)((j % PULL_SLICES) * S + j / PULL_SLICES);
+    }
+    for (int64_t b = 0; b < nblk; b++) blocks[group[b] / S].push_back((int32_t)b);
+    const int64_t ng = nbin * nb;
+    std::vector<int64_t> cnt((size_t)ng, 0);
+    // one thread per slice: it owns the groups of its bins, so the counts and
+    // the fill below need no shared counters
+    auto per_slice = [&](auto &&body) {
+        parallel_for(PULL_SLICES, [&](int64_t lo, int64_t hi) {
+            for (int64_t x = lo; x < hi; x++)
+                for (const int32_t b : blocks[x]) {
+                    const int64_t v1 = std::min(V, (int64_t)(b + 1) << SWEEP_SLICE_SHIFT);
+                    for (int64_t v = (int64_t)b << SWEEP_SLICE_SHIFT; v < v1; v++) body(v, group[b] * nb);
+                }
+        }, 1);
+    };
+    per_slice([&](int64_t v, int64_t g0) {
+        for (int32_t e = rp[v]; e < rp[v + 1]; e++) cnt[g0 + (src[e] >> SWEEP_BAND_BITS)]++;
+    });
+    std::vector<int64_t> pos((size_t)ng + 1, 0);
+    for (int64_t g = 0; g < ng; g++) pos[g + 1] = pos[g] + (cnt[g] + SWEEP_VT - 1) / SWEEP_VT * SWEEP_VT;
+    out.rec.resize((size_t)pos[ng]);  // every slot is written below: a record or a sentinel
+    for (int64_t g = 0; g < ng; g++)
+        for (int64_t i = pos[g] + cnt[g]; i < pos[g + 1]; i++) out.rec[i] = make_uint2(SWEEP_SENTINEL, 0u);
+    std::vector<int64_t> fill(pos.begin(), pos.end() - 1);
+    per_slice([&](int64_t v, int64_t g0) {
+        for (int32_t e = rp[v]; e < rp[v + 1]; e++) {
+            const uint32_t u = (uint32_t)src[e];
+            out.rec[fill[g0 + (u >> SWEEP_BAND_BITS)]++] =
+                make_uint2((uint32_t)v, (u & (SWEEP_BAND - 1)) << 8 | (w ? w[e] : 0u));
+        }
+    });
+    out.units.clear();
+    for (int x = 0; x < PULL_SLICES; x++) {
+        out.uoff[x] = (int64_t)out.units.size();
+        for (int64_t g = x * S * nb; g < (x + 1) * S * nb; g++)
+            for (int64_t s0 = pos[g]; s0 < pos[g + 1]; s0 += SWEEP_UNIT)
+                out.units.push_back(make_uint4((uint32_t)s0, (uint32_t)std::min<int64_t>(SWEEP_UNIT, pos[g + 1] - s0),
+                                               (uint32_t)((g % nb) << SWEEP_BAND_BITS), 0u));
+    }
+    out.uoff[PULL_SLICES] = (int64_t)out.units.size();
+    out.recs.reserve(out.units.size());
+    for (const uint4 &u : out.units) out.recs.push_back(u.y);
+}
+
 static void build_sym(const gx_graph_desc *d, HostImages &h) {
     int64_t V = d->V;
     const int32_t *orp = d->row_ptr, *oc = d->col;
@@ -549,7 +677,12 @@ static void build_flags(const gx_graph_desc *d, int32_t W, HostImages &h) {
 
 // Device layout; with a measuring Carver it only sizes the arena.  E_sym
 // must be known for the symmetric image (computed by the caller).
-static void layout(const gx_graph_desc *desc, int64_t E_sym, Carver &c, DevGraph *d) {
+static void take_sweep(int64_t V, int64_t E, Carver &c, Sweep *s) {
+    s->rec = c.take<uint2>(sweep_rec_cap(V, E));
+    s->units = c.take<uint4>(sweep_unit_cap(V, E));
+}
+
+static void layout(const gx_graph_desc *desc, int64_t E_sym, const SweepRule &sweep, Carver &c, DevGraph *d) {
     int64_t V = desc->V, E = desc->E;
     d->V = V;
     d->E = E;
@@ -587,11 +720,13 @@ static void layout(const gx_graph_desc *desc, int64_t E_sym, Carver &c, DevGraph
         d->in_blk = c.take<int32_t>((V + 63) / 64 + 1);
         d->pull_segs = c.take<uint4>(pull_seg_cap(E));
         d->packs = c.take<uint4>(pull_pack_cap(V, E));
+        if (sweep.in) take_sweep(V, E, c, &d->sweep_in);
     }
     if (desc->needs & GX_NEED_SYM) {
         d->sym_rp = c.take<int32_t>(V + 1);
         d->sym_col = c.take<int32_t>(E_sym);
         d->sym_segs = c.take<uint4>(pull_seg_cap(E_sym));
+        if (sweep.sym) take_sweep(V, E_sym, c, &d->sweep_sym);
     }
     if (desc->l2g) d->l2g = c.take<int32_t>(V);
     if (desc->outdeg_global) {
@@ -698,7 +833,7 @@ extern "C" gx_status gx_graph_bytes(const gx_graph_desc *desc, size_t *arena_byt
     if (st != GX_OK) return st;
     Carver c(nullptr, 0);
     DevGraph d;
-    layout(desc, sym_bound(desc), c, &d);
+    layout(desc, sym_bound(desc), sweep_rule(desc), c, &d);
     *arena_bytes = c.used;
     return GX_OK;
 }
@@ -712,10 +847,11 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
     if (st != GX_OK) return st;
     GX_REQUIRE(dev_arena || arena_bytes == 0, GX_EINVAL, "dev_arena is NULL");
     GX_REQUIRE(reinterpret_cast<uintptr_t>(dev_arena) % ALIGN == 0, GX_EINVAL, "dev_arena not 256-byte aligned");
+    const SweepRule sweep = sweep_rule(desc);
     {
         Carver m(nullptr, 0);
         DevGraph tmp;
-        layout(desc, sym_bound(desc), m, &tmp);
+        layout(desc, sym_bound(desc), sweep, m, &tmp);
         GX_REQUIRE(m.used <= arena_bytes, GX_ENOMEM, "arena too small: need %zu bytes, have %zu", m.used, arena_bytes);
     }
 
@@ -735,10 +871,14 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
             });
             std::fill(h.pr_src.begin() + desc->E, h.pr_src.end(), (int32_t)desc->V);  // (no slot)
         }
-        if ((desc->needs & GX_NEED_OUT) && desc->E > 0 && byte_weights(desc)) build_in_adj(h);
+        if ((desc->needs & GX_NEED_OUT) && desc->E > 0 && byte_weights(desc)) {
+            build_in_adj(h);
+            if (sweep.in) build_sweep(h.in_rp, h.in_col.data(), h.in_w.data(), h.sweep_in);
+        }
         if (desc->needs & GX_NEED_SYM) {
             build_sym(desc, h);
             build_segs(h.sym_rp, h.sym_segs);
+            if (sweep.sym) build_sweep(h.sym_rp, h.sym_col.data(), nullptr, h.sweep_sym);
         }
         build_flags(desc, W, h);
     } catch (const std::bad_alloc &) {
@@ -752,7 +892,7 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
     gx_graph *g = new (std::nothrow) gx_graph();
     GX_REQUIRE(g, GX_ENOMEM, "host allocation failed");
     Carver c(dev_arena, arena_bytes);
-    layout(desc, (int64_t)h.sym_col.size(), c, &g->d);
+    layout(desc, (int64_t)h.sym_col.size(), sweep, c, &g->d);
     g->d.pr_hot = g->d.pr_hot && h.lds_edges * PR_LDS_PART >= desc->E;
     g->d.pull_nsegs = (int64_t)h.pull_segs.size();
     g->d.n_nz = (int64_t)h.nz.size();
@@ -767,6 +907,10 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
     g->d.n_packs = (int64_t)h.packs.size();
     g->d.sym_nsegs = (int64_t)h.sym_segs.size();
     g->d.sym_ascending = h.sym_ascending;
+    g->sweep_in_recs = std::move(h.sweep_in.recs);
+    g->sweep_sym_recs = std::move(h.sweep_sym.recs);
+    std::copy(h.sweep_in.uoff, h.sweep_in.uoff + PULL_SLICES + 1, g->d.sweep_in.uoff);
+    std::copy(h.sweep_sym.uoff, h.sweep_sym.uoff + PULL_SLICES + 1, g->d.sweep_sym.uoff);
     g->needs = desc->needs;
     g->arena = dev_arena;
     g->arena_bytes = arena_bytes;
@@ -820,6 +964,10 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
         if (e == hipSuccess)
             e = up.put_array((void *)d.pull_segs, h.pull_segs.data(), h.pull_segs.size() * sizeof(uint4));
         if (e == hipSuccess) e = up.put_array((void *)d.packs, h.packs.data(), h.packs.size() * sizeof(uint4));
+    }
+    for (auto [r, t] : {std::pair(&d.sweep_in, &h.sweep_in), std::pair(&d.sweep_sym, &h.sweep_sym)}) {
+        if (e == hipSuccess && r->rec) e = up.put_array((void *)r->rec, t->rec.data(), t->rec.size() * sizeof(uint2));
+        if (e == hipSuccess && r->rec) e = up.put_array((void *)r->units, t->units.data(), t->units.size() * sizeof(uint4));
     }
     if (e == hipSuccess && d.sym_rp) {
         e = up.put_array((void *)d.sym_rp, h.sym_rp.data(), (V + 1) * 4);

@@ -100,6 +100,37 @@ constexpr int PULL_RUN_FROM = 2048;
 // on R-MAT scale 22 the sources of 75% of the in-edges).
 constexpr int PULL_BITS = 1 << 17;
 constexpr int PULL_BIT_WORDS = PULL_BITS / 32;
+
+// The other pull of SSSP / CC, a sweep over every in-edge (CC: neighbour) as a
+// record {destination, source and weight}: destinations are dealt to bins of
+// at most SWEEP_BIN_BYTES of values, each bin to one of PULL_SLICES slices; a
+// bin's records are grouped by source band (source >> SWEEP_BAND_BITS), groups
+// are padded to whole SWEEP_VT records with sentinels and cut into units of at
+// most SWEEP_UNIT records.  It costs the same whatever the values are, and its
+// random reads stay in LDS and one L2.  The row pull reads a value per entry
+// from anywhere, so it needs its rows to stop early and most of its sources to
+// be among a few; sweep_rule says which graphs sweep.
+constexpr int SWEEP_SLICE_SHIFT = 6;  // destinations are dealt in blocks of 64
+constexpr int64_t SWEEP_BIN_BYTES = int64_t(2) << 20;
+constexpr int SWEEP_BAND_BITS = 13;  // 8192 sources: 32 KiB of values in LDS
+constexpr int SWEEP_BAND = 1 << SWEEP_BAND_BITS;
+constexpr int SWEEP_VT = 8;
+constexpr int SWEEP_UNIT = 8192;
+constexpr uint32_t SWEEP_SENTINEL = 0xFFFFFFFFu;  // destination of a padding record
+constexpr int64_t SWEEP_V_MIN = int64_t(1) << 20, SWEEP_V_MAX = int64_t(1) << 28;
+struct Sweep {
+    const uint2 *rec = nullptr;    // {destination, (source mod SWEEP_BAND) << 8 | weight}; NULL: the row pull is used
+    const uint4 *units = nullptr;  // {first record, records, first source of the band, 0}
+    int64_t uoff[PULL_SLICES + 1] = {};  // slice x owns units uoff[x] .. uoff[x + 1] - 1
+};
+inline int64_t sweep_bins(int64_t V) {
+    return PULL_SLICES *
+           std::max<int64_t>(1, (V * 4 + PULL_SLICES * SWEEP_BIN_BYTES - 1) / (PULL_SLICES * SWEEP_BIN_BYTES));
+}
+inline int64_t sweep_groups(int64_t V) { return sweep_bins(V) * ((V >> SWEEP_BAND_BITS) + 1); }
+// Capacities of the records and units of E entries (known before the layout is).
+inline int64_t sweep_rec_cap(int64_t V, int64_t E) { return E + (SWEEP_VT - 1) * sweep_groups(V) + SWEEP_VT; }
+inline int64_t sweep_unit_cap(int64_t V, int64_t E) { return sweep_rec_cap(V, E) / SWEEP_UNIT + sweep_groups(V) + 1; }
 // Capacity of the segment table of E entries (known before the rows are: a
 // row in it has more than PULL_SMALL entries).
 inline int64_t pull_seg_cap(int64_t E) { return E / PULL_SMALL + 1; }
@@ -182,6 +213,8 @@ struct DevGraph {
     bool sym_ascending = true;  // every row's neighbours ascend (rows of the host CSR that do not are merged as they are)
     const uint4 *sym_segs = nullptr;
     int64_t sym_nsegs = 0;
+    // records of the sweep, on graphs where it is the faster pull
+    Sweep sweep_in, sweep_sym;
     // partition metadata
     const int32_t *l2g = nullptr;          // nullptr = identity
     const uint32_t *remote_out = nullptr;  // bitmaps of W words (nullptr = none remote)
@@ -220,6 +253,7 @@ struct gx_graph {
     std::vector<int32_t> host_outdeg;  // out-degree (host copy, for sources and stats)
     std::mutex lp_mu;
     gx::LpPlan lp;
+    std::vector<uint32_t> sweep_in_recs, sweep_sym_recs;  // records of each of the sweep's units (size its fix-up regions)
     std::vector<int32_t> host_symdeg;  // distinct neighbours (with GX_NEED_SYM; label propagation classes)
     // supersteps of the last converged SSSP / CC run on this graph: the size
     // of the next run's first speculative group (solves on one graph tend to
@@ -297,9 +331,13 @@ struct gx_state {
     uint8_t *dirty8 = nullptr;                // changed since the last sync (byte per vertex)
     uint4 *list = nullptr;
     uint32_t *tile_start = nullptr;
-    uint32_t *snap = nullptr;      // start-of-superstep values of every vertex (pull; SSSP: by slot)
+    uint32_t *snap = nullptr;      // start-of-superstep values of every vertex (pull; SSSP's row pull: by slot)
     uint32_t *hot[2] = {nullptr, nullptr};  // SSSP: at least A_k's bits of the first PULL_BITS slots, hot[k & 1]
     uint32_t pull_edges = 0xFFFFFFFFu;
+    uint2 *fix = nullptr;          // sweep: fix-up regions, fix_cap entries per relaxation workgroup
+    uint32_t *fixn = nullptr;      // and the entries recorded in each
+    uint32_t fix_cap = 0;
+    const gx::Sweep *sweep = nullptr;  // the pull sweeps these (NULL: the row pull); snapshots are then by vertex
     bool merged = false;           // other parts' values were merged (gx_apply_delta)
     // PageRank
     float *x[2] = {nullptr, nullptr};

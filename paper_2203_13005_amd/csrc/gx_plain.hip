@@ -19,8 +19,10 @@
 //   pull      : for large frontiers instead: every row of in-edges (CC:
 //               neighbours) takes the minimum over its entries itself, in an
 //               order that lets it stop early, and is its value's only
-//               writer.  The device picks push or pull from the frontier's
-//               out-edge count; no host round trip.
+//               writer.  On large graphs without hubs the pull sweeps over
+//               every in-edge instead, destination slice by source band
+//               (k_relax_sweep, and k_fixup after it).  The device picks push
+//               or pull from the frontier's out-edge count; no host round trip.
 //   k_compact : frontier byte map A_{k+1} -> active list of (edge offset,
 //               CSR base, snapshot) for active vertices with out-edges; one
 //               64-bit atomic per workgroup reserves list slots and edge
@@ -543,6 +545,34 @@ __device__ __forceinline__ void stream_rows(uint32_t *best, const uint32_t *bits
     }
 }
 
+// Row v takes the label of its first neighbour, the smallest.
+__device__ __forceinline__ void first_neighbour(const PullArgs &pa, int64_t v, uint32_t beg, uint32_t end, uint32_t low,
+                                                uint32_t cur, const uint32_t *__restrict__ snap, uint32_t *tgt,
+                                                uint8_t *__restrict__ front_next) {
+    if (beg >= end || low >= cur) return;
+    const uint32_t c = snap[(uint32_t) static_cast<const int32_t *>(pa.adj)[beg]];
+    if (c >= cur) return;
+    if (pa.atomic_rows) atomicMin(&tgt[v], c);
+    else tgt[v] = c;
+    front_next[v] = 1;
+}
+
+// The slice of a pulling workgroup: the XCD it runs on.  The hardware deals a
+// launch's workgroups to the XCDs in turn, from XCD r for workgroup 0 (r has
+// been seen to differ between launches), so workgroup b runs on XCD
+// (b + r) mod 8 and is the (b / 8)-th of its XCD (the grid is a multiple of
+// 8).  If the workgroups of one launch saw different r, some work would be
+// taken twice and some never: each leaves the r it saw, and the launch that
+// follows flags the superstep if they differ.  (xcd_shift, zero outside tests,
+// offsets the odd workgroups' XCD to exercise that check.)
+__device__ __forceinline__ uint32_t pull_slice(DevStep *__restrict__ step, uint32_t xcd_shift,
+                                               uint32_t *__restrict__ rot) {
+    const uint32_t x = (xcc_id() + ((blockIdx.x & 1u) ? xcd_shift : 0u)) % PULL_SLICES;
+    if (threadIdx.x == 0) rot[blockIdx.x] = (x + PULL_SLICES - blockIdx.x % PULL_SLICES) % PULL_SLICES;
+    if (blockIdx.x == 0 && threadIdx.x == 0) step->pad = 1;
+    return x;
+}
+
 template <bool WEIGHTED>
 __device__ __forceinline__ void pull_body(const PullArgs &pa, int64_t V, const uint32_t *__restrict__ snap,
                                           uint32_t *tgt, uint8_t *__restrict__ front_next,
@@ -551,23 +581,12 @@ __device__ __forceinline__ void pull_body(const PullArgs &pa, int64_t V, const u
     const int tid = threadIdx.x;
     RowItems &it = lds.items[tid >> 6];
     const uint32_t low = ~step->inv_min;
-    // The workgroup takes the slice of the XCD it runs on: of every 8 runs of
-    // consecutive blocks one run (neighbouring rows, whose sources often
-    // neighbour each other too, share an L2), another one in each group of 8:
-    // where rows get shorter with every bit set in their id, as on R-MAT, a
-    // fixed one would give one XCD many times the others' entries (scale 22,
-    // first pull of a solve: 380 us, with the turn 335 us).  The hardware deals a launch's
-    // workgroups to the XCDs in turn, from XCD r for workgroup 0 (r has been
-    // seen to differ between launches), so workgroup b runs on XCD
-    // (b + r) mod 8 and is the (b / 8)-th of its XCD (the grid is a multiple
-    // of 8).  If the workgroups of one launch saw different r, some blocks
-    // would be taken twice and others never: each leaves the r it saw, and
-    // the launch that follows flags the superstep if they differ.
-    // (xcd_shift, zero outside tests, offsets the odd workgroups' XCD to
-    // exercise that check.)
-    const uint32_t x = (xcc_id() + ((blockIdx.x & 1u) ? xcd_shift : 0u)) % PULL_SLICES;
-    if (tid == 0) rot[blockIdx.x] = (x + PULL_SLICES - blockIdx.x % PULL_SLICES) % PULL_SLICES;
-    if (blockIdx.x == 0 && tid == 0) step->pad = 1;
+    // Of every 8 runs of consecutive blocks a slice takes one run (neighbouring
+    // rows, whose sources often neighbour each other too, share an L2), another
+    // one in each group of 8: where rows get shorter with every bit set in their
+    // id, as on R-MAT, a fixed one would give one XCD many times the others'
+    // entries (scale 22, first pull of a solve: 380 us, with the turn 335 us).
+    const uint32_t x = pull_slice(step, xcd_shift, rot);
     const int64_t nper = gridDim.x / PULL_SLICES;
     const int64_t nseg = pa.first_only ? 0 : (pa.nsegs + PULL_SEG_BLOCK - 1) / PULL_SEG_BLOCK;
     const int64_t nblk = nseg + (V + PULL_BLOCK - 1) / PULL_BLOCK;
@@ -613,18 +632,118 @@ __device__ __forceinline__ void pull_body(const PullArgs &pa, int64_t V, const u
             end = (uint32_t)pa.rp[v + 1];
         }
         if (pa.first_only) {
-            if (beg < end && low < cur) {
-                const uint32_t c = snap[(uint32_t) static_cast<const int32_t *>(pa.adj)[beg]];
-                if (c < cur) {
-                    if (pa.atomic_rows) atomicMin(&tgt[v], c);
-                    else tgt[v] = c;
-                    front_next[v] = 1;
-                }
-            }
+            first_neighbour(pa, v, beg, end, low, cur, snap, tgt, front_next);
             continue;
         }
         const int n = queue_items(it, beg < end && end - beg <= PULL_SMALL && low < cur, (uint32_t)v, beg, end, cur);
         scan_items<WEIGHTED, 4, 2>(it, lds.bits, n, pa, low, snap, tgt, front_next, pa.atomic_rows != 0);
+    }
+}
+
+// CC's first superstep where the sweep is the pull: one neighbour per row.
+__device__ __forceinline__ void first_body(const PullArgs &pa, int64_t V, const uint32_t *__restrict__ snap,
+                                           uint32_t *tgt, uint8_t *__restrict__ front_next,
+                                           DevStep *__restrict__ step, uint32_t *__restrict__ rot) {
+    if (threadIdx.x == 0) rot[blockIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) step->pad = 1;
+    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < V; v += (int64_t)gridDim.x * 256)
+        first_neighbour(pa, v, (uint32_t)pa.rp[v], (uint32_t)pa.rp[v + 1], ~step->inv_min, pa.bound[v], snap, tgt,
+                        front_next);
+}
+
+// Pull form on graphs without hubs (see Sweep): every record once.  A
+// workgroup takes units of its slice, so each XCD's L2 holds one bin's
+// destinations; a unit's band of source values is staged in LDS, INF where the
+// frontier map says the source is inactive, so a record's gather is an LDS
+// read.  The 64 lanes of a wave take 64 consecutive records (destinations
+// ascending), so lanes whose destinations share a cache line make one request
+// between them: those reads, one per record, bound it.  A record without a
+// candidate reads nothing (its offset lies past the buffer).
+//
+// A candidate below a value read during the superstep is below the
+// destination's start value (values only fall), so the destination changes
+// whatever else lands: it is marked, its value is set with a plain store, and
+// the pair goes to the workgroup's fix-up region.  Racing stores may leave a
+// larger candidate; k_fixup, a later launch, re-applies every recorded one that
+// is still below.  Every writer of a destination runs on the XCD of its slice,
+// so one L2 sees all of its stores, and a region holds every record its
+// workgroup can meet, so no candidate goes another way.  (With an atomic
+// minimum instead, 2^22 vertices, 67 M uniform edges, the first pull of a solve
+// takes 820 us, 590 so.)
+struct FixRegion {
+    uint2 *ent;       // this workgroup's region
+    uint32_t *count;  // LDS: candidates so far
+};
+
+template <bool WEIGHTED>
+__device__ __forceinline__ void sweep_body(const Sweep &sw, int64_t V, const uint32_t *__restrict__ snap,
+                                           const uint8_t *__restrict__ front_cur, uint32_t *tgt,
+                                           uint8_t *__restrict__ front_next, DevStep *__restrict__ step,
+                                           uint32_t *s_val, const FixRegion &fr, uint32_t xcd_shift,
+                                           uint32_t *__restrict__ rot) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t x = pull_slice(step, xcd_shift, rot);
+    const __amdgpu_buffer_rsrc_t trs =
+        __builtin_amdgcn_make_buffer_rsrc(tgt, (short)0, (int)(uint32_t)(V * 4), 0x00020000);
+    const int64_t nper = gridDim.x / PULL_SLICES;
+    for (int64_t ui = sw.uoff[x] + blockIdx.x / PULL_SLICES; ui < sw.uoff[x + 1]; ui += nper) {
+        const uint4 un = sw.units[ui];
+        const uint32_t start = un.x, end = un.x + un.y, bb = un.z;
+        __syncthreads();  // the previous unit's gathers are done
+        if ((int64_t)bb + SWEEP_BAND <= V) {
+            const uint4 *s4 = reinterpret_cast<const uint4 *>(snap + bb);
+            const uint32_t *f4 = reinterpret_cast<const uint32_t *>(front_cur + bb);
+            constexpr int N = SWEEP_BAND / 4 / 256;
+            uint4 sv[N];
+            uint32_t fv[N];
+#pragma unroll
+            for (int q = 0; q < N; q++) {
+                sv[q] = s4[q * 256 + tid];
+                fv[q] = f4[q * 256 + tid];
+            }
+#pragma unroll
+            for (int q = 0; q < N; q++)
+                reinterpret_cast<uint4 *>(s_val)[q * 256 + tid] =
+                    make_uint4(fv[q] & 0xFFu ? sv[q].x : INF, fv[q] & 0xFF00u ? sv[q].y : INF,
+                               fv[q] & 0xFF0000u ? sv[q].z : INF, fv[q] & 0xFF000000u ? sv[q].w : INF);
+        } else {  // the last band ends at V
+            for (int i = tid; i < SWEEP_BAND; i += 256) s_val[i] = bb + i < V && front_cur[bb + i] ? snap[bb + i] : INF;
+        }
+        __syncthreads();
+        for (uint32_t c0 = start; c0 < end; c0 += 256 * SWEEP_VT) {
+            uint32_t dst[SWEEP_VT], m[SWEEP_VT], cur[SWEEP_VT];
+            uint2 q[SWEEP_VT];
+#pragma unroll
+            for (int i = 0; i < SWEEP_VT; i++) q[i] = sw.rec[min(c0 + (uint32_t)i * 256 + (uint32_t)tid, end - 1)];
+#pragma unroll
+            for (int i = 0; i < SWEEP_VT; i++) {  // (past the unit's end: no candidate, so a region holds them all)
+                dst[i] = c0 + (uint32_t)i * 256 + (uint32_t)tid < end ? q[i].x : SWEEP_SENTINEL;
+                const uint32_t sv = s_val[q[i].y >> 8];
+                m[i] = dst[i] == SWEEP_SENTINEL ? INF : WEIGHTED ? sat_add(sv, q[i].y & 0xFFu) : sv;
+                cur[i] = __builtin_amdgcn_raw_buffer_load_b32(trs, m[i] != INF ? dst[i] * 4u : 0x80000000u, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);  // every read above is issued before the first compare
+            uint32_t cnt = 0;
+#pragma unroll
+            for (int i = 0; i < SWEEP_VT; i++) cnt += m[i] < cur[i];
+            // one reservation per wave, entries in lane order
+            uint32_t incl = cnt;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t y = __shfl_up(incl, o, 64);
+                if (lane >= o) incl += y;
+            }
+            uint32_t pos = 0;
+            if (lane == 63 && incl) pos = atomicAdd(fr.count, incl);
+            pos = __shfl(pos, 63, 64) + incl - cnt;
+#pragma unroll
+            for (int i = 0; i < SWEEP_VT; i++)
+                if (m[i] < cur[i]) {
+                    fr.ent[pos++] = make_uint2(dst[i], m[i]);
+                    tgt[dst[i]] = m[i];
+                    front_next[dst[i]] = 1;
+                }
+        }
     }
 }
 
@@ -635,6 +754,45 @@ union RelaxLds {
     PushLds push;
     PullLds pull;
 };
+union SweepLds {
+    PushLds push;
+    uint32_t val[SWEEP_BAND];
+};
+
+// (CC's first superstep reads one neighbour per row in either pull.)
+template <bool WEIGHTED>
+__global__ __launch_bounds__(256) void k_relax_sweep(
+    const uint4 *__restrict__ list, const uint32_t *__restrict__ tile_start, const void *__restrict__ adj, PullArgs pa,
+    Sweep sw, const uint8_t *__restrict__ front_cur, int64_t V, const uint32_t *__restrict__ snap, uint32_t *val,
+    uint8_t *__restrict__ front_next, DevStep *__restrict__ step, uint32_t pull_edges, uint2 *__restrict__ fix,
+    uint32_t *__restrict__ fixn, uint32_t fix_cap, uint32_t *__restrict__ rot, uint32_t xcd_shift) {
+    __shared__ SweepLds lds;
+    __shared__ uint32_t s_fixn;
+    if (threadIdx.x == 0) s_fixn = 0;
+    __syncthreads();
+    const unsigned long long le = step->list;
+    if ((uint32_t)le < pull_edges)
+        push_body<WEIGHTED>(list, tile_start, adj, val, front_next, le, lds.push);
+    else if (!WEIGHTED && pa.first_only)
+        first_body(pa, V, snap, val, front_next, step, rot);
+    else
+        sweep_body<WEIGHTED>(sw, V, snap, front_cur, val, front_next, step, lds.val,
+                             FixRegion{fix + (size_t)blockIdx.x * fix_cap, &s_fixn}, xcd_shift, rot);
+    __syncthreads();
+    if (threadIdx.x == 0) fixn[blockIdx.x] = s_fixn;
+}
+
+// Workgroup b re-applies the candidates that relaxation workgroup b recorded
+// and that are still below the stored value (after a push there are none).
+__global__ __launch_bounds__(256) void k_fixup(const uint2 *__restrict__ fix, const uint32_t *__restrict__ fixn,
+                                               uint32_t fix_cap, uint32_t *__restrict__ val) {
+    const uint32_t n = fixn[blockIdx.x];
+    const uint2 *e = fix + (size_t)blockIdx.x * fix_cap;
+    for (uint32_t i = threadIdx.x; i < n; i += 256) {
+        const uint2 q = e[i];
+        if (q.y < val[q.x]) atomicMin(&val[q.x], q.y);
+    }
+}
 
 template <bool WEIGHTED>
 __global__ __launch_bounds__(256) void k_relax(const uint4 *__restrict__ list, const uint32_t *__restrict__ tile_start,
@@ -1359,9 +1517,27 @@ static int persistent_grid(gx_graph *g, K kernel, int block) {
 
 // Persistent grid of the relaxation: whole multiples of the slice count (a
 // pulling XCD's workgroups share its slice's units evenly).
-static int relax_grid_for(gx_graph *g, const gx_params *p) {
-    const int pg = p->algo == GX_CC ? persistent_grid(g, k_relax<false>, 256) : persistent_grid(g, k_relax<true>, 256);
+static int relax_grid_for(gx_graph *g, const gx_params *p, bool sweep) {
+    const int pg = sweep ? (p->algo == GX_CC ? persistent_grid(g, k_relax_sweep<false>, 256)
+                                             : persistent_grid(g, k_relax_sweep<true>, 256))
+                         : (p->algo == GX_CC ? persistent_grid(g, k_relax<false>, 256)
+                                             : persistent_grid(g, k_relax<true>, 256));
     return std::max(PULL_SLICES, pg / PULL_SLICES * PULL_SLICES);
+}
+
+// Fix-up entries per workgroup of a sweep: the records of the units one takes
+// (the j-th workgroup on the XCD of slice x takes units j, j + nper, ... of
+// slice x), maximised over x and j, so a region never overflows.
+static uint32_t fix_cap_for(const Sweep &sw, const std::vector<uint32_t> &recs, int grid) {
+    const int64_t nper = grid / PULL_SLICES;
+    int64_t most = 0;
+    for (int x = 0; x < PULL_SLICES; x++)
+        for (int64_t j = 0; j < nper; j++) {
+            int64_t sum = 0;
+            for (int64_t u = sw.uoff[x] + j; u < sw.uoff[x + 1]; u += nper) sum += recs[(size_t)u];
+            most = std::max(most, sum);
+        }
+    return (uint32_t)most;
 }
 
 // What the pull of `s` reads; `bound`: the vertex values.  CC labels ascend
@@ -1374,6 +1550,26 @@ static PullArgs pull_args(const gx_state *s) {
         return {d.sym_rp, d.sym_col, d.sym_segs, d.sym_nsegs, s->k == 0 && !s->merged && d.sym_ascending,
                 s->acc != nullptr, s->val, nullptr};
     return {d.in_blk, d.in_adj, d.pull_segs, d.pull_nsegs, 0, s->acc != nullptr, s->val, s->hot[s->k & 1]};
+}
+
+// The relaxation of the active list and the frontier map `front` it was built
+// from, against `tgt` (the values, or an accumulator).
+static void launch_relax(gx_state *s, hipStream_t hs, const uint8_t *front, uint32_t *tgt, uint8_t *front_next,
+                         DevStep *step) {
+    const DevGraph &d = s->g->d;
+    const bool cc = s->p.algo == GX_CC;
+    const void *adj = cc ? (const void *)d.sym_col : (const void *)d.out_adj;
+    const PullArgs pa = pull_args(s);
+    if (s->sweep) {
+        hipLaunchKernelGGL(cc ? k_relax_sweep<false> : k_relax_sweep<true>, dim3(s->relax_grid), dim3(256), 0, hs, s->list,
+                           s->tile_start, adj, pa, *s->sweep, front, d.V, s->snap, tgt, front_next, step,
+                           s->pull_edges, s->fix, s->fixn, s->fix_cap, s->rot, s->xcd_shift);
+        hipLaunchKernelGGL(k_fixup, dim3(s->relax_grid), dim3(256), 0, hs, s->fix, s->fixn, s->fix_cap, tgt);
+    } else {
+        hipLaunchKernelGGL(cc ? k_relax<false> : k_relax<true>, dim3(s->relax_grid), dim3(256), 0, hs, s->list,
+                           s->tile_start, adj, pa, d.V, s->snap, tgt, front_next, step, s->pull_edges, s->rot,
+                           s->xcd_shift);
+    }
 }
 
 // Compacts the map `front` (A_{s->k + ahead}) into the active list, counting
@@ -1479,9 +1675,16 @@ static size_t state_layout(gx_graph *g, const gx_params *p, Carver &c, gx_state 
         s->list = c.take<uint4>(V);
         s->tile_start = c.take<uint32_t>(Eimg / PUSH_TILE + 2);
         s->snap = c.take<uint32_t>(V);
-        s->relax_grid = relax_grid_for(g, p);
+        const Sweep &sw = p->algo == GX_CC ? d.sweep_sym : d.sweep_in;
+        s->sweep = sw.rec ? &sw : nullptr;
+        s->relax_grid = relax_grid_for(g, p, s->sweep != nullptr);
         s->rot = c.take<uint32_t>(s->relax_grid);
-        if (p->algo == GX_SSSP)
+        if (s->sweep) {
+            s->fix_cap = fix_cap_for(sw, p->algo == GX_CC ? g->sweep_sym_recs : g->sweep_in_recs, s->relax_grid);
+            s->fix = c.take<uint2>((size_t)s->relax_grid * s->fix_cap);
+            s->fixn = c.take<uint32_t>(s->relax_grid);
+        }
+        if (p->algo == GX_SSSP && !s->sweep)
             for (uint32_t *&h : s->hot) h = c.take<uint32_t>(PULL_BIT_WORDS);
     }
     if (p->phases) {
@@ -1771,13 +1974,9 @@ static gx_status enqueue_superstep(gx_state *s, hipStream_t hs) {
         // superstep k: relax A_k (list built by the previous compaction), then
         // compact A_{k+1} for superstep k+1
         const int cur = (int)(s->k & 1);
-        const bool cc = p.algo == GX_CC;
         if (d.V > 0) {
             if (e0) (void)hipEventRecord(e0, hs);
-            auto relax = cc ? k_relax<false> : k_relax<true>;
-            hipLaunchKernelGGL(relax, dim3(s->relax_grid), dim3(256), 0, hs, s->list, s->tile_start,
-                               cc ? (const void *)d.sym_col : (const void *)d.out_adj, pull_args(s), d.V, s->snap, s->val,
-                               s->front8[cur ^ 1], step, s->pull_edges, s->rot, s->xcd_shift);
+            launch_relax(s, hs, s->front8[cur], s->val, s->front8[cur ^ 1], step);
             if (e1) (void)hipEventRecord(e1, hs);
             launch_compact(s, hs, s->front8[cur ^ 1], s->front8[cur], 1, step, s->dirty8);
         }
@@ -2243,12 +2442,8 @@ extern "C" gx_status gx_msg_merge(gx_state *s, void *stream) {
         } else {
             // the relaxation of the fused superstep, against the accumulator:
             // it combines the messages by minimum and changes no vertex value
-            DevStep *step = s->steps + (s->k % STEP_RING);
-            const bool cc = s->p.algo == GX_CC;
-            auto relax = cc ? k_relax<false> : k_relax<true>;
-            hipLaunchKernelGGL(relax, dim3(s->relax_grid), dim3(256), 0, hs, s->list, s->tile_start,
-                               cc ? (const void *)d.sym_col : (const void *)d.out_adj, pull_args(s), d.V, s->snap, s->acc,
-                               s->junk8, step, s->pull_edges, s->rot, s->xcd_shift);
+            // (MSGGen has turned the maps round)
+            launch_relax(s, hs, s->front8[s->ph_p ^ 1], s->acc, s->junk8, s->steps + (s->k % STEP_RING));
         }
         GX_CHECK_HIP(hipGetLastError(), s);
     }

@@ -1,8 +1,11 @@
 """The limits in gx_limits.h, compiled as plain C++ (no GPU): widths of
-counters and indexes at the largest graphs that a load accepts."""
+counters and indexes at the largest graphs that a load accepts; and the graphs
+whose load builds the sweep's image, by the arena bytes it asks for."""
+import ctypes
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -49,3 +52,41 @@ def test_chunk_ends_at_the_last_entries(tmp_path, chunk):
              if 0 <= b]
     body = "".join(f'std::printf("%d\\n", chunk_end({b}, {e}, {chunk}));' for b, e in cases)
     assert [r[0] for r in run_cpp(tmp_path, body)] == [min(e, b + chunk) for b, e in cases]
+
+
+V0 = 1 << 20  # smallest vertex count that sweeps
+
+
+def arena_bytes(V, degree, hub_degree, need):
+    """gx_graph_bytes of a CSR whose first 2^17 rows have hub_degree entries, the others `degree`."""
+    from paper_2203_13005_amd import binding as b
+    deg = np.full(V, degree)
+    deg[:1 << 17] = hub_degree
+    rp = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    col, w = np.zeros(rp[-1], np.int32), np.ones(rp[-1], np.uint32)
+    d = b._GraphDesc(V, int(rp[-1]), b._np_ptr(rp), b._np_ptr(col), b._np_ptr(w), None, None, need)
+    n = ctypes.c_size_t()
+    assert b.lib.gx_graph_bytes(ctypes.byref(d), ctypes.byref(n)) == b.GX_OK
+    return n.value, int(rp[-1])
+
+
+def test_which_graphs_sweep():
+    from paper_2203_13005_amd import binding as b
+
+    def sssp(V, degree, hub_degree):  # 8 bytes an edge more (no others grow so)
+        n, E = arena_bytes(V, degree, hub_degree, b.GX_NEED_OUT)
+        return n > 18.5 * E + 24 * V
+
+    assert sssp(V0, 12, 12) and not sssp(V0 - 1, 12, 12)
+    assert not sssp(V0, 11, 11) and not sssp(3 * V0 // 2 - 1, 11, 11)  # sparse: from 1.5 * 2^20 vertices on
+    assert sssp(3 * V0 // 2, 3, 3) and not sssp(2 * V0, 2, 2)
+    assert not sssp(V0, 12, 84)  # 2^17 vertices are the sources of half the edges
+    assert sssp(2 * V0, 8, 40) and not sssp(2 * V0, 8, 100)  # of 0.25, of 0.45
+
+    def cc(V, degree, hub_degree):  # 8 bytes an entry, two entries an edge
+        n, E = arena_bytes(V, degree, hub_degree, b.GX_NEED_SYM)
+        return n > 21 * E
+
+    assert cc(V0, 12, 12) and not cc(V0 - 1, 12, 12) and not cc(V0, 11, 11)
+    assert cc(3 * V0 // 2, 6, 6) and not cc(2 * V0, 5, 5)
+    assert not cc(V0, 12, 84) and cc(2 * V0, 8, 40) and not cc(2 * V0, 8, 70)
