@@ -114,10 +114,16 @@ __global__ __launch_bounds__(256) void k_min_init(uint32_t *val, uint32_t *snap,
 // graph then still has several workgroups, and a thread with hubs writes few
 // list entries one after another (scale-15 solve: 155 us against 212 us with
 // 16, together with idle pull workgroups leaving before they stage the
-// frontier bits; scale 22: 1212 us with 8 against 1357 us with 16, which
-// leaves no registers for the slots).
-constexpr int COMPACT_WIDE = 8;
-constexpr int64_t COMPACT_WIDE_FROM = int64_t(1) << 20;
+// frontier bits; R-MAT scale 20: 436 us with 8, 515 with 16; scale 22: 1055 and
+// 1069).  It is COMPACT_WIDEST where half as many reservations count more: from
+// COMPACT_WIDEST_FROM vertices on, half of that on graphs of fewer than
+// COMPACT_SPARSE edges per vertex, whose many supersteps have active vertices
+// everywhere (with 8 and 16: 2^22 vertices of degree 1 1.78 and 1.64 ms, 2 1.80
+// and 1.71, 4 2.00 and 2.00; 2^23 of degree 2 3.19 and 3.05, 4 4.31 and 4.19; R-MAT
+// scale 23 of degree 8 1.58 and 1.58).
+constexpr int COMPACT_WIDE = 8, COMPACT_WIDEST = 16;
+constexpr int64_t COMPACT_WIDE_FROM = int64_t(1) << 20, COMPACT_WIDEST_FROM = int64_t(1) << 23;
+constexpr int64_t COMPACT_SPARSE = 4;
 // Threads per compaction workgroup: each workgroup makes one list
 // reservation (an add with return on a single counter, which serialises
 // across workgroups), so fewer, larger workgroups shorten that chain.
@@ -162,7 +168,7 @@ __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ 
     // map read here is still the cleared one and the map cleared here is
     // empty, so A_{k+1} is empty without a sweep (its counters stay zero).
     // (A small graph's map is read as fast as the counter.)
-    if (CVT == COMPACT_WIDE && prev != nullptr && prev->frontier == 0) return;
+    if (CVT >= COMPACT_WIDE && prev != nullptr && prev->frontier == 0) return;
     if (slot != nullptr)  // the bits of the superstep after the one compacted here
         for (int64_t i = (int64_t)blockIdx.x * CBLOCK + tid; i < PULL_BIT_WORDS; i += (int64_t)(gridDim.x - 1) * CBLOCK)
             hot_clear[i] = 0u;
@@ -194,6 +200,8 @@ __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ 
     int32_t r[CVT + 1];
     uint32_t x[CVT];
     int32_t sl[CVT];
+    // (16 vertices leave no registers for the slots until the row pointers are counted)
+    constexpr bool SLOTS_EARLY = CVT <= COMPACT_WIDE;
     const bool by_slot = snap_all && slot != nullptr;
 #pragma unroll
     for (int i = 0; i < CVT; i++) {
@@ -214,7 +222,7 @@ __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ 
                 x[4 * q] = b.x, x[4 * q + 1] = b.y, x[4 * q + 2] = b.z, x[4 * q + 3] = b.w;
             }
             r[CVT] = rp[u0 + CVT];
-            if (by_slot)
+            if (by_slot && SLOTS_EARLY)
 #pragma unroll
                 for (int q = 0; q < CVT / 4; q++) {
                     const int4 a = reinterpret_cast<const int4 *>(slot + u0)[q];
@@ -224,7 +232,7 @@ __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ 
 #pragma unroll
             for (int i = 0; i < CVT; i++) {
                 if (u0 + i < V) x[i] = val[u0 + i];
-                if (by_slot && u0 + i < V) sl[i] = slot[u0 + i];
+                if (by_slot && SLOTS_EARLY && u0 + i < V) sl[i] = slot[u0 + i];
                 if (u0 + i <= V) r[i] = rp[u0 + i];
             }
         }
@@ -258,6 +266,10 @@ __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ 
     // vertices (whole vectors; an inactive vertex's value is the one its
     // snapshot holds already).
     if (by_slot) {
+        if (!SLOTS_EARLY)
+#pragma unroll
+            for (int i = 0; i < CVT; i++)
+                if ((actmask >> i) & 1u) sl[i] = slot[u0 + i];
 #pragma unroll
         for (int i = 0; i < CVT; i++) {
             if (!((actmask >> i) & 1u)) continue;
@@ -1580,9 +1592,12 @@ static void launch_compact(gx_state *s, hipStream_t hs, const uint8_t *front, ui
                            uint8_t *dirty) {
     const DevGraph &d = s->g->d;
     const int64_t k = s->k + ahead;
-    const bool wide = d.V >= COMPACT_WIDE_FROM;
-    auto kern = wide ? k_compact<COMPACT_WIDE> : k_compact<4>;
-    hipLaunchKernelGGL(kern, dim3(grid_for<int64_t>(d.V, CBLOCK * (wide ? COMPACT_WIDE : 4)) + 1), dim3(CBLOCK), 0, hs, front,
+    const int cvt = d.V >= COMPACT_WIDEST_FROM || (2 * d.V >= COMPACT_WIDEST_FROM && d.E < COMPACT_SPARSE * d.V)
+                        ? COMPACT_WIDEST
+                    : d.V >= COMPACT_WIDE_FROM ? COMPACT_WIDE : 4;
+    auto kern = cvt == COMPACT_WIDEST ? k_compact<COMPACT_WIDEST>
+              : cvt == COMPACT_WIDE ? k_compact<COMPACT_WIDE> : k_compact<4>;
+    hipLaunchKernelGGL(kern, dim3(grid_for<int64_t>(d.V, CBLOCK * cvt) + 1), dim3(CBLOCK), 0, hs, front,
                        clear, s->p.algo == GX_CC ? d.sym_rp : d.out_rp, s->val, s->snap, d.V, s->list, s->tile_start,
                        s->steps + (k % STEP_RING), s->steps + ((k + 1) % STEP_RING),
                        (int)(s->pull_edges != 0xFFFFFFFFu), prev, dirty, s->pull_edges, s->rot, s->relax_grid,
