@@ -513,14 +513,16 @@ static bool byte_weights(const gx_graph_desc *d) {
 //     2^20 of degree 4, 16, 64, share 0.2: 0.81, 1.44, 3.4 and 0.87, 1.33, 2.7;
 //   CC, 2^22 of degree 16, the same shares: 7.2, 4.6, 2.6, 1.9 and 4.4, 3.1, 2.2, 2.0;
 //     2^22 of degree 4, share 0.07: 3.6 and 4.0; 2^20 of degree 8, 16, share 0.2:
-//     0.62, 0.88 and 0.68, 0.79.
+//     0.62, 0.88 and 0.68, 0.79; about one edge per vertex, 3 M and 4.2 M vertices,
+//     uniform: 2.80, 4.25 and 2.54, 3.63; 4.2 M, share 0.16: 2.33 and 2.42; 8.4 M,
+//     share 0.08: 6.9 and 7.4.
 struct SweepRule {
     bool in = false, sym = false;
 };
 static SweepRule sweep_rule(const gx_graph_desc *d) {
     SweepRule r;
     const int64_t V = d->V, E = d->E;
-    if (!(d->needs & (GX_NEED_OUT | GX_NEED_SYM)) || V < SWEEP_V_MIN || V > SWEEP_V_MAX || E < V ||
+    if (!(d->needs & (GX_NEED_OUT | GX_NEED_SYM)) || V < SWEEP_V_MIN || V > SWEEP_V_MAX || 2 * E < V ||
         sweep_groups(V) * SWEEP_VT > E)
         return r;
     // the edges of the PULL_BITS largest out-degrees (fewer than that many have FAR or more)
@@ -542,7 +544,8 @@ static SweepRule sweep_rule(const gx_graph_desc *d) {
     const double mv = (double)V / (double)SWEEP_V_MIN, degree = (double)E / (double)V;
     const bool large = mv >= 1.5;  // (below, the values nearly fit)
     r.in = (d->needs & GX_NEED_OUT) && degree >= (large ? 3 : 12) && share * share * std::sqrt(degree) * mv < 0.8;
-    r.sym = (d->needs & GX_NEED_SYM) && degree >= (large ? 6 : 12) && share * std::cbrt(mv) < 0.38;
+    const bool few = degree < 1.8 && large && mv < 6 && share * std::cbrt(mv) < 0.22;
+    r.sym = (d->needs & GX_NEED_SYM) && (few || (degree >= (large ? 6 : 12) && share * std::cbrt(mv) < 0.38));
     return r;
 }
 

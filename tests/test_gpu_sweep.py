@@ -87,11 +87,11 @@ def test_sssp_sweep(gx, V, E, weights):
         follow(g, separate(st), st.values_numpy, *start(g, source), True, False, cap)
 
 
-@pytest.mark.parametrize("V", [V0, V0 + 65])
-def test_cc_sweep(gx, V):
+@pytest.mark.parametrize("V,degree", [(V0, 12), (V0 + 65, 12), (4 * V0 - 65, 1)])
+def test_cc_sweep(gx, V, degree):
     import torch
-    g = uniform(V, 12 * V + V // 50, "zero", V)
-    assert g.E >= 12 * V
+    g = uniform(V, degree * V + V // 50, "zero", V)
+    assert g.E >= degree * V
     dg = gx.DeviceGraph(g, gx.GX_NEED_SYM)
     lab, front = np.arange(V, dtype=np.uint32), np.zeros(V, bool)
     front[np.unique(np.r_[np.nonzero(np.diff(g.row_ptr))[0], g.col])] = True

@@ -89,4 +89,5 @@ def test_which_graphs_sweep():
 
     assert cc(V0, 12, 12) and not cc(V0 - 1, 12, 12) and not cc(V0, 11, 11)
     assert cc(3 * V0 // 2, 6, 6) and not cc(2 * V0, 5, 5)
+    assert cc(4 * V0, 1, 2) and not cc(4 * V0, 1, 9) and not cc(6 * V0, 1, 1) and not cc(4 * V0, 2, 2)
     assert not cc(V0, 12, 84) and cc(2 * V0, 8, 40) and not cc(2 * V0, 8, 70)
