@@ -626,7 +626,7 @@ static void build_sym(const gx_graph_desc *d, HostImages &h) {
     int64_t V = d->V;
     const int32_t *orp = d->row_ptr, *oc = d->col;
     const int32_t *irp = h.in_rp.data(), *ic = h.in_col.data();
-    auto merge_row = [&](int64_t u, int32_t *out) -> int32_t {
+    auto merge_row = [&](int64_t u, int32_t *out, bool &up) -> int32_t {
         int32_t a = orp[u], ae = orp[u + 1], b = irp[u], be = irp[u + 1], n = 0, last = -1;
         while (a < ae || b < be) {
             int32_t x;
@@ -635,29 +635,27 @@ static void build_sym(const gx_graph_desc *d, HostImages &h) {
             if (x == (int32_t)u || x == last) continue;
             if (out) out[n] = x;
             n++;
+            up &= x > last;
             last = x;
         }
         return n;
     };
-    h.sym_rp.assign(V + 1, 0);
-    parallel_for(V, [&](int64_t lo, int64_t hi) {
-        for (int64_t u = lo; u < hi; u++) h.sym_rp[u + 1] = merge_row(u, nullptr);
-    });
-    for (int64_t v = 0; v < V; v++) h.sym_rp[v + 1] += h.sym_rp[v];
-    h.sym_col.resize(h.sym_rp[V]);
     // Out-rows that the caller did not sort leave rows that do not ascend and
     // may hold a neighbour twice: no one neighbour then stands for a row.
     std::atomic<bool> ascending{true};
+    h.sym_rp.assign(V + 1, 0);
     parallel_for(V, [&](int64_t lo, int64_t hi) {
         bool up = true;
-        for (int64_t u = lo; u < hi; u++) {
-            int32_t *row = h.sym_col.data() + h.sym_rp[u];
-            const int32_t n = merge_row(u, row);
-            for (int32_t i = 1; i < n; i++) up &= row[i - 1] < row[i];
-        }
+        for (int64_t u = lo; u < hi; u++) h.sym_rp[u + 1] = merge_row(u, nullptr, up);
         if (!up) ascending = false;
     });
     h.sym_ascending = ascending;
+    for (int64_t v = 0; v < V; v++) h.sym_rp[v + 1] += h.sym_rp[v];
+    h.sym_col.resize(h.sym_rp[V]);
+    parallel_for(V, [&](int64_t lo, int64_t hi) {
+        bool up = true;
+        for (int64_t u = lo; u < hi; u++) merge_row(u, h.sym_col.data() + h.sym_rp[u], up);
+    });
 }
 
 static void build_flags(const gx_graph_desc *d, int32_t W, HostImages &h) {
