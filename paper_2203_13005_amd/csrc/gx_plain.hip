@@ -1223,21 +1223,23 @@ __global__ __launch_bounds__(256) void k_part_emit(const int32_t *__restrict__ p
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int32_t v = part_list[i];
-    gid_out[i] = l2g[v];
+    gid_out[i] = l2g ? l2g[v] : v;
     val_out[i] = acc[v];
 }
 
-// Local id of a global one (-1: not held): a search over 256 samples of the
+// Local id of a global one (-1: not held; no map: the same id): a search over 256 samples of the
 // ascending map in LDS, then over one 256th of the map.  The chain of
 // dependent reads bounds it: the whole search in global memory took 7.2 us
 // for a part of R-MAT scale 18 (one of four; a launch alone about 3), 6.4 us so.
 constexpr int MAP_SAMPLES = 256;
 __device__ __forceinline__ void sample_map(const int32_t *__restrict__ l2g, int64_t V, int32_t *s_top) {
+    if (!l2g) return;
     const int64_t end = (threadIdx.x + 1) * V / MAP_SAMPLES;  // (256 threads)
     s_top[threadIdx.x] = end > 0 ? l2g[end - 1] : -1;
     __syncthreads();
 }
 __device__ __forceinline__ int64_t local_of(const int32_t *__restrict__ l2g, int64_t V, const int32_t *s_top, int32_t g) {
+    if (!l2g) return g >= 0 && g < V ? g : -1;
     int p = 0;
 #pragma unroll
     for (int step = MAP_SAMPLES / 2; step > 0; step /= 2)
@@ -1410,16 +1412,10 @@ __global__ __launch_bounds__(256) void k_apply_delta(const int32_t *__restrict__
     __shared__ int32_t s_top[MAP_SAMPLES];
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     const int32_t g = i < n ? gid[i] : -1;
-    if (l2g) sample_map(l2g, V, s_top);
+    sample_map(l2g, V, s_top);
     if (i >= n) return;
-    int64_t x;
-    if (l2g) {
-        x = local_of(l2g, V, s_top, g);
-        if (x < 0) return;
-    } else {
-        if (g < 0 || g >= V) return;
-        x = g;
-    }
+    const int64_t x = local_of(l2g, V, s_top, g);
+    if (x < 0) return;
     const uint32_t v = vals[i];
     if (v < val[x]) {  // below the value before the merge: the replica changes
         atomicMin(&val[x], v);
