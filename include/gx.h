@@ -457,11 +457,13 @@ gx_status gx_balance_split(const double *c, int32_t m, double D, double *d_out);
  * --------------------------------------------------------------------- */
 
 typedef struct gx_tune {
-    uint32_t block;   /* threads per workgroup (64..1024, multiple of 64); 0 = default */
-    uint32_t tile;    /* edges per work tile; 0 = default */
+    uint32_t block;   /* SSSP: threads per workgroup of the push (256, 512 or 1024); 0 = default */
+    uint32_t tile;    /* SSSP: edges per work tile of the push; 0 = default */
     uint32_t width;   /* lanes per pass (32, 64, 128 or 256, <= B); 0 = default.  On a graph of 2^29 edges
                          or more a pass takes fewer where edges * width / 32 would not fit 32 bits */
-    uint32_t grid;    /* workgroups of the push; 0 = as many as are resident */
+    uint32_t grid;    /* SSSP: workgroups of the push; PPR: bounds the workgroups that complete the
+                         rows crossing tiles (the pull itself takes at least as many as are
+                         resident); 0 = default.  PPR ignores block, tile and width. */
 } gx_tune;
 
 /* Device workspace bytes gx_batch_run needs (excluding the output tile). */
@@ -472,7 +474,7 @@ gx_status gx_batch_bytes(const gx_graph *g, int32_t algo, uint32_t B, size_t *by
  * equals the plain solve from its source), PPR lanes for `iters`
  * supersteps with seed sources[b].  dev_out: [V x B] uint32 (SSSP) or
  * float32 (PPR), row-major (lane b of vertex v at v*B + b).  sources: B host
- * ids.  B: 1..1024 (SSSP: multiple of 32).  tune may be NULL.  Synchronises
+ * ids.  B: 1..256 (SSSP: multiple of 32).  tune may be NULL.  Synchronises
  * `stream`.
  */
 gx_status gx_batch_run(gx_graph *g, int32_t algo, const int32_t *sources, uint32_t B,

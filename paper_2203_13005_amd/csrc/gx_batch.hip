@@ -858,8 +858,10 @@ BpArgs bp_args_for(const DevGraph &d, const BpWork &w, float *x, uint32_t B, flo
 }
 
 // A superstep pulls when its units are at least 1 / BS_PULL_PART of all
-// (edge, group) pairs: the two benchmarked batches took 720 us and 14.8 ms
-// with 1/6, 714 us and 15.4 ms with 1/3, 778 us and 15.2 ms with 1/12.
+// (edge, group) pairs.  With 1/3, 1/6 and 1/12: 32 lanes, 50000 vertices 714, 720,
+// 778 us; 256 lanes, R-MAT scale 20 15.4, 14.8, 15.2 ms; scale 16 2.17, 2.00, 2.01 ms;
+// 64 lanes, scale 20 6.40, 6.40, 7.20 ms; uniform of 4 M edges, 256 lanes 13.8, 14.0,
+// 14.5 ms, 32 lanes 3.40, 3.46, 3.54; a 300 x 300 grid 24.6, 25.1, 25.6 ms.
 constexpr int64_t BS_PULL_PART = 6;
 
 BsArgs bs_args_for(const DevGraph &d, const BsWork &w, uint32_t *D, uint32_t B, uint32_t l0, uint32_t G) {
@@ -952,7 +954,9 @@ gx_status run_bsssp(gx_graph *g, const int32_t *dev_src, uint32_t B, BsWork &w, 
                            G);
         const BsArgs a = bs_args_for(d, w, D, B, l0, G);
         // supersteps in groups, one readback each (one past the end costs less
-        // than the wait for a readback)
+        // than the wait for a readback: groups of 6 and 6, 12 and 6, 20 and 12 take 535,
+        // 500, 450 us for 32 lanes on R-MAT scale 12 and 4.73, 4.71, 4.60 ms for 256 on
+        // scale 18)
         BsCtl ctl{};
         for (uint32_t k = 0, n = 12; ctl.steps == 0; n = 6) {
             for (const uint32_t to = k + n; k < to; k++)
@@ -1230,6 +1234,8 @@ extern "C" gx_status gx_batch_autotune(gx_graph *g, int32_t algo, const int32_t 
         }
         GX_CHECK_HIP(hipMemcpyAsync(bsw.src, sources, B * 4, hipMemcpyHostToDevice, s), g);
     } else {
+        // (the grid only bounds the workgroups that complete the rows crossing tiles: the
+        // pull takes every workgroup the CUs hold, the graph fixes its tiles)
         for (int frac : {1, 2, 4}) cands.push_back(gx_tune{256, BP_TILE, B, (uint32_t)(g->num_cus * frac)});
         GX_CHECK_HIP(hipMemcpyAsync(bpw.seed, sources, B * 4, hipMemcpyHostToDevice, s), g);
     }

@@ -139,6 +139,11 @@ inline int64_t pull_pack_cap(int64_t V, int64_t E) { return std::min(E, E / PULL
 // Row ends of the in-CSR (PageRank, batched PPR): rows without in-edges are
 // left out, a bit per in-edge marks the last one of its row.  The in-edges are cut into
 // tiles, rows that cross tiles are listed.
+// (A row of at least ROWS_LONG partials is summed by a wave, batched by a
+// workgroup, a piece per wave of it: with 32 every case takes the same; with 256
+// batched PPR of 5 lanes on R-MAT scale 17 takes 890 us for 20 supersteps, 790 so;
+// with no row cut, a star of 2 M vertices takes 1357 us for 20 PageRank supersteps,
+// 832 so, and one of 200 000 3.76 ms for 20 of batched PPR, 64 lanes, 1.30 so.)
 constexpr int ROWS_PIECES = 16;     // a sum of at least ROWS_LONG partials is cut into this many pieces
 constexpr int ROWS_LONG = 64;
 constexpr int ROWS_MID = 4;         // (a single step of loads covers fewer)
@@ -150,9 +155,13 @@ struct RowTiles {
     int32_t n_long = 0, n_mid = 0;     // with at least ROWS_MID
 };
 // Batched PPR, a lane group's tile: a graph of few edges has too few longer
-// ones to occupy the chip (100003 vertices, 1.6 M edges, 5 lanes: 1.7 ms with
-// 64, 2.2 with 128, 2.8 with 256); a large one saves partials (scale 20,
-// 64 lanes: 37.6, 35.8 and 34.0 ms, contributions by vertex then).
+// ones to occupy the chip, a large one saves partials, the more the wider the
+// batch.  20 supersteps with 64 and 256 in-edges: R-MAT scale 16 (1 M edges), 5
+// lanes 690 and 1455 us, 64 lanes 1.02 and 1.24 ms; scale 18 (4 M, the last below
+// the line) 5 lanes 1.20 and 1.73, 64 2.92 and 2.68, 128 4.68 and 4.60; scale 19,
+// 5 lanes 1.87 and 2.11, 64 6.24 and 5.25, 128 10.1 and 9.6; scale 20, 5 lanes 3.0 and
+// 3.74, 64 13.1 and 11.4; uniform, 6 M edges, 64 lanes 6.24 and 5.30.  (Up to 16 lanes
+// the shorter tile would be the better one above the line too.)
 inline int64_t bp_rows_tile(int64_t E) { return E >= (int64_t(1) << 22) ? 256 : 64; }
 constexpr int ROWS_DANGLING = 512;  // tiles of dangling vertices at most
 

@@ -61,7 +61,9 @@ __device__ __forceinline__ uint32_t lp_hash(uint32_t x) { return x * 0x9E3779B1u
 // step->list counts (entries << 32) | their neighbours.
 constexpr int LP_CHANGED_CHUNK = 1024;
 // A superstep after changes with more than E_sym / LP_DENSE neighbours
-// recomputes every vertex.
+// recomputes every vertex: marking nearly all costs more than it saves (15
+// iterations with 2, 4, 8, 16: R-MAT scale 20, shuffled ids 2.75, 2.67, 2.67, 2.67 ms,
+// as they are 1.52, 1.45, 1.45, 1.45; scale 16 570, 558, 550, 552 us).
 constexpr int64_t LP_DENSE = 4;
 
 struct LpStep {

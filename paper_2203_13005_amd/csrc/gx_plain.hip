@@ -424,10 +424,10 @@ __device__ __forceinline__ void push_body(const uint4 *__restrict__ list, const 
 //
 // Bound by the latency of dependent reads (entries, then values) and, in the
 // first pull of a solve, by the rate of random 4-byte reads.  R-MAT scale 22
-// (65 M in-edges), the six pulls of one solve: a sweep over every in-edge
-// record with racing stores and a fix-up pass took 250-280 us each; this one
-// 272, 197, 122, 95, 84 and 77 us.  Short rows of at most 16, 32, 64, 128:
-// 861, 847, 1060, 1104 us for the six.
+// (65 M in-edges), the four pulls of the benchmarked solve: 241, 132, 85 and
+// 75 us; the sweep takes 250-280 us for each there.  Short rows of at most 16, 32,
+// 64, 128 entries: 861, 847, 1060, 1104 us for six pulls of another solve, before
+// the frontier bits were kept in LDS.
 struct RowItems {
     uint32_t row[64], beg[64], end[64], best[64];
 };
@@ -597,7 +597,8 @@ __device__ __forceinline__ void pull_body(const PullArgs &pa, int64_t V, const u
     // rows, whose sources often neighbour each other too, share an L2), another
     // one in each group of 8: where rows get shorter with every bit set in their
     // id, as on R-MAT, a fixed one would give one XCD many times the others'
-    // entries (scale 22, first pull of a solve: 380 us, with the turn 335 us).
+    // entries (scale 22, first pull of a solve, in an earlier form: 380 us, with the
+    // turn 335 us).
     const uint32_t x = pull_slice(step, xcd_shift, rot);
     const int64_t nper = gridDim.x / PULL_SLICES;
     const int64_t nseg = pa.first_only ? 0 : (pa.nsegs + PULL_SEG_BLOCK - 1) / PULL_SEG_BLOCK;
@@ -1671,6 +1672,10 @@ static size_t state_layout(gx_graph *g, const gx_params *p, Carver &c, gx_state 
         s->cpart = c.take<uint32_t>(s->pr_parts);
         s->Dval = c.take<double>(1);
         const int units = PrFixUnits(d.pr_rows.n_cross, d.pr_rows.n_long, d.pr_rows.n_mid, s->pr_parts).all;
+        // a single workgroup where one holds the units; many small ones until their
+        // returning atomics queue (20 supersteps of R-MAT with 256 threads always, 1024
+        // always and by this rule: scale 14 280, 262, 260 us, 16 320, 398, 320, 18 563, 593,
+        // 564, 22 5.81, 5.65, 5.65 ms)
         s->pr_fix_block = units <= PR_FIX_BLOCK / 64 || units >= 1024 ? PR_FIX_BLOCK : 256;
         s->pr_fix_grid = std::min(PR_FIX_MAX_GRID, (units * 64 + s->pr_fix_block - 1) / s->pr_fix_block);
         s->fix_d = c.take<double>(s->pr_fix_grid);
@@ -1792,6 +1797,12 @@ extern "C" gx_status gx_state_init(gx_graph *g, const gx_params *p, void *dev_st
     if (p->algo == GX_SSSP || p->algo == GX_CC) {
         const DevGraph &dg = g->d;
         bool can_pull = p->algo == GX_SSSP ? dg.in_adj != nullptr : dg.sym_col != nullptr;
+        // The default is where the sweep meets the push (4 M vertices, 67 M uniform edges:
+        // a pull at 0.33 takes 305 us, a push at 0.27 306).  The row pull gets cheaper as
+        // a solve goes on and meets it lower, per superstep near 0.1 on R-MAT scales 18 to
+        // 22 and 0.2 on uniform graphs, but a solve has few supersteps between; whole solves at 0.1, 0.2 and 0.3 from three sources: R-MAT
+        // scale 18 374, 376, 377 us, 20 509, 520, 607, 22 1230, 1251, 1341, uniform of 1 M
+        // vertices and 16 M edges 1419, 1395, 1403; CC scale 22 443, 451, 458.
         double frac = p->pull_fraction > 0.f ? (double)p->pull_fraction : 0.3;
         double Eimg = (double)(p->algo == GX_SSSP ? dg.E : dg.E_sym);
         s->pull_edges = (!can_pull || frac >= 1.0) ? 0xFFFFFFFFu : (uint32_t)std::max(1.0, std::ceil(frac * Eimg));
