@@ -118,7 +118,9 @@ typedef struct gx_params {
     uint32_t timing;          /* nonzero: time the edge kernels of every superstep with HIP events */
     float    pull_fraction;   /* SSSP/CC: a superstep whose active out-edges exceed this fraction of
                                  all edges pulls (over the rows of in-edges, or over all in-edges
-                                 on large graphs without hubs) instead of pushing; 0 = default (0.3), >= 1 = always push */
+                                 on large graphs without hubs) instead of pushing; 0 = default
+                                 (0.3; SSSP on large sparse graphs without hubs: 1), >= 1 = always
+                                 push */
     uint32_t phases;          /* GX_PHASES_LOCAL or GX_PHASES_MASTERS (PageRank, SSSP, CC): the state
                                  is driven by the separate template calls gx_msg_gen / gx_msg_merge /
                                  gx_msg_apply in any order an upper system uses (BSP or GAS);

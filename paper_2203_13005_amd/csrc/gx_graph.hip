@@ -516,8 +516,16 @@ static bool byte_weights(const gx_graph_desc *d) {
 //     0.62, 0.88 and 0.68, 0.79; about one edge per vertex, 3 M and 4.2 M vertices,
 //     uniform: 2.80, 4.25 and 2.54, 3.63; 4.2 M, share 0.16: 2.33 and 2.42; 8.4 M,
 //     share 0.08: 6.9 and 7.4.
+//
+// SSSP on graphs of fewer than 3 edges per vertex gains from neither: a solve
+// takes some forty supersteps, few of them dense, and what a pull saves in those
+// is spent on keeping every vertex's snapshot in the others.  Row pull (at the
+// default fraction) against pushing only: 2^20 vertices of degree 2, share 0.29, 897
+// and 834 us; 2^22 of degree 1 1.68 and 1.47 ms, 2, shares 0.09, 0.28, 0.76: 1.76, 1.62,
+// 1.00 and 1.56, 1.43, 1.14 ms; 2^23 of degree 2, shares 0.05, 0.20, 0.67: 2.86, 3.18,
+// 1.48 and 2.42, 2.46, 1.70 ms.
 struct SweepRule {
-    bool in = false, sym = false;
+    bool in = false, sym = false, push = false;
 };
 static SweepRule sweep_rule(const gx_graph_desc *d) {
     SweepRule r;
@@ -543,6 +551,7 @@ static SweepRule sweep_rule(const gx_graph_desc *d) {
     const double share = (double)edges / (double)E;
     const double mv = (double)V / (double)SWEEP_V_MIN, degree = (double)E / (double)V;
     const bool large = mv >= 1.5;  // (below, the values nearly fit)
+    r.push = degree < 3 && share < 0.45;
     r.in = (d->needs & GX_NEED_OUT) && degree >= (large ? 3 : 12) && share * share * std::sqrt(degree) * mv < 0.8;
     const bool few = degree < 1.8 && large && mv < 6 && share * std::cbrt(mv) < 0.22;
     r.sym = (d->needs & GX_NEED_SYM) && (few || (degree >= (large ? 6 : 12) && share * std::cbrt(mv) < 0.38));
@@ -908,6 +917,7 @@ extern "C" gx_status gx_graph_load(const gx_graph_desc *desc, void *dev_arena, s
     g->d.n_packs = (int64_t)h.packs.size();
     g->d.sym_nsegs = (int64_t)h.sym_segs.size();
     g->d.sym_ascending = h.sym_ascending;
+    g->d.sssp_pushes = sweep.push;
     g->sweep_in_recs = std::move(h.sweep_in.recs);
     g->sweep_sym_recs = std::move(h.sweep_sym.recs);
     std::copy(h.sweep_in.uoff, h.sweep_in.uoff + PULL_SLICES + 1, g->d.sweep_in.uoff);

@@ -224,6 +224,7 @@ struct DevGraph {
     int64_t sym_nsegs = 0;
     // records of the sweep, on graphs where it is the faster pull
     Sweep sweep_in, sweep_sym;
+    bool sssp_pushes = false;  // SSSP pushes unless the caller names a pull fraction
     // partition metadata
     const int32_t *l2g = nullptr;          // nullptr = identity
     const uint32_t *remote_out = nullptr;  // bitmaps of W words (nullptr = none remote)

@@ -115,12 +115,13 @@ __global__ __launch_bounds__(256) void k_min_init(uint32_t *val, uint32_t *snap,
 // list entries one after another (scale-15 solve: 155 us against 212 us with
 // 16, together with idle pull workgroups leaving before they stage the
 // frontier bits; R-MAT scale 20: 436 us with 8, 515 with 16; scale 22: 1055 and
-// 1069).  It is COMPACT_WIDEST where half as many reservations count more: from
-// COMPACT_WIDEST_FROM vertices on, half of that on graphs of fewer than
-// COMPACT_SPARSE edges per vertex, whose many supersteps have active vertices
-// everywhere (with 8 and 16: 2^22 vertices of degree 1 1.78 and 1.64 ms, 2 1.80
-// and 1.71, 4 2.00 and 2.00; 2^23 of degree 2 3.19 and 3.05, 4 4.31 and 4.19; R-MAT
-// scale 23 of degree 8 1.58 and 1.58).
+// 1069, scale 23 of degree 8 1.58 and 1.60 ms; 16 leaves no registers for the slots).
+// Without slots it is COMPACT_WIDEST where half as many reservations count
+// more: from COMPACT_WIDEST_FROM vertices on, half of that on graphs of fewer
+// than COMPACT_SPARSE edges per vertex, whose many supersteps have active
+// vertices everywhere (SSSP with 8 and 16: 2^22 vertices of degree 1 1.61 and
+// 1.50 ms, 2 1.64 and 1.55, 3 1.86 and 1.81; 2^23 of degree 2 2.56 and 2.42, 4 4.32 and
+// 4.20; CC, R-MAT scale 23 of degree 8 755 and 742 us).
 constexpr int COMPACT_WIDE = 8, COMPACT_WIDEST = 16;
 constexpr int64_t COMPACT_WIDE_FROM = int64_t(1) << 20, COMPACT_WIDEST_FROM = int64_t(1) << 23;
 constexpr int64_t COMPACT_SPARSE = 4;
@@ -200,9 +201,7 @@ __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ 
     int32_t r[CVT + 1];
     uint32_t x[CVT];
     int32_t sl[CVT];
-    // (16 vertices leave no registers for the slots until the row pointers are counted)
-    constexpr bool SLOTS_EARLY = CVT <= COMPACT_WIDE;
-    const bool by_slot = snap_all && slot != nullptr;
+    const bool by_slot = CVT <= COMPACT_WIDE && snap_all && slot != nullptr;
 #pragma unroll
     for (int i = 0; i < CVT; i++) {
         r[i] = 0;
@@ -222,7 +221,7 @@ __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ 
                 x[4 * q] = b.x, x[4 * q + 1] = b.y, x[4 * q + 2] = b.z, x[4 * q + 3] = b.w;
             }
             r[CVT] = rp[u0 + CVT];
-            if (by_slot && SLOTS_EARLY)
+            if (by_slot)
 #pragma unroll
                 for (int q = 0; q < CVT / 4; q++) {
                     const int4 a = reinterpret_cast<const int4 *>(slot + u0)[q];
@@ -232,7 +231,7 @@ __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ 
 #pragma unroll
             for (int i = 0; i < CVT; i++) {
                 if (u0 + i < V) x[i] = val[u0 + i];
-                if (by_slot && SLOTS_EARLY && u0 + i < V) sl[i] = slot[u0 + i];
+                if (by_slot && u0 + i < V) sl[i] = slot[u0 + i];
                 if (u0 + i <= V) r[i] = rp[u0 + i];
             }
         }
@@ -266,10 +265,6 @@ __global__ __launch_bounds__(CBLOCK) void k_compact(const uint8_t *__restrict__ 
     // vertices (whole vectors; an inactive vertex's value is the one its
     // snapshot holds already).
     if (by_slot) {
-        if (!SLOTS_EARLY)
-#pragma unroll
-            for (int i = 0; i < CVT; i++)
-                if ((actmask >> i) & 1u) sl[i] = slot[u0 + i];
 #pragma unroll
         for (int i = 0; i < CVT; i++) {
             if (!((actmask >> i) & 1u)) continue;
@@ -1589,7 +1584,9 @@ static void launch_compact(gx_state *s, hipStream_t hs, const uint8_t *front, ui
                            uint8_t *dirty) {
     const DevGraph &d = s->g->d;
     const int64_t k = s->k + ahead;
-    const int cvt = d.V >= COMPACT_WIDEST_FROM || (2 * d.V >= COMPACT_WIDEST_FROM && d.E < COMPACT_SPARSE * d.V)
+    const bool slots = s->hot[0] && s->pull_edges != 0xFFFFFFFFu;
+    const int cvt = !slots && (d.V >= COMPACT_WIDEST_FROM ||
+                               (2 * d.V >= COMPACT_WIDEST_FROM && d.E < COMPACT_SPARSE * d.V))
                         ? COMPACT_WIDEST
                     : d.V >= COMPACT_WIDE_FROM ? COMPACT_WIDE : 4;
     auto kern = cvt == COMPACT_WIDEST ? k_compact<COMPACT_WIDEST>
@@ -1598,7 +1595,7 @@ static void launch_compact(gx_state *s, hipStream_t hs, const uint8_t *front, ui
                        clear, s->p.algo == GX_CC ? d.sym_rp : d.out_rp, s->val, s->snap, d.V, s->list, s->tile_start,
                        s->steps + (k % STEP_RING), s->steps + ((k + 1) % STEP_RING),
                        (int)(s->pull_edges != 0xFFFFFFFFu), prev, dirty, s->pull_edges, s->rot, s->relax_grid,
-                       s->hot[0] ? d.slot : nullptr, s->hot[k & 1], s->hot[(k + 1) & 1]);
+                       slots ? d.slot : nullptr, s->hot[k & 1], s->hot[(k + 1) & 1]);
 }
 
 // The pull of this graph's tiles (and the fewest workgroups that hold every
@@ -1800,10 +1797,13 @@ extern "C" gx_status gx_state_init(gx_graph *g, const gx_params *p, void *dev_st
         // The default is where the sweep meets the push (4 M vertices, 67 M uniform edges:
         // a pull at 0.33 takes 305 us, a push at 0.27 306).  The row pull gets cheaper as
         // a solve goes on and meets it lower, per superstep near 0.1 on R-MAT scales 18 to
-        // 22 and 0.2 on uniform graphs, but a solve has few supersteps between; whole solves at 0.1, 0.2 and 0.3 from three sources: R-MAT
-        // scale 18 374, 376, 377 us, 20 509, 520, 607, 22 1230, 1251, 1341, uniform of 1 M
-        // vertices and 16 M edges 1419, 1395, 1403; CC scale 22 443, 451, 458.
-        double frac = p->pull_fraction > 0.f ? (double)p->pull_fraction : 0.3;
+        // 22 and 0.2 on uniform graphs, but a solve has few supersteps between; whole
+        // solves at 0.1, 0.2 and 0.3 from three sources: R-MAT scale 18 374, 376, 377 us,
+        // 20 509, 520, 607, 22 1230, 1251, 1341, uniform of 1 M vertices and 16 M edges 1419,
+        // 1395, 1403; CC scale 22 443, 451, 458.  (A state that only pushes keeps no
+        // snapshots: the default where that is faster, see sweep_rule.)
+        const double usual = p->algo == GX_SSSP && dg.sssp_pushes ? 1.0 : 0.3;
+        double frac = p->pull_fraction > 0.f ? (double)p->pull_fraction : usual;
         double Eimg = (double)(p->algo == GX_SSSP ? dg.E : dg.E_sym);
         s->pull_edges = (!can_pull || frac >= 1.0) ? 0xFFFFFFFFu : (uint32_t)std::max(1.0, std::ceil(frac * Eimg));
     }
