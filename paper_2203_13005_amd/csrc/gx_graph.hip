@@ -499,7 +499,7 @@ static bool byte_weights(const gx_graph_desc *d) {
 
 // Symmetric adjacency: sorted union of out- and in-neighbours, self
 // excluded, duplicates removed (needs the in-CSR).
-// Whether SSSP and CC sweep on this graph.  From a million vertices on an L2
+// Whether SSSP and CC sweep on this graph.  From about a million vertices on an L2
 // no longer holds all values, and what counts is the share of the edges whose
 // source is among the PULL_BITS vertices with the most out-edges: the row pull
 // gains with it, the sweep does not, and a larger or denser graph needs more.
@@ -510,7 +510,9 @@ static bool byte_weights(const gx_graph_desc *d) {
 //     3.7 and 6.3, 5.2, 4.4, 3.9; 2^21 of degree 4, shares 0.13, 0.33, 0.39: 1.29,
 //     1.34, 1.21 and 1.19, 1.23, 1.16; 2^23 of degree 8, shares 0.03, 0.14, 0.19:
 //     10.8, 7.6, 6.1 and 7.0, 6.7, 6.3; degree 2, 2^22, share 0.09: 1.82 and 1.87;
-//     2^20 of degree 4, 16, 64, share 0.2: 0.81, 1.44, 3.4 and 0.87, 1.33, 2.7;
+//     2^20 of degree 4, 16, 64, share 0.2: 0.81, 1.44, 3.4 and 0.87, 1.33, 2.7; 2^19
+//     of degree 32, 64, 100, share 0.3: 1.16, 1.65, 1.98 and 1.13, 1.49, 1.94, of degree
+//     64, share 0.47: 1.34 and 1.33; 2^18 of degree 128: 1.06 and 1.20;
 //   CC, 2^22 of degree 16, the same shares: 7.2, 4.6, 2.6, 1.9 and 4.4, 3.1, 2.2, 2.0;
 //     2^22 of degree 4, share 0.07: 3.6 and 4.0; 2^20 of degree 8, 16, share 0.2:
 //     0.62, 0.88 and 0.68, 0.79; about one edge per vertex, 3 M and 4.2 M vertices,
@@ -549,12 +551,13 @@ static SweepRule sweep_rule(const gx_graph_desc *d) {
         left -= n;
     }
     const double share = (double)edges / (double)E;
-    const double mv = (double)V / (double)SWEEP_V_MIN, degree = (double)E / (double)V;
-    const bool large = mv >= 1.5;  // (below, the values nearly fit)
-    r.push = degree < 3 && share < 0.45;
-    r.in = (d->needs & GX_NEED_OUT) && degree >= (large ? 3 : 12) && share * share * std::sqrt(degree) * mv < 0.8;
+    const double mv = (double)V / (double)(1 << 20), degree = (double)E / (double)V;
+    const bool large = mv >= 1.5;  // (below, the values fit or nearly)
+    r.push = mv >= 1 && degree < 3 && share < 0.45;
+    r.in = (d->needs & GX_NEED_OUT) && degree >= (large ? 3 : mv >= 1 ? 12 : 32) &&
+           share * share * std::sqrt(degree) * mv < 0.8;
     const bool few = degree < 1.8 && large && mv < 6 && share * std::cbrt(mv) < 0.22;
-    r.sym = (d->needs & GX_NEED_SYM) && (few || (degree >= (large ? 6 : 12) && share * std::cbrt(mv) < 0.38));
+    r.sym = (d->needs & GX_NEED_SYM) && (few || (mv >= 1 && degree >= (large ? 6 : 12) && share * std::cbrt(mv) < 0.38));
     return r;
 }
 

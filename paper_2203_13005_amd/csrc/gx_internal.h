@@ -117,7 +117,7 @@ constexpr int SWEEP_BAND = 1 << SWEEP_BAND_BITS;
 constexpr int SWEEP_VT = 8;
 constexpr int SWEEP_UNIT = 8192;
 constexpr uint32_t SWEEP_SENTINEL = 0xFFFFFFFFu;  // destination of a padding record
-constexpr int64_t SWEEP_V_MIN = int64_t(1) << 20, SWEEP_V_MAX = int64_t(1) << 28;
+constexpr int64_t SWEEP_V_MIN = int64_t(1) << 19, SWEEP_V_MAX = int64_t(1) << 28;
 struct Sweep {
     const uint2 *rec = nullptr;    // {destination, (source mod SWEEP_BAND) << 8 | weight}; NULL: the row pull is used
     const uint4 *units = nullptr;  // {first record, records, first source of the band, 0}

@@ -69,10 +69,11 @@ def start(g, source):
 
 @pytest.mark.parametrize("V,E,weights", [(V1, 5_000_000, "mixed"), (V1 + 1, 5_000_000, "zero"), (V1 + 8191, 5_000_000, "equal"),
                                          (V1 + 8192, 6_000_000, "mixed"), (V0 + 63, 13_000_000, "mixed"),
+                                         (V0 // 2 + 1, 17_000_000, "mixed"),
                                          (V1 + 63, 5_000_000, "wide")])
 def test_sssp_sweep(gx, V, E, weights):
     g = uniform(V, E, weights, V)
-    assert g.E >= (3 if V >= V1 else 12) * V
+    assert g.E >= (3 if V >= V1 else 12 if V >= V0 else 32) * V
     source = int(np.argmax(np.diff(g.row_ptr)))
     dg = gx.DeviceGraph(g, gx.GX_NEED_OUT)
     cap = 400

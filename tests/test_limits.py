@@ -54,7 +54,7 @@ def test_chunk_ends_at_the_last_entries(tmp_path, chunk):
     assert [r[0] for r in run_cpp(tmp_path, body)] == [min(e, b + chunk) for b, e in cases]
 
 
-V0 = 1 << 20  # smallest vertex count that sweeps
+V0 = 1 << 20  # smallest vertex count that sweeps with 12 edges per vertex
 
 
 def arena_bytes(V, degree, hub_degree, need):
@@ -77,7 +77,7 @@ def test_which_graphs_sweep():
         n, E = arena_bytes(V, degree, hub_degree, b.GX_NEED_OUT)
         return n > 18.5 * E + 24 * V
 
-    assert sssp(V0, 12, 12) and not sssp(V0 - 1, 12, 12)
+    assert sssp(V0, 12, 12) and not sssp(V0 - 1, 12, 12) and sssp(V0 // 2, 32, 32) and not sssp(V0 // 2 - 1, 32, 32)
     assert not sssp(V0, 11, 11) and not sssp(3 * V0 // 2 - 1, 11, 11)  # sparse: from 1.5 * 2^20 vertices on
     assert sssp(3 * V0 // 2, 3, 3) and not sssp(2 * V0, 2, 2)
     assert not sssp(V0, 12, 84)  # 2^17 vertices are the sources of half the edges
